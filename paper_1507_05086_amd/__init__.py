@@ -68,6 +68,9 @@ class _RoundRecord(ctypes.Structure):
                 ("conflicts", ctypes.c_int64), ("eps_used", ctypes.c_double), ("t_ns", ctypes.c_int64)]
 
 
+_ROUND_DTYPE = np.dtype([(f, np.float64 if f == "eps_used" else np.int64) for f in TRACE_FIELDS])
+
+
 class _RunStats(ctypes.Structure):
     _fields_ = [("rounds", ctypes.c_int64), ("scanned_elect", ctypes.c_int64),
                 ("scanned_claim", ctypes.c_int64), ("scanned_peel", ctypes.c_int64),
@@ -241,8 +244,8 @@ def _run(fn, graph: Graph, order, eps, labels=None, trace_capacity=1 << 14, stre
     st = _RunStats()
     rec = None
     if trace_capacity > 0:
-        rec = (_RoundRecord * trace_capacity)()
-        st.trace = ctypes.cast(rec, ctypes.POINTER(_RoundRecord))
+        rec = np.empty(trace_capacity, dtype=_ROUND_DTYPE)  # only the rounds that ran are touched
+        st.trace = ctypes.cast(rec.ctypes.data, ctypes.POINTER(_RoundRecord))
         st.trace_capacity = trace_capacity
     st.max_rounds = int(max_rounds)
     st.fault_round = int(fault_round)
@@ -255,10 +258,7 @@ def _run(fn, graph: Graph, order, eps, labels=None, trace_capacity=1 << 14, stre
                    loop_ms=st.loop_ms, policy_fallback=st.policy_fallback,
                    truncated=st.truncated, graph_rounds=gr)
     if rec is not None:
-        k = min(st.rounds, trace_capacity)
-        dt = np.dtype([(f, np.float64 if f == "eps_used" else np.int64) for f in TRACE_FIELDS])
-        arr = np.frombuffer(bytes(rec)[: k * ctypes.sizeof(_RoundRecord)], dtype=dt) if k else np.zeros(0, dt)
-        out.trace = arr.copy()
+        out.trace = rec[:min(st.rounds, trace_capacity)].copy()
     return labels, out
 
 
