@@ -75,6 +75,15 @@ struct RoundGraph {
   hipGraphExec_t exec = nullptr;
 };
 
+// What a run leaves for the host, copied in one go: the control block, the
+// error word after the labels are written, and the first rounds' records.
+constexpr int64_t kHostTrace = 512;
+struct HostOut {
+  Ctrl ctrl;
+  int error;
+  RoundRec trace[kHostTrace];
+};
+
 // Device workspace of a run (allocated on the first run of a graph).
 struct Workspace {
   bool ready = false;
@@ -97,6 +106,7 @@ struct Workspace {
   unsigned long long *tstat = nullptr;
   int64_t tstat_cap = 0;
   Ctrl *ctrl = nullptr;
+  TeamCtl *team = nullptr;
   RoundRec *trace = nullptr;
   int64_t trace_cap = 0;
   int32_t *order_buf = nullptr, *label_buf = nullptr, *iorder = nullptr;
@@ -109,12 +119,13 @@ struct Workspace {
   SchedKey sched_key;      // the practical schedule the sched buffer holds, if any
   int64_t sched_len = 0;   // its length
   float *mlp = nullptr;
-  int *host_flags = nullptr;  // pinned: the device error word, read after the labels are finalized
+  HostOut *host = nullptr;    // pinned: what the host reads when a run has ended
   unsigned long long *progress = nullptr;  // pinned, coherent: k_close's progress word
   unsigned long long *progress_dev = nullptr;  // the same word as the device addresses it
   int32_t *cost_size = nullptr;
   long long *cost_acc = nullptr;
   int *dev_err = nullptr;
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around a run's rounds
   hipStream_t cap = nullptr;  // private stream the round groups are captured on
   std::vector<RoundGraph> graphs;
 };
@@ -170,11 +181,13 @@ namespace {
 void free_ws(Workspace &w) {
   void *ptrs[] = {w.rank, w.lab, w.ub, w.unc, w.state, w.flag, w.alist, w.clist, w.nlist, w.blist,
                   w.awork, w.cwork, w.rlist, w.xlist, w.rwork, w.xwork, w.racc, w.lvl, w.hist, w.plist, w.pwork,
-                  w.cedge, w.tstat, w.ctrl, w.trace, w.order_buf, w.label_buf, w.sched, w.mlp, w.ainfo, w.cinfo,
+                  w.cedge, w.tstat, w.ctrl, w.team, w.trace, w.order_buf, w.label_buf, w.sched, w.mlp, w.ainfo, w.cinfo,
                   w.iorder, w.cost_size, w.cost_acc, w.dev_err, w.bpos, w.bpend, w.bdec, w.bdep, w.bq, w.bradj, w.omap_buf, w.ccol, w.cend};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
-  if (w.host_flags) (void)hipHostFree(w.host_flags);
+  if (w.host) (void)hipHostFree(w.host);
+  if (w.ev0) (void)hipEventDestroy(w.ev0);
+  if (w.ev1) (void)hipEventDestroy(w.ev1);
   if (w.progress) (void)hipHostFree(w.progress);
   for (RoundGraph &g : w.graphs)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -218,7 +231,7 @@ int32_t ensure_ws(cc_graph *g) {
   HIP_TRY(dalloc(&w.ub, n));
   HIP_TRY(dalloc(&w.unc, (size_t)(n + 31) / 32));
   HIP_TRY(dalloc(&w.state, n));
-  HIP_TRY(dalloc(&w.flag, n));
+  HIP_TRY(dalloc(&w.flag, n + 3));  // marked by whole words
   HIP_TRY(dalloc(&w.alist, n));
   HIP_TRY(dalloc(&w.clist, n));
   HIP_TRY(dalloc(&w.nlist, n));
@@ -250,6 +263,7 @@ int32_t ensure_ws(cc_graph *g) {
   HIP_TRY(dalloc(&w.tstat, (size_t)w.tstat_cap));
   HIP_TRY(hipMemset(w.tstat, 0, sizeof(unsigned long long) * (size_t)w.tstat_cap));
   HIP_TRY(dalloc(&w.ctrl, 1));
+  HIP_TRY(dalloc(&w.team, 1));
   w.trace_cap = 1 << 16;
   HIP_TRY(dalloc(&w.trace, (size_t)w.trace_cap));
   HIP_TRY(dalloc(&w.order_buf, n));
@@ -267,7 +281,9 @@ int32_t ensure_ws(cc_graph *g) {
   HIP_TRY(dalloc(&w.cost_size, n));
   HIP_TRY(dalloc(&w.cost_acc, 2 * (size_t)g->num_graphs));
   HIP_TRY(dalloc(&w.dev_err, 1));
-  HIP_TRY(hipHostMalloc((void **)&w.host_flags, 8 * sizeof(int), hipHostMallocDefault));
+  HIP_TRY(hipHostMalloc((void **)&w.host, sizeof(HostOut), hipHostMallocDefault));
+  HIP_TRY(hipEventCreate(&w.ev0));
+  HIP_TRY(hipEventCreate(&w.ev1));
   HIP_TRY(hipHostMalloc((void **)&w.progress, sizeof(unsigned long long), hipHostMallocCoherent | hipHostMallocMapped));
   HIP_TRY(hipHostGetDevicePointer((void **)&w.progress_dev, w.progress, 0));
   w.ready = true;
@@ -461,58 +477,65 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
   w.max_rounds = stats ? stats->max_rounds : 0;
   w.fault_round = stats ? stats->fault_round : 0;
   w.progress = ws.progress_dev;
+  // a team's item counts are 32-bit; TEAM_MAX_N and TEAM_SOLO say where each pays
+  w.team_n = n > TEAM_MAX_N || g->nnz >= ((int64_t)1 << 31) ? 0 : n + g->nnz <= TEAM_SOLO ? 1 : TEAM_MAX;
+  w.team = w.team_n > 0 ? ws.team : nullptr;
+  // exact degrees from the start where the lazy search would switch to them
+  // in its first round anyway, and on graphs too small for it to pay
+  w.start_exact = pol.kind != CC_EPS_BINOMIAL &&
+                  (g->nnz <= TEAM_EXACT || ceilf(band_factor(0) * (float)g->max_deg) < (float)SWL);
+  if (w.start_exact) {
+    w.xcol = g->rcol;
+    w.xend = g->roff + 1;
+  }
+
+  w.solo = w.team_n == 1 && (w.start_exact || pol.kind == CC_EPS_BINOMIAL);
+  if (w.team_n == 1 && !w.solo) w.team_n = TEAM_MAX;
+  const bool solo = w.solo != 0;
+  w.labels_out = (flags & CC_OUTPUT_ON_DEVICE) ? labels : ws.label_buf;
 
   // init.  The permutation check needs no host round trip: an entry out of
   // range is never used as an index, and a failed check sets the device
   // error, which ends the run in its first k_close; every later kernel of
   // the call then returns at once.
   __atomic_store_n(ws.progress, 0ull, __ATOMIC_RELEASE);  // nothing of this handle is in flight
-  HIP_TRY(hipMemsetAsync(ws.ctrl, 0, sizeof(Ctrl), s));
-  if (w.order_mapped) {
-    HIP_TRY(launch_order_map(ws.omap, d_order, g->perm, n, ws.iorder, ws.ctrl, s));
-  } else {
-    HIP_TRY(hipMemsetAsync(ws.state, 0, (size_t)n, s));  // k_check_order marks the vertices pi names
+  if (!w.solo) {
+    HIP_TRY(hipMemsetAsync(ws.ctrl, 0, sizeof(Ctrl), s));
+    if (w.order_mapped) {
+      HIP_TRY(launch_order_map(ws.omap, d_order, g->perm, n, ws.iorder, ws.ctrl, s));
+    } else {
+      HIP_TRY(hipMemsetAsync(ws.state, 0, (size_t)n, s));  // k_check_order marks the vertices pi names
+    }
+    HIP_TRY(hipMemsetAsync(ws.hist, 0, sizeof(int) * (size_t)ws.hist_len, s));
+    if (g->lvl_total > 0)
+      HIP_TRY(hipMemcpyAsync(ws.lvl, g->lvl_init, sizeof(int32_t) * (size_t)g->lvl_total, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(launch_init(w, g->lvl_cnt0, s));
   }
-  HIP_TRY(hipMemsetAsync(ws.hist, 0, sizeof(int) * (size_t)ws.hist_len, s));
-  if (g->lvl_total > 0)
-    HIP_TRY(hipMemcpyAsync(ws.lvl, g->lvl_init, sizeof(int32_t) * (size_t)g->lvl_total, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(launch_init(w, g->lvl_cnt0, s));
 
-  LaunchShape ls{512, 1024, 512, 0, 0};
-  int64_t launched = 0;
+  LaunchShape ls{512, 1024, 512, 0, w.start_exact};
   // the fixed rule clusters a vertex every round; the practical schedule's
   // rounds may be empty, and it has as many as it drew
   const int64_t round_limit = pol.kind == CC_EPS_BINOMIAL ? std::max<int64_t>(n, w.sched_len) : n;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  HIP_TRY(hipEventCreate(&ev0));
-  HIP_TRY(hipEventCreate(&ev1));
-  struct EvGuard {
-    hipEvent_t a, b;
-    ~EvGuard() {
-      (void)hipEventDestroy(a);
-      (void)hipEventDestroy(b);
-    }
-  } evg{ev0, ev1};
+  const hipEvent_t ev0 = ws.ev0, ev1 = ws.ev1;
   HIP_TRY(hipEventRecord(ev0, s));
-  // Two groups of rounds stay queued: while one runs, the host waits on the
-  // progress word for the older one and queues the next.  The device never
-  // idles on the host, and a finished run leaves at most one group and the
-  // rest of the current one (all kernels return at once) behind it.
-  if (int32_t rc = launch_rounds(ws, w, ls, kRoundGroup, s)) return rc;
-  launched = kRoundGroup;
-  for (;;) {
-    const int64_t older = launched;
-    if (int32_t rc = launch_rounds(ws, w, ls, kRoundGroup, s)) {
-      (void)hipStreamSynchronize(s);  // nothing of this call may still write the progress word
-      return rc;
-    }
-    launched += kRoundGroup;
-    bool done = false;
+  // A launch is a round slot with a team in it, or a graph of kRoundGroup
+  // rounds.  Without a team, and while the team has nothing to run, two
+  // launches are queued: while one runs, the host waits on the progress word
+  // for the older one and queues the next, so the device never idles on the
+  // host, and a finished run leaves little behind it (all kernels return at
+  // once).  A team runs many rounds as a rule, so nothing is queued behind it.
+  const int64_t per = w.team ? 1 : kRoundGroup;
+  int64_t launched = 0, finished = 0, depth = w.team ? 1 : 2;
+  bool done = false;
+  // Waits until `slots` slots are finished or the run is done.
+  auto wait_slots = [&](int64_t slots) -> int32_t {
     for (unsigned spin = 1;; spin++) {
       const unsigned long long p = __atomic_load_n(ws.progress, __ATOMIC_ACQUIRE);
       done = (p >> PROGRESS_DONE & 1) || (p >> PROGRESS_ERROR & 1);
       if (p >> PROGRESS_EXACT & 1) ls.exact_seen = 1;
-      if (done || (int64_t)(p & 0xFFFFFFFFull) >= older) break;
+      if (w.team) depth = (p >> PROGRESS_RAN & 1) ? 1 : 2;
+      finished = (int64_t)(p & 0xFFFFFFFFull);
+      if (done || finished >= slots) return CC_OK;
       if (spin % 64 == 0) {
         const hipError_t q = hipStreamQuery(s);
         if (q != hipErrorNotReady) {  // drained: read the state itself
@@ -522,25 +545,51 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
           HIP_TRY(hipStreamSynchronize(s));
           done = now.done || now.error;
           if (now.phase == PHASE_EXACT) ls.exact_seen = 1;
-          break;
+          finished = launched;
+          return CC_OK;
         }
       }
       std::this_thread::yield();
     }
-    if (done) break;
-    if (launched > round_limit + 4 * kRoundGroup) {  // a backstop: the device stops a runaway loop itself
+  };
+  if (w.team) {  // the first slot is a team alone
+    HIP_TRY(launch_team(w, s));
+    w.solo = 0;  // what a solo run leaves (more conflict edges than fit its LDS) is for the device and a team
+    if (w.team_n == 1) w.team_n = TEAM_MAX;
+    launched = 1;
+    if (int32_t rc = wait_slots(1)) return rc;
+  }
+  const bool labelled = solo && done;  // the team has written the labels
+  while (!done) {
+    do {
+      if (int32_t rc = launch_rounds(ws, w, ls, per, s)) {
+        (void)hipStreamSynchronize(s);  // nothing of this call may still write the progress word
+        return rc;
+      }
+      launched += per;
+    } while (launched - finished < depth * per);
+    if (int32_t rc = wait_slots(launched - (depth - 1) * per)) return rc;
+    if (!done && launched > round_limit + 4 * kRoundGroup) {  // a backstop: the device stops a runaway loop itself
       (void)hipStreamSynchronize(s);
       return fail(CC_ERR_NO_PROGRESS, "round loop exceeded its round limit");
     }
   }
   HIP_TRY(hipEventRecord(ev1, s));
-  Ctrl hc;
-  HIP_TRY(hipMemcpyAsync(&hc, ws.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-  // labels go to the workspace first and reach the caller only on success,
-  // so a failed run leaves the caller's buffer untouched
-  HIP_TRY(launch_finalize(w, ws.label_buf, s));
-  HIP_TRY(hipMemcpyAsync(ws.host_flags, &ws.ctrl->error, sizeof(int), hipMemcpyDeviceToHost, s));
+  HostOut &out = *ws.host;
+  const int64_t want = stats ? std::min(stats->trace_capacity, ws.trace_cap) : 0;  // records asked for
+  HIP_TRY(hipMemcpyAsync(&out.ctrl, ws.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+  if (want > 0)
+    HIP_TRY(hipMemcpyAsync(out.trace, ws.trace, sizeof(RoundRec) * (size_t)std::min(want, kHostTrace),
+                           hipMemcpyDeviceToHost, s));
+  out.error = 0;
+  if (!labelled) {
+    // labels go to the workspace first and reach the caller only on success,
+    // so a failed run leaves the caller's buffer untouched
+    HIP_TRY(launch_finalize(w, ws.label_buf, s));
+    HIP_TRY(hipMemcpyAsync(&out.error, &ws.ctrl->error, sizeof(int), hipMemcpyDeviceToHost, s));
+  }
   HIP_TRY(hipStreamSynchronize(s));
+  const Ctrl &hc = out.ctrl;
   if (hc.error) {
     const int e = hc.error;
     if (e == ERR_PERM) return fail(CC_ERR_NOT_PERMUTATION, "order is not a permutation of 0..n-1");
@@ -549,10 +598,13 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     if (e == ERR_INJECTED) return fail(CC_ERR_DEVICE, "device error injected by stats->fault_round");
     return fail(CC_ERR_DEVICE, "device error " + std::to_string(e) + " in the round loop");
   }
-  if (ws.host_flags[0]) return fail(CC_ERR_DEVICE, "device error " + std::to_string(ws.host_flags[0]) + " while finishing");
-  HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n,
-                         (flags & CC_OUTPUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  if (out.error) return fail(CC_ERR_DEVICE, "device error " + std::to_string(out.error) + " while finishing");
+  const bool on_dev = (flags & CC_OUTPUT_ON_DEVICE) != 0;
+  if (!labelled || !on_dev) {
+    HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n,
+                           on_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
   if (stats) {
     stats->rounds = hc.round;
     if (stats->graph_rounds) stats->graph_rounds[0] = (int32_t)hc.round;
@@ -570,13 +622,18 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     stats->truncated = (hc.round > stats->trace_capacity || hc.round > ws.trace_cap) ? 1 : 0;
     const int64_t ncopy = stats->trace_capacity < have ? stats->trace_capacity : have;
     if (ncopy > 0) {
-      std::vector<RoundRec> rr((size_t)ncopy);
-      HIP_TRY(hipMemcpy(rr.data(), ws.trace, sizeof(RoundRec) * (size_t)ncopy, hipMemcpyDeviceToHost));
+      std::vector<RoundRec> rest;
+      const RoundRec *rr = out.trace;
+      if (ncopy > kHostTrace) {
+        rest.resize((size_t)ncopy);
+        HIP_TRY(hipMemcpy(rest.data(), ws.trace, sizeof(RoundRec) * (size_t)ncopy, hipMemcpyDeviceToHost));
+        rr = rest.data();
+      }
       int khz = 100000;
       if (int32_t rc = wall_clock_khz(&khz)) return rc;
       for (int64_t i = 0; i < ncopy; i++) {
         cc_round_record &o = stats->trace[i];
-        const RoundRec &r = rr[(size_t)i];
+        const RoundRec &r = rr[i];
         o.n_i = r.n_i;
         o.delta_i = r.delta_i;
         o.b_i = r.b_i;

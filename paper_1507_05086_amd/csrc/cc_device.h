@@ -43,6 +43,9 @@ enum : int { ALGO_C4 = 0, ALGO_CW = 1 };
 enum : int { POL_FIXED = 0, POL_LEARNED = 1, POL_TRACE = 2, POL_BINOMIAL = 3 };
 enum : int { ERR_NONE = 0, ERR_PERM = 5, ERR_NO_PROGRESS = 8, ERR_OVERFLOW = 11, ERR_LABEL = 12, ERR_INJECTED = 13 };
 enum : int { PHASE_LAZY = 0, PHASE_EXACT = 1 };
+// The part of the current round from which the round kernels have to run it:
+// nothing (k_team takes the round), all of it, or what k_team has left.
+enum : int { ST_TEAM = 0, ST_SELECT = 1, ST_ELECT = 2, ST_CLASSIFY = 3, ST_DELTA = 4 };
 
 // A list is packed in one 64-bit counter: (total weight << 31) | count, so a
 // single atomic reserves both a slot range and its weight range, and the
@@ -65,7 +68,8 @@ struct RoundRec {  // mirrors cc_round_record
 // idle kernel cost).
 struct CtrlHead {
   int done;                  // the run is finished (or failed)
-  int phase;                 // PHASE_LAZY (upper bounds) or PHASE_EXACT (exact degrees)
+  int16_t phase;             // PHASE_LAZY (upper bounds) or PHASE_EXACT (exact degrees)
+  int16_t stage;             // ST_*: where the round kernels take up the round
   unsigned int n_blocked;    // C4: blocked active vertices of this round
   unsigned int n_cedges;     // C4: conflict edges listed this round
   long long delta;           // Delta_i of the current round
@@ -82,7 +86,7 @@ struct CtrlHead {
 struct Ctrl {
   // ---- the head (same layout as CtrlHead) ----
   int done;
-  int phase;
+  int16_t phase, stage;
   unsigned int n_blocked, n_cedges;
   long long delta;
   long long b;
@@ -103,7 +107,8 @@ struct Ctrl {
   int select_done;         // per round: the active set is complete
   double eps_used;         // eps behind b
   float feat_conf, feat_claim, feat_eps;  // previous-round features for the learned policy
-  int pad1;
+  float rate;              // entries walked per active vertex in the last round
+  int slots;               // round slots (the round kernels, k_team if there is one) the device has finished
   long long t_start;       // wall clock at round start
   unsigned long long conflicts;  // per round: ClusterWild! conflict marks counted by k_clear
   unsigned long long x_low[64];  // adjacency entries of the lower-degree rows recounted at the switch (spread)
@@ -120,6 +125,7 @@ struct Ctrl {
 };
 static_assert(sizeof(CtrlHead) == 128, "the head is one 128-byte line");
 static_assert(offsetof(Ctrl, done) == offsetof(CtrlHead, done) && offsetof(Ctrl, phase) == offsetof(CtrlHead, phase) &&
+                  offsetof(Ctrl, stage) == offsetof(CtrlHead, stage) &&
                   offsetof(Ctrl, n_blocked) == offsetof(CtrlHead, n_blocked) &&
                   offsetof(Ctrl, n_cedges) == offsetof(CtrlHead, n_cedges) &&
                   offsetof(Ctrl, delta) == offsetof(CtrlHead, delta) && offsetof(Ctrl, b) == offsetof(CtrlHead, b) &&
@@ -159,6 +165,52 @@ struct RowInfo {
   int64_t start;
   int32_t deg;
   int32_t rank;
+};
+
+// What k_team takes (one XCD, an eighth of the device).  A round with more
+// positions to pass, or more to walk, is a matter of throughput and runs on
+// the whole device; so does the rest of a round whose Delta candidates or
+// level entries turn out longer.  A round costs 20 - 45 us on a team and 70 -
+// 100 us as kernels while it is short.  Measured (median call, team limits
+// varied): TEAM_ITEMS 2^17 / 2^18 / 2^19: power law 2 M ClusterWild! 6.3 /
+// 5.5 / 5.6 ms, R-MAT 22 under the learned policy 3.59 / 3.73 / 3.83 ms,
+// R-MAT 23 C4 11.6 / 11.1 / 11.0 ms; TEAM_WORK 2^20 / 2^22: R-MAT 23 C4 11.1 /
+// 11.8 ms; TEAM_POS 2^16 / 2^18 / 2^20: R-MAT 22 C4 9.1 / 7.65 / 7.65 ms,
+// learned 3.8 / 3.7 / 4.0 ms.  Graphs above TEAM_MAX_N vertices stay with the
+// kernels: R-MAT 23 C4 13.4 -> 11.1 ms, but R-MAT 24 14.1 -> 14.2 and R-MAT 26
+// (C4 + ClusterWild!) 56.6 -> 61 ms.
+constexpr int64_t TEAM_MAX_N = int64_t(1) << 23;
+constexpr long long TEAM_POS = 1 << 18;     // positions of pi to pass
+constexpr long long TEAM_ITEMS = 1 << 18;   // entries that claims and peeling are expected to walk
+constexpr long long TEAM_WORK = 1 << 20;    // entries of a Delta pass's candidates
+constexpr long long TEAM_SCAN = 1 << 18;    // entries of the bound levels to look through
+// A graph of at most this many vertices and stored entries runs whole in one
+// workgroup (SOLO): C4 on 517 vertices and 14 K entries takes 256 us so, 356
+// us on 8 workgroups and 377 us on 32; ClusterWild! on 5 K and 60 K, 467, 446
+// and 468 us.
+constexpr int64_t TEAM_SOLO = 48 * 1024;
+// Up to this many stored entries a run keeps exact degrees from the start
+// (no Delta passes, no switch).  On a power-law graph of 4 M entries that
+// costs more than it saves: 8.9 against 2.2 ms.
+constexpr int64_t TEAM_EXACT = 1 << 17;
+
+// k_team: workgroups, and what one of its rounds counts (four in turn).
+constexpr int TEAM_NT = 512;       // threads of a workgroup
+constexpr int TEAM_MAX = 32;       // workgroups: the compute units of one XCD
+struct TeamSlot {
+  unsigned long long a_pack, c_pack, r_pack[DITER];  // long active rows / promoted / rescan lists
+  unsigned long long listed;  // active vertices with a row (low half), settled alone (high half)
+  unsigned long long claimed; // newly claimed (low half), entries walked by claims and peeling (high half)
+  long long r_last;
+  int d_max[DITER];
+  int err;
+  unsigned n_cedges, n_blocked, conflicts;
+};
+struct TeamCtl {  // zero when k_team starts
+  unsigned pick, reg, size;    // the XCD (id + 1), registrations (top bit: closed), members
+  unsigned arrive, gen, abort; // the barrier
+  unsigned tcnt[2][64];        // unclustered positions found by each workgroup
+  TeamSlot slot[4];
 };
 
 struct Ws {
@@ -220,13 +272,19 @@ struct Ws {
   float eps_min, eps_max;
   int64_t max_rounds;   // > 0: stop after this many rounds (partial run)
   int64_t fault_round;  // > 0: test hook, the loop reports a device error after this round
+  TeamCtl *team;        // null: the round kernels run every round
+  int team_n;           // workgroups of k_team (1: it runs whole runs by itself)
+  int solo;             // team_n == 1: k_team also sets the run up and writes the labels
+  int32_t *labels_out;  // solo: where they go
+  int start_exact;      // the run starts with exact degrees (xcol / xend are the full rows)
   // progress word in pinned host memory, written by k_close at the end of
-  // every round: rounds finished (bits 0..31), done (32), exact phase (33),
-  // error (34)
+  // every round slot: slots finished (bits 0..31), done (32), exact phase
+  // (33), error (34); by k_team where there is one, which also says whether it
+  // leaves a round to the round kernels (35) and has run one itself (36)
   unsigned long long *progress;
 };
 
-constexpr int PROGRESS_DONE = 32, PROGRESS_EXACT = 33, PROGRESS_ERROR = 34;
+constexpr int PROGRESS_DONE = 32, PROGRESS_EXACT = 33, PROGRESS_ERROR = 34, PROGRESS_LEFT = 35, PROGRESS_RAN = 36;
 
 __host__ __device__ inline int level_of(int64_t x) {  // floor(log2(x)), x >= 1
   int l = 0;

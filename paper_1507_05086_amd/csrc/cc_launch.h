@@ -16,6 +16,8 @@ struct LaunchShape {
 
 hipError_t launch_init(const Ws &w, const unsigned *lvl_init_cnt, hipStream_t s);
 hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls);
+// Rounds on one XCD (cc_team.hip) until one is for the whole device; w.team set.
+hipError_t launch_team(const Ws &w, hipStream_t s);
 hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s);
 
 // Graph set-up: row-weight prefix wall[n+1] (the "all rows" list of the

@@ -28,21 +28,10 @@
 // edge-by-edge peeling starts only when little of the graph is left.
 #include "cc_device.h"
 #include "cc_launch.h"
+#include "cc_round.h"
 #include "cc_walk.h"
 
 namespace ccd {
-
-// Per-row partial counts of rows split across tiles: one 64-bit atomic adds
-// (items covered << 32 | count); the contributor that completes the row
-// (covered == degree) owns the total.
-__device__ inline bool row_combine(unsigned long long *acc, int64_t slot, int cnt, int64_t covered, int32_t deg,
-                                   int *total) {
-  const unsigned long long add = ((unsigned long long)covered << 32) | (unsigned)cnt;
-  const unsigned long long tot = atomicAdd(&acc[slot], add) + add;
-  if ((int64_t)(tot >> 32) != (int64_t)deg) return false;
-  *total = (int)(tot & 0xFFFFFFFFu);
-  return true;
-}
 
 // ------------------------------------------------------------------ init --
 
@@ -74,6 +63,9 @@ __global__ void __launch_bounds__(BS) k_check_order(Ws w) {
 __global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt) {
   const int64_t n = w.n;
   const int64_t end = (w.order_mapped && w.max_rounds == 0) ? w.iso_start : n;
+  __shared__ int s_hist[HLDS];
+  for (int i = threadIdx.x; i < HLDS; i += BS) s_hist[i] = 0;
+  __syncthreads();
   for (int64_t v = (int64_t)blockIdx.x * BS + threadIdx.x; v < end; v += (int64_t)gridDim.x * BS) {
     if (!w.order_mapped && w.state[v] != ORDER_SEEN) set_error(w.ctrl, ERR_PERM);  // no entry of pi names v
     w.lab[v] = INF;
@@ -81,7 +73,12 @@ __global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt)
     w.state[v] = UNCL;
     w.flag[v] = 0;
     w.ub[v] = (int32_t)(w.off[v + 1] - w.off[v]);
+    if (w.start_exact) hist_add(s_hist, w.hist, w.ub[v], 1);
   }
+  __syncthreads();
+  if (w.start_exact)
+    for (int i = threadIdx.x; i < HLDS; i += BS)
+      if (s_hist[i]) atomicAdd(&w.hist[i], s_hist[i]);
   const int64_t nw = (n + 31) / 32;
   for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < nw; i += (int64_t)gridDim.x * BS) {
     const int64_t rem = n - i * 32;
@@ -94,128 +91,13 @@ __global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt)
       c->n_rem = n;
       c->n_start = n;
       c->done = (n == 0);
-      c->phase = PHASE_LAZY;
+      c->phase = w.start_exact ? PHASE_EXACT : PHASE_LAZY;
       c->feat_eps = (float)w.eps;
+      // an active vertex claims a row of neighbours; with exact degrees, each of their rows is peeled
+      const float deg = w.iso_start > 0 ? (float)w.off[n] / (float)w.iso_start : 0.f;
+      c->rate = w.start_exact ? deg + deg * deg : deg;
     }
   }
-}
-
-// ------------------------------------------------------------ policy ------
-
-__device__ inline long long fixed_batch(long long eps_q, long long n_rem, long long delta) {
-  if (delta <= 0) return n_rem;
-  const long long num = eps_q * n_rem, den = 1000000LL * delta;
-  long long b = (num + den - 1) / den;
-  if (b < 1) b = 1;
-  if (b > n_rem) b = n_rem;
-  return b;
-}
-
-// Learned policy: eps = clamp(exp(w2 . relu(W1 x + b1) + b2)).  Wave 0 only;
-// lane j computes hidden unit j.  Returns false on a non-finite output.
-__device__ inline bool mlp_eps(const Ws &w, const float x[6], float *eps_out) {
-  const float *W1 = w.mlp, *b1 = w.mlp + 64 * 6, *w2 = b1 + 64, *b2 = w2 + 64;
-  const int j = lane_id();
-  float h = b1[j];
-#pragma unroll
-  for (int k = 0; k < 6; k++) h = fmaf(W1[j * 6 + k], x[k], h);
-  h = h > 0.f ? h : 0.f;
-  float y = w2[j] * h;
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) y += __shfl_xor(y, d, 64);
-  y += b2[0];
-  if (!isfinite(y)) return false;
-  float e = expf(y);
-  e = fminf(fmaxf(e, w.eps_min), w.eps_max);
-  *eps_out = e;
-  return isfinite(e);
-}
-
-// Delta-hat of round i under the practical schedule: Delta_0 halved every
-// bin_period rounds (rounded down, as the trace records it).
-__device__ inline long long delta_hat(const Ws &w, long long round) {
-  const long long h = round / w.bin_period;
-  return h >= 63 ? 0 : (long long)w.max_deg >> h;
-}
-
-// Sizes the next round; called by all lanes of wave 0 with the same values.
-__device__ void next_batch(const Ws &w, long long n_rem, long long delta, long long round, float fconf,
-                           float fclaim, float feps, long long *b_out, double *eps_out, int *fallback) {
-  long long b = 0;
-  double eps_used = w.eps;
-  bool have = false;
-  if (w.policy == POL_BINOMIAL) {  // round < sched_len: checked by the caller
-    b = w.sched[round];
-    eps_used = w.eps;
-    have = true;
-  } else if (w.policy == POL_TRACE && round < w.sched_len) {
-    b = w.sched[round];
-    if (b > n_rem) b = n_rem;
-    eps_used = delta > 0 ? (double)b * (double)delta / (double)n_rem : 0.0;
-    have = true;
-  } else if (w.policy == POL_LEARNED) {
-    float x[6] = {logf((float)n_rem), logf((float)(delta > 1 ? delta : 1)), fconf, fclaim, feps, (float)round};
-    float e = 0.f;
-    if (mlp_eps(w, x, &e)) {
-      const long long q = (long long)((double)e * 1e6 + 0.5);
-      b = fixed_batch(q > 0 ? q : 1, n_rem, delta);
-      eps_used = (double)e;
-      have = true;
-    } else {
-      *fallback = 1;
-    }
-  }
-  if (!have) b = fixed_batch(w.eps_q, n_rem, delta);
-  *b_out = b;
-  *eps_out = eps_used;
-}
-
-// ------------------------------------------------- lazy Delta search -----
-// Pass j rescans every candidate whose bound is >= L_j = ceil(f_j * T_j)
-// (T_0 = Delta_i; f = 0.7, 0.3, 0.05).  Every other vertex has a bound below
-// L_j, so if the largest exact degree found is >= L_j it is Delta_{i+1};
-// otherwise T_{j+1} = L_j - 1.  When a band floor would fall below SWL, or all
-// passes fail, the run switches to exact remaining degrees.
-
-struct DSearch {
-  int pending;      // 1 while the search still needs the next pass
-  int switching;    // 1 when the run moves to exact degrees
-  long long delta;  // resolved Delta (when neither pending nor switching)
-  long long T, L;   // bounds of the pending pass
-};
-
-__device__ inline long long band_floor(int pass, long long T) {
-  return (long long)ceilf(band_factor(pass) * (float)T);
-}
-
-// State of the search after `done` passes (every thread computes the same);
-// C is Ctrl or a CtrlHead snapshot of it.
-template <class C>
-__device__ inline DSearch dsearch(const C *c, int done) {
-  DSearch s{0, 0, -1, 0, 0};
-  if (c->phase != PHASE_LAZY) return s;
-  long long T = c->delta;
-  for (int j = 0; j < done; j++) {
-    const long long L = band_floor(j, T);
-    if (L < SWL) {  // pass j never ran: the search switched before it
-      s.switching = 1;
-      return s;
-    }
-    const long long M = c->d_max[j];
-    if (M >= L) {
-      s.delta = M;
-      return s;
-    }
-    T = L - 1;
-  }
-  if (done >= DITER || band_floor(done, T) < SWL) {
-    s.switching = 1;
-    return s;
-  }
-  s.pending = 1;
-  s.T = T;
-  s.L = band_floor(done, T);
-  return s;
 }
 
 // Candidates of pass IT: live entries with bound >= L, found in the levels
@@ -224,7 +106,7 @@ template <int IT>
 __global__ void __launch_bounds__(BS) k_dscan(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_DELTA)) return;
   const DSearch s = dsearch(&h, IT);
   if (!s.pending) return;
   const int kL = level_of(s.L < DSW ? DSW : s.L), kT = NLVL - 1;
@@ -264,7 +146,7 @@ template <int IT>
 __global__ void __launch_bounds__(BS) k_rescan(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_DELTA)) return;
   const DSearch s = dsearch(&h, IT);
   if (!s.pending) return;
   __shared__ int lcnt[TW];
@@ -338,7 +220,7 @@ __global__ void __launch_bounds__(BS) k_rescan(Ws w) {
 __global__ void __launch_bounds__(BS) k_xlist(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_DELTA)) return;
   const DSearch s = dsearch(&h, DITER);
   if (!s.switching) return;
   unsigned long long *xacc = (unsigned long long *)w.awork;
@@ -372,7 +254,7 @@ __global__ void __launch_bounds__(BS) k_xlist(Ws w) {
 __global__ void __launch_bounds__(BS) k_xcount(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_DELTA)) return;
   const DSearch s = dsearch(&h, DITER);
   if (!s.switching) return;
   __shared__ int lcnt[TW];
@@ -489,12 +371,6 @@ __device__ inline long long lookback(const Ws &w, unsigned t) {
   return excl;
 }
 
-// The rows a round walks: the full rows until the run switches to exact
-// degrees, the rows the switch compacted after it (the phase is read at the
-// start of each kernel and changes only at the end of a round, in k_close).
-__device__ inline const int64_t *round_end(const Ws &w, int phase) { return phase == PHASE_EXACT ? w.xend : w.rend; }
-__device__ inline const int32_t *round_col(const Ws &w, int phase) { return phase == PHASE_EXACT ? w.xcol : w.col; }
-
 // The positions of this thread's slots marked in `act` hold this round's
 // active vertices (vv[k] at position base + k).  An active vertex with no
 // unclustered neighbour (degree 0, or an exact remaining degree of 0) is a
@@ -589,7 +465,7 @@ __device__ inline unsigned load_slots(const Ws &w, int64_t base, int64_t end, in
 __global__ void __launch_bounds__(SEL_BS) k_select(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_SELECT)) return;
   __shared__ unsigned s_tile;
   __shared__ int s_stop;
   __shared__ long long s_excl;
@@ -662,7 +538,7 @@ __global__ void __launch_bounds__(SEL_BS) k_select(Ws w) {
 __global__ void __launch_bounds__(SEL_BS) k_select_range(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_SELECT)) return;
   __shared__ int64_t sh[SEL_BS / 64 + 1];
   __shared__ unsigned long long s_base;
   const int64_t cur0 = h.cursor;
@@ -681,7 +557,7 @@ __global__ void __launch_bounds__(SEL_BS) k_select_range(Ws w) {
 __global__ void __launch_bounds__(BS) k_elect(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_ELECT)) return;
   const unsigned long long ap = h.a_pack;
   lb_walk(w.alist, w.awork, pk_cnt(ap), pk_work(ap), w.off, round_end(w, h.phase), round_col(w, h.phase), nullptr,
           w.ainfo, [&](Items &it) {
@@ -713,7 +589,7 @@ __global__ void __launch_bounds__(BS) k_elect(Ws w) {
 __global__ void __launch_bounds__(BS) k_classify(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_CLASSIFY)) return;
   __shared__ StageBufI<2 * BS> sb;
   stage_init(sb);
   const int64_t na = pk_cnt(h.a_pack);
@@ -916,7 +792,7 @@ __device__ void resolve_rows(Ws &w, Ctrl *c, int64_t nb, const int64_t *rend, co
 __global__ void __launch_bounds__(RBS) k_resolve(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_CLASSIFY)) return;
   const int64_t nb = h.n_blocked;
   if (nb == 0) return;
   const int64_t ne = h.n_cedges;
@@ -933,7 +809,7 @@ constexpr int CLAIM_CAP = 2 * TW;  // staged newly claimed vertices (a tile adds
 __global__ void __launch_bounds__(BS) k_claim(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_CLASSIFY)) return;
   const bool c4 = w.algo == ALGO_C4;
   const unsigned long long lp = c4 ? h.c_pack : h.a_pack;
   const int32_t *list = c4 ? w.clist : w.alist;
@@ -980,12 +856,6 @@ __global__ void __launch_bounds__(BS) k_claim(Ws w) {
   if (threadIdx.x == 0 && s_atom) atomicAdd(&c->spread_atom[blockIdx.x & 63], (unsigned long long)s_atom);
 }
 
-__device__ inline void hist_add(int *s_hist, int *g_hist, int d, int x) {
-  if (d <= 0) return;
-  if (d < HLDS) atomicAdd(&s_hist[d], x);
-  else atomicAdd(&g_hist[d], x);
-}
-
 // The newly clustered -- the listed centers (C4's center list, ClusterWild!'s
 // active list) and the newly claimed -- leave the unclustered bitmap;
 // ClusterWild! conflict marks are counted; the scan tiles of this round are
@@ -998,7 +868,7 @@ __device__ inline void hist_add(int *s_hist, int *g_hist, int d, int x) {
 __global__ void __launch_bounds__(BS) k_clear(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done) return;
+  if (idle(h, ST_CLASSIFY)) return;
   __shared__ StageBuf<2 * BS> sp;
   __shared__ int s_hist[HLDS];
   for (int i = threadIdx.x; i < HLDS; i += BS) s_hist[i] = 0;
@@ -1017,9 +887,12 @@ __global__ void __launch_bounds__(BS) k_clear(Ws w) {
       const bool center = i < nc;
       const int32_t u = center ? centers[i] : w.nlist[i - nc];
       atomicAnd(&w.unc[u >> 5], ~(1u << (u & 31)));
-      if (cw && w.flag[u]) {
-        w.flag[u] = 0;
-        conf++;
+      if (cw && center) {
+        w.state[u] = CENTER;  // an ACTIVE mark is always this round's (k_team relies on it)
+        if (w.flag[u]) {
+          w.flag[u] = 0;
+          conf++;
+        }
       }
       if (exact) {
         const int32_t d = w.ub[u];
@@ -1053,7 +926,7 @@ __global__ void __launch_bounds__(BS) k_clear(Ws w) {
 __global__ void __launch_bounds__(BS) k_peel(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (h.done || h.phase != PHASE_EXACT) return;
+  if (idle(h, ST_CLASSIFY) || h.phase != PHASE_EXACT) return;
   __shared__ int s_hist[HLDS];
   __shared__ unsigned s_atom;
   for (int i = threadIdx.x; i < HLDS; i += BS) s_hist[i] = 0;
@@ -1092,6 +965,10 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
   Ctrl *c = w.ctrl;
   if (c->done) return;
   const long long now = (long long)wall_clock64();
+  if (w.team) {  // the next k_team starts from zeroed counters
+    unsigned *t = reinterpret_cast<unsigned *>(w.team);
+    for (int i = threadIdx.x; i < (int)(sizeof(TeamCtl) / sizeof(unsigned)); i += 64) t[i] = 0;
+  }
   long long lone = 0;  // centers settled by k_select
   long long xlow = 0;  // entries of lower-degree rows recounted at the switch
   {  // fold the spread statistics of the round
@@ -1113,8 +990,15 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
   int done = 0;
   float fconf = 0.f, fclaim = 0.f, feps = 0.f;
   long long prev_delta = 0;
+  int slots = 0;
   if (threadIdx.x == 0) {
-    prev_delta = c->delta;
+    prev_delta = c->has_round ? c->delta : w.max_deg;
+    if (!w.team) {  // (k_team ends the slots where there is one)
+      slots = c->has_round ? c->slots + 1 : 0;
+      c->slots = slots;
+    } else {
+      slots = c->slots;
+    }
     if (c->has_round) {
       const int phase_run = c->phase;  // phase the finished round ran in
       const bool c4 = w.algo == ALGO_C4;
@@ -1146,6 +1030,7 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
       c->feat_conf = c->b > 0 ? (float)conf / (float)c->b : 0.f;
       c->feat_claim = c->n_start > 0 ? (float)(newly - centers) / (float)c->n_start : 0.f;
       c->feat_eps = (float)c->eps_used;
+      c->rate = c->b > 0 ? (float)(pk_work(c->a_pack) + pk_work(c->p_pack)) / (float)c->b : 0.f;
       c->cursor = c->r_last + 1;
       c->n_rem = c->n_start - newly;
       c->round += 1;
@@ -1158,7 +1043,10 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
         d = delta_hat(w, c->round);  // Delta-hat_{i+1}: no remaining degree is kept
       } else if (phase_run == PHASE_LAZY) {  // Delta_{i+1} (lazy search, or the exact histogram below)
         const DSearch s = dsearch(c, DITER);
-        if (s.switching) c->phase = PHASE_EXACT;
+        if (s.switching) {
+          c->phase = PHASE_EXACT;
+          c->rate = 1e30f;  // peeling starts: its first round is measured on the whole device
+        }
         else d = s.delta;
       }
       c->delta = d;
@@ -1237,10 +1125,11 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
       if (fb) c->fallback = 1;
       c->n_start = n_rem;
       c->t_start = now;
+      c->stage = (int16_t)next_stage(w, b, c->cursor, n_rem, c->rate);
     }
   }
-  if (threadIdx.x == 0 && w.progress) {
-    const unsigned long long p = (unsigned long long)(unsigned)round | (unsigned long long)(done != 0) << PROGRESS_DONE |
+  if (threadIdx.x == 0 && w.progress && (!w.team || done)) {
+    const unsigned long long p = (unsigned long long)(unsigned)slots | (unsigned long long)(done != 0) << PROGRESS_DONE |
                                  (unsigned long long)(c->phase == PHASE_EXACT) << PROGRESS_EXACT |
                                  (unsigned long long)(c->error != 0) << PROGRESS_ERROR;
     // relaxed: the host acts on this word alone and reads the rest of the
@@ -1323,6 +1212,7 @@ hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls) {
     hipLaunchKernelGGL(k_xcount, dim3(ls.edge_grid), dim3(BS), 0, s, w);
   }
   hipLaunchKernelGGL(k_close, dim3(1), dim3(64), 0, s, w);
+  if (w.team) return launch_team(w, s);
   return hipGetLastError();
 }
 
