@@ -582,10 +582,12 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     HIP_TRY(hipMemcpyAsync(out.trace, ws.trace, sizeof(RoundRec) * (size_t)std::min(want, kHostTrace),
                            hipMemcpyDeviceToHost, s));
   out.error = 0;
+  const bool on_dev = (flags & CC_OUTPUT_ON_DEVICE) != 0;
   if (!labelled) {
     // labels go to the workspace first and reach the caller only on success,
     // so a failed run leaves the caller's buffer untouched
     HIP_TRY(launch_finalize(w, ws.label_buf, s));
+    if (on_dev) HIP_TRY(launch_deliver(ws.label_buf, labels, n, &ws.ctrl->error, s));
     HIP_TRY(hipMemcpyAsync(&out.error, &ws.ctrl->error, sizeof(int), hipMemcpyDeviceToHost, s));
   }
   HIP_TRY(hipStreamSynchronize(s));
@@ -599,10 +601,8 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     return fail(CC_ERR_DEVICE, "device error " + std::to_string(e) + " in the round loop");
   }
   if (out.error) return fail(CC_ERR_DEVICE, "device error " + std::to_string(out.error) + " while finishing");
-  const bool on_dev = (flags & CC_OUTPUT_ON_DEVICE) != 0;
-  if (!labelled || !on_dev) {
-    HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n,
-                           on_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
+  if (!on_dev) {
+    HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
   if (stats) {
@@ -675,30 +675,24 @@ int32_t run_async(cc_graph *g, int algo, const int32_t *order, int32_t *labels, 
     d_order = ws.order_buf;
   }
   HIP_TRY(hipMemsetAsync(ws.ctrl, 0, sizeof(Ctrl), s));
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  HIP_TRY(hipEventCreate(&ev0));
-  HIP_TRY(hipEventCreate(&ev1));
-  struct EvGuard {
-    hipEvent_t a, b;
-    ~EvGuard() {
-      (void)hipEventDestroy(a);
-      (void)hipEventDestroy(b);
-    }
-  } evg{ev0, ev1};
+  const hipEvent_t ev0 = ws.ev0, ev1 = ws.ev1;
   // the long-row claim list borrows two vertex lists of the round loop
   AsyncArgs a{g->roff, g->rcol, n, g->iso_start, ws.iorder, ws.rank, ws.lab, ws.ctrl, ws.xlist, ws.plist, n};
   // labels reach the caller only on success
   HIP_TRY(launch_async(a, algo, d_order, g->perm, ws.iorder, ws.label_buf, stats ? (int)stats->async_waves : 0, s,
                        ev0, ev1, ws.omap_buf ? &ws.omap : nullptr));
-  Ctrl hc;
-  HIP_TRY(hipMemcpyAsync(&hc, ws.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+  const bool on_dev = (flags & CC_OUTPUT_ON_DEVICE) != 0;
+  if (on_dev) HIP_TRY(launch_deliver(ws.label_buf, labels, n, &ws.ctrl->error, s));
+  HIP_TRY(hipMemcpyAsync(&ws.host->ctrl, ws.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  const Ctrl &hc = ws.host->ctrl;
   if (hc.error == ERR_PERM) return fail(CC_ERR_NOT_PERMUTATION, "order is not a permutation of 0..n-1");
   if (hc.error == ERR_NO_PROGRESS) return fail(CC_ERR_NO_PROGRESS, "a bounded wait for an earlier vertex expired");
   if (hc.error) return fail(CC_ERR_DEVICE, "device error " + std::to_string(hc.error) + " in the asynchronous run");
-  HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n,
-                         (flags & CC_OUTPUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  if (!on_dev) {
+    HIP_TRY(hipMemcpyAsync(labels, ws.label_buf, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
   if (stats) {
     unsigned long long walked = 0, claimed = 0, atoms = 0;
     for (int i = 0; i < 64; i++) {

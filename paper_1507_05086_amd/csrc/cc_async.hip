@@ -6,10 +6,8 @@
 // holds position 64 c + l) from a shared counter and settles them:
 //
 //   C4 (attemptCluster / isCenter): a vertex still unclustered when reached
-//   is a center iff none of its earlier-ranked neighbours is one.  An earlier
-//   neighbour in an earlier chunk is waited for until it is decided; one in
-//   the same chunk is settled by a short in-order pass over the 64 lanes.
-//   The labels are KwikCluster's whatever the interleaving (C4 is
+//   is a center iff none of its earlier-ranked neighbours is one; an undecided
+//   earlier neighbour is waited for.  The labels are KwikCluster's whatever the interleaving (C4 is
 //   serializable).
 //   ClusterWild! (createCluster): a vertex still unclustered when reached
 //   becomes a center (compare-and-swap from "unclustered"), no waiting.  Its
@@ -25,15 +23,26 @@
 // and is read and written only with device-scope atomics, so a wave on one
 // XCD sees another XCD's decisions.
 //
-// Progress: chunks are handed out in pi order (a run of AS_BATCH
-// consecutive chunks per visit to the counter, worked through in order), and
-// a wave waits only for vertices of earlier chunks: its own, finished, or
-// ones handed out before its run, which running waves hold and whose own
-// waits point further back still.  The earliest unfinished chunk is the one
-// its wave is working on, and it never waits.  A wave takes a new run only
-// after finishing the last, so no resident-set assumption is needed.  Every
-// wait is bounded (and stops when another wave has reported an error);
-// every wave leaves when the counter passes the last chunk.
+// What bounds it.  Random gathers of ranks and labels, one memory line each
+// where the arrays outgrow the caches, once the waits are short.  The waits
+// were most of the time while a chunk's decisions were published together and
+// a wave took 8 chunks per visit from the start: nearly every chunk has a
+// neighbour in the chunk before it, so the chunks in flight finished one after
+// the other.  Now a vertex is published when it is decided, a wave keeps the
+// undecided neighbours of its 64 vertices as pairs and looks at those only,
+// and the runs of chunks grow with the position.  Whole calls: R-MAT 24 10.6
+// -> 2.3 ms, R-MAT 26 13.9 -> 7.4, R-MAT 20 10.1 -> 0.48, power law 4 M 31.6 ->
+// 1.1, ER 500 K 16.1 -> 0.35 ms.
+//
+// Progress: chunks are handed out in pi order (a run of consecutive chunks
+// per visit to the counter, worked through in order), and a vertex waits
+// only for earlier ones.  The earliest undecided vertex is in the chunk its
+// wave is working on (that wave's earlier chunks are finished) or in the next
+// one to be handed out, and it waits for nobody; its wave's loop never blocks
+// on one of its other vertices.  A wave takes a new run only after finishing
+// the last, so no resident-set assumption is needed.  Every wait is bounded
+// (and stops when another wave has reported an error); every wave leaves when
+// the counter passes the last chunk.
 #include "cc_device.h"
 #include "cc_launch.h"
 
@@ -43,25 +52,93 @@ constexpr int AS_BS = 256;  // 4 waves per workgroup, each on its own chunks
 constexpr int AS_BIG = 2048;  // C4 centers with longer rows claim in a second, device-wide pass
 // chunks a wave takes per visit to the shared counter (one device-scope
 // atomic on one address serialises with every other wave's)
-constexpr int AS_BATCH = 8;
+constexpr int AS_BATCH = 8;  // (4: R-MAT 26 8.2 ms when every run is as long, 16: 9.2, growing to 8: 7.4)
 constexpr int32_t LAB_NONCENTER = INF - 1;
-constexpr unsigned AS_SPIN_LIMIT = 1u << 24;
+constexpr int AS_PAIRS = 512;  // undecided earlier neighbours a wave keeps
+// Above this many vertices isCenter reads a neighbour's label before its rank
+// (two arrays no longer stay in the 256 MB cache, and most neighbours, the
+// hubs, are decided early): R-MAT 26 8.0 -> 7.35 ms a call, R-MAT 24 2.3 both
+// ways, power law 4 M 1.12 -> 1.19 ms.
+constexpr int64_t AS_LAB_FIRST = int64_t(1) << 25;
+constexpr long long AS_LIMIT = 200000000;  // longest wait without a decision, wall clock ticks (100 MHz)
 
 __device__ inline int32_t lab_load(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Row of each pending lane walked edge-balanced by the whole wave: entry e
-// of the concatenated rows belongs to the first lane j whose inclusive
-// prefix incl_j exceeds e (six steps of a lane-indexed binary search).
-__device__ inline int owner_lane(int64_t incl, int64_t e) {
+// A wave walks the rows of its lanes in two ways.  Rows of more than AS_LONG
+// entries are streamed one after the other; the others (at most 64 * AS_LONG
+// entries together) edge-balanced over the wave: entry e of the concatenated
+// rows belongs to the first lane j whose inclusive prefix incl_j exceeds e
+// (six steps of a lane-indexed binary search).  Either way AS_K entries per
+// lane are in flight together (4 and 8 are alike; one makes a hub's row, met
+// before anybody has claimed it, a chain of 6 K steps per 400 K entries).
+constexpr int AS_LONG = 512;
+constexpr int AS_K = 4;
+
+__device__ inline int owner_lane(int incl, int e) {
   int j = 0;
 #pragma unroll
   for (int step = 32; step >= 1; step >>= 1) {
-    const int64_t pj = __shfl(incl, j + step - 1, 64);
+    const int pj = __shfl(incl, j + step - 1, 64);
     if (pj <= e) j += step;
   }
   return j;
+}
+
+__device__ inline int wave_incl_scan32(int x) {
+  const int l = lane_id();
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d, 64);
+    if (l >= d) x += y;
+  }
+  return x;
+}
+
+// f(u, j): AS_K neighbours of this lane (u[k] < 0: none) and the lanes whose
+// rows they are in, for the rows [start, start + deg) of the lanes in `rows`;
+// stop(mask) says whether the rows of those lanes need no further look.
+// Every lane of the wave calls f each time.
+template <class F, class S>
+__device__ inline void wave_rows(const int32_t *col, unsigned long long rows, int64_t start, int32_t deg, F &&f, S &&stop) {
+  const int lane = lane_id();
+  int32_t u[AS_K];
+  int jj[AS_K];
+  const unsigned long long longs = __ballot((rows >> lane & 1) && deg > AS_LONG);
+  const int sdeg = (rows >> lane & 1) && deg <= AS_LONG ? deg : 0;
+  const int incl = wave_incl_scan32(sdeg);
+  const int total = __shfl(incl, 63, 64);
+  const int64_t base = start - (incl - sdeg);  // of entry e of this lane's row: col[base + e]
+  const unsigned long long shorts = rows & ~longs;
+  for (int e0 = 0; e0 < total; e0 += 64 * AS_K) {
+    if (stop(shorts)) break;
+#pragma unroll
+    for (int k = 0; k < AS_K; k++) {
+      // lane-indexed shuffles run with the whole wave active
+      const int e = e0 + 64 * k + lane;
+      jj[k] = owner_lane(incl, e < total ? e : total - 1);
+      const int64_t b = __shfl(base, jj[k], 64);
+      u[k] = -1;
+      if (e < total) u[k] = col[b + e];
+    }
+    f(u, jj);
+  }
+  for (unsigned long long m = longs; m; m &= m - 1) {
+    const int j = __ffsll((long long)m) - 1;
+    const int64_t s0 = __shfl(start, j, 64);
+    const int32_t d = __shfl(deg, j, 64);
+    for (int32_t e0 = 0; e0 < d; e0 += 64 * AS_K) {
+      if (stop(1ull << j)) break;
+#pragma unroll
+      for (int k = 0; k < AS_K; k++) {
+        const int32_t e = e0 + 64 * k + lane;
+        jj[k] = j;
+        u[k] = e < d ? col[s0 + e] : -1;
+      }
+      f(u, jj);
+    }
+  }
 }
 
 __device__ inline unsigned long long wave_or(unsigned long long x) {
@@ -70,22 +147,36 @@ __device__ inline unsigned long long wave_or(unsigned long long x) {
   return x;
 }
 
+// Next run of chunks of this wave (AS_BATCH of them; ramp: fewer while the
+// run is young).  The vertices in flight are all met before anybody has
+// claimed them, so C4 starts with one chunk per visit and a narrow window;
+// later, when most positions are settled when reached, the counter (one
+// device-scope atomic, serialised with every other wave's) would be the limit.
+__device__ inline void next_run(Ctrl *c, int64_t nchunks, bool ramp, int64_t *chunk, int64_t *end) {
+  long long run = AS_BATCH;
+  if (ramp) {
+    run = *end / (4 * (int64_t)gridDim.x * (AS_BS / 64)) + 1;
+    if (run > AS_BATCH) run = AS_BATCH;
+  }
+  unsigned b = 0;
+  if (lane_id() == 0) b = atomicAdd(&c->tile_counter, (unsigned)run);
+  *chunk = (int64_t)__shfl(b, 0, 64);
+  *end = *chunk + run < nchunks ? *chunk + run : nchunks;
+}
+
 template <int ALGO>
 __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
   Ctrl *c = a.ctrl;
   const int lane = lane_id();
-  __shared__ unsigned long long s_intra[AS_BS / 64][64];
-  unsigned long long *intra = s_intra[wave_id()];
+  __shared__ int32_t s_u[ALGO == ALGO_C4 ? AS_BS / 64 : 1][AS_PAIRS];
+  __shared__ uint8_t s_j[ALGO == ALGO_C4 ? AS_BS / 64 : 1][AS_PAIRS];
+  __shared__ int s_n[AS_BS / 64];
   const int64_t nchunks = (a.n + 63) / 64;
   unsigned long long walked = 0, claimed = 0, atoms = 0, waits = 0;
-  int64_t chunk = 0, chunk_end = 0;  // the wave's current run of AS_BATCH chunks
+  int64_t chunk = 0, chunk_end = 0;  // the wave's current run of chunks
+  const bool lab_first = a.n > AS_LAB_FIRST;
   for (;; chunk++) {
-    if (chunk >= chunk_end) {
-      int64_t b = 0;
-      if (lane == 0) b = (int64_t)atomicAdd(&c->tile_counter, 1u) * AS_BATCH;
-      chunk = __shfl(b, 0, 64);
-      chunk_end = chunk + AS_BATCH < nchunks ? chunk + AS_BATCH : nchunks;
-    }
+    if (chunk >= chunk_end) next_run(c, nchunks, ALGO == ALGO_C4, &chunk, &chunk_end);
     if (chunk >= nchunks) break;
     if (ld_rlx(&c->error)) break;
     const int64_t c0 = chunk * 64, p = c0 + lane;
@@ -100,104 +191,172 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
       start = a.off[v];
       deg = (int32_t)(a.off[v + 1] - start);
     }
-    unsigned long long centers = 0;
-    if (ALGO == ALGO_C4) {
-      // isCenter: earlier-ranked neighbours, edge-balanced over the pending rows
-      intra[lane] = 0;
-      const int64_t incl = wave_incl_scan(deg);
-      const int64_t total = __shfl(incl, 63, 64);
-      const unsigned long long pend = __ballot(pending);
-      unsigned long long blocked = 0;
-      for (int64_t base = 0; base < total; base += 64) {
-        if ((blocked & pend) == pend) break;  // every pending vertex already has an earlier center
-        // lane-indexed shuffles run with the whole wave active
-        const int64_t e = base + lane;
-        const int j = owner_lane(incl, e < total ? e : total - 1);
-        const int64_t row_start = __shfl(start, j, 64);
-        const int64_t row_first = __shfl(incl, j, 64) - __shfl((int64_t)deg, j, 64);
-        bool found = false;
-        if (e < total && !(blocked >> j & 1)) {
-          const int32_t u = a.col[row_start + (e - row_first)];
-          const int64_t pj = c0 + j;
-          const int32_t ru = a.rank[u];
-          walked++;
-          if (ru < pj) {
-            if (ru >= c0) {
-              atomicOr(&intra[j], 1ull << (ru - c0));  // same chunk: settled below
-            } else {
-              int32_t x = lab_load(&a.lab[u]);
-              unsigned spins = 0;
-              while (x == INF) {  // wait until the earlier neighbour is decided
-                if (++spins > AS_SPIN_LIMIT) {
-                  set_error(c, ERR_NO_PROGRESS);
-                  break;
-                }
-                if ((spins & 255) == 0 && ld_rlx(&c->error)) break;
-                __builtin_amdgcn_s_sleep(2);
-                x = lab_load(&a.lab[u]);
+    // claims of the centers in a mask.  A C4 center with a long row is listed
+    // and claims in k_async_big instead, spread over the whole device: a label
+    // only decides whether its vertex is still unclustered when reached, and
+    // a C4 vertex that should have been claimed already finds its earlier
+    // center in isCenter anyway.  (ClusterWild! has no such check, so its
+    // claims are never put off.)
+    auto claim = [&](unsigned long long centers) {
+      bool defer = false;
+      if (ALGO == ALGO_C4 && (centers >> lane & 1) && deg > AS_BIG) {
+        const unsigned slot = atomicAdd(&c->n_blocked, 1u);
+        if ((int64_t)slot < a.big_cap) {
+          a.big_v[slot] = v;
+          a.big_p[slot] = (int32_t)p;
+          defer = true;
+        } else {
+          set_error(c, ERR_OVERFLOW);  // cannot happen: a list slot per vertex
+        }
+      }
+      wave_rows(
+          a.col, __ballot((centers >> lane & 1) && !defer), start, deg,
+          [&](const int32_t *u, const int *jj) {
+            int32_t x[AS_K];
+#pragma unroll
+            for (int k = 0; k < AS_K; k++) x[k] = u[k] >= 0 ? a.lab[u[k]] : -1;
+#pragma unroll
+            for (int k = 0; k < AS_K; k++) {
+              const int32_t pj = (int32_t)(c0 + jj[k]);
+              claimed += u[k] >= 0;
+              if (x[k] > pj) {  // stale reads are safe: a label only decreases
+                atomicMin(&a.lab[u[k]], pj);
+                atoms++;
               }
-              waits += spins;
-              found = x < 0;  // a center
             }
-          }
-        }
-        blocked |= wave_or(found ? 1ull << j : 0ull);
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // same-chunk dependences: in pi order, lane by lane
-      const unsigned long long my_intra = intra[lane];
-      const unsigned long long cand = pend & ~blocked;
-      if (__ballot((cand >> lane & 1) && my_intra != 0)) {
-        for (int l = 0; l < 64; l++) {
-          const unsigned long long il = __shfl(my_intra, l, 64);
-          if ((cand >> l & 1) && !(il & centers)) centers |= 1ull << l;
-        }
-      } else {
-        centers = cand;
-      }
-      if (pending) {
-        if (centers >> lane & 1) __hip_atomic_store(&a.lab[v], -(int32_t)p - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else atomicMin(&a.lab[v], LAB_NONCENTER);
-      }
-    } else {
+          },
+          [](unsigned long long) { return false; });
+    };
+    if constexpr (ALGO == ALGO_CW) {
       // createCluster: a vertex still unclustered becomes a center
       bool won = false;
       if (pending) won = atomicCAS(&a.lab[v], INF, -(int32_t)p - 1) == INF;
-      centers = __ballot(won);
-    }
-    // claims: the centers' rows, edge-balanced over the wave.  A C4 center
-    // with a long row is listed and claims in k_async_big instead, spread over
-    // the whole device: a label only decides whether its vertex is still
-    // unclustered when reached, and a C4 vertex that should have been claimed
-    // already finds its earlier center in isCenter anyway.  (ClusterWild! has
-    // no such check, so its claims are never put off.)
-    bool defer = false;
-    if (ALGO == ALGO_C4 && (centers >> lane & 1) && deg > AS_BIG) {
-      const unsigned slot = atomicAdd(&c->n_blocked, 1u);
-      if ((int64_t)slot < a.big_cap) {
-        a.big_v[slot] = v;
-        a.big_p[slot] = (int32_t)p;
-        defer = true;
-      } else {
-        set_error(c, ERR_OVERFLOW);  // cannot happen: a list slot per vertex
-      }
-    }
-    const int32_t cdeg = (centers >> lane & 1) && !defer ? deg : 0;
-    const int64_t incl = wave_incl_scan(cdeg);
-    const int64_t total = __shfl(incl, 63, 64);
-    for (int64_t base = 0; base < total; base += 64) {
-      const int64_t e = base + lane;
-      const int j = owner_lane(incl, e < total ? e : total - 1);
-      const int64_t row_start = __shfl(start, j, 64);
-      const int64_t row_first = __shfl(incl, j, 64) - __shfl((int64_t)cdeg, j, 64);
-      if (e < total) {
-        const int32_t u = a.col[row_start + (e - row_first)];
-        const int32_t pj = (int32_t)(c0 + j);
-        claimed++;
-        if (a.lab[u] > pj) {  // stale reads are safe: a label only decreases
-          atomicMin(&a.lab[u], pj);
-          atoms++;
+      claim(__ballot(won));
+    } else {
+      // isCenter.  A pass over the rows finds the earlier-ranked neighbours:
+      // a center decides its vertex at once, an undecided one is kept as a
+      // pair (neighbour, lane); then only the pairs are looked at again.  A
+      // vertex is published as soon as it is decided, not with its chunk.
+      int32_t *pu = s_u[wave_id()];
+      uint8_t *pj = s_j[wave_id()];
+      int *pn = &s_n[wave_id()];
+      unsigned long long undecided = __ballot(pending);
+      unsigned long long again = undecided;  // rows (still) to be walked: a pair did not fit
+      unsigned long long toclaim = 0;
+      long long t0 = 0;
+      if (lane == 0) *pn = 0;
+      __builtin_amdgcn_wave_barrier();
+      while (undecided) {
+        unsigned long long blocked = 0, waiting = 0;
+        if (again) {
+          unsigned long long skip = 0;  // lanes whose pairs do not all fit
+          const unsigned long long rows = again;
+          wave_rows(
+              a.col, rows, start, deg,
+              [&](const int32_t *u, const int *jj) {
+                int32_t ru[AS_K], x[AS_K];
+                unsigned long long found = 0, lost = 0;
+#pragma unroll
+                for (int k = 0; k < AS_K; k++) {
+                  walked += u[k] >= 0;
+                  // a plain load: a decision it sees is final, and a hub's label stays cached
+                  x[k] = u[k] < 0 ? 0 : lab_first ? a.lab[u[k]] : INF;
+                }
+#pragma unroll
+                for (int k = 0; k < AS_K; k++) ru[k] = x[k] == INF ? a.rank[u[k]] : -1;
+#pragma unroll
+                for (int k = 0; k < AS_K; k++) {
+                  if (x[k] == INF) x[k] = ru[k] < c0 + jj[k] ? lab_load(&a.lab[u[k]]) : 0;
+                  else if (x[k] < 0 && -x[k] - 1 > c0 + jj[k]) x[k] = 0;  // a later center
+                }
+#pragma unroll
+                for (int k = 0; k < AS_K; k++) {
+                  if (x[k] < 0) found |= 1ull << jj[k];  // a center
+                  if (x[k] == INF && !(blocked >> jj[k] & 1)) {
+                    const int q = atomicAdd(pn, 1);
+                    if (q < AS_PAIRS) {
+                      pu[q] = u[k];
+                      pj[q] = (uint8_t)jj[k];
+                    } else {
+                      lost |= 1ull << jj[k];
+                    }
+                  }
+                }
+                if (__ballot(found != 0)) blocked |= wave_or(found);
+                if (__ballot(lost != 0)) skip |= wave_or(lost);
+              },
+              // until every vertex of these rows has an earlier center
+              [&](unsigned long long rows) { return (blocked & rows) == rows; });
+          again = skip & ~blocked;
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+        }
+        // the pairs: decided ones go, the others close ranks
+        const int np = *pn < AS_PAIRS ? *pn : AS_PAIRS;
+        int out = 0;
+        unsigned long long found = 0, wait = 0;
+        for (int i0 = 0; i0 < np; i0 += 64) {
+          const int i = i0 + lane;
+          int32_t u = -1;
+          int j = 0;
+          if (i < np) {
+            u = pu[i];
+            j = pj[i];
+          }
+          bool keep = false;
+          if (u >= 0 && (undecided & ~blocked) >> j & 1) {
+            const int32_t x = lab_load(&a.lab[u]);
+            if (x < 0) found |= 1ull << j;
+            keep = x == INF;
+          }
+          if (keep) wait |= 1ull << j;
+          const unsigned long long m = __ballot(keep);
+          __builtin_amdgcn_wave_barrier();  // every lane has read its pair
+          if (keep) {
+            const int q = out + __popcll(m & lanemask_lt());
+            pu[q] = u;
+            pj[q] = (uint8_t)j;
+          }
+          out += __popcll(m);
+          __builtin_amdgcn_wave_barrier();
+        }
+        if (lane == 0) *pn = out;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (np > 0) {
+          blocked |= wave_or(found);
+          waiting = wave_or(wait);
+        }
+        // a vertex claimed meanwhile has an earlier center too
+        const bool mine = undecided >> lane & 1;
+        const bool taken = mine && lab_load(&a.lab[v]) != INF;
+        blocked = (blocked | __ballot(taken)) & undecided;
+        const unsigned long long centers = undecided & ~blocked & ~waiting & ~again;
+        if (centers >> lane & 1)
+          __hip_atomic_store(&a.lab[v], -(int32_t)p - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else if ((blocked >> lane & 1) && !taken)
+          atomicMin(&a.lab[v], LAB_NONCENTER);
+        undecided &= ~(blocked | centers);
+        again &= undecided;
+        toclaim |= centers;
+        if ((blocked | centers) == 0 || undecided == 0) {
+          if (toclaim) {  // nothing more to decide for now
+            claim(toclaim);
+            toclaim = 0;
+          } else if (undecided) {
+            waits++;
+            if (t0 == 0) t0 = wall_clock64();
+            if ((waits & 255) == 0) {
+              if (ld_rlx(&c->error)) break;
+              if (wall_clock64() - t0 > AS_LIMIT) {
+                set_error(c, ERR_NO_PROGRESS);
+                break;
+              }
+            }
+            __builtin_amdgcn_s_sleep(2);
+          }
+        } else {
+          t0 = 0;
         }
       }
     }

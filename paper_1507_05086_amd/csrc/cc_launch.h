@@ -19,6 +19,8 @@ hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls);
 // Rounds on one XCD (cc_team.hip) until one is for the whole device; w.team set.
 hipError_t launch_team(const Ws &w, hipStream_t s);
 hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s);
+// Copies n labels (device memory, any alignment) unless *error is set.
+hipError_t launch_deliver(const int32_t *from, int32_t *to, int64_t n, const int *error, hipStream_t s);
 
 // Graph set-up: row-weight prefix wall[n+1] (the "all rows" list of the
 // edge-balanced walk), per-row graph ids (batches), column-range check and,

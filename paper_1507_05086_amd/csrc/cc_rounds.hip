@@ -1168,6 +1168,16 @@ __global__ void __launch_bounds__(BS) k_finalize(Ws w, int32_t *labels) {
   }
 }
 
+// The labels of a run that has not failed reach the caller's device buffer; a
+// failed run leaves it alone, with no host round trip in between.
+__global__ void __launch_bounds__(BS) k_deliver(const int32_t *from, int32_t *to, int64_t n, const int *error) {
+  if (*error) return;
+  const int64_t q = (((uintptr_t)to | (uintptr_t)from) & 15) ? 0 : n / 4;  // whole 16-byte words, if both are aligned
+  for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < q; i += (int64_t)gridDim.x * BS)
+    reinterpret_cast<int4 *>(to)[i] = reinterpret_cast<const int4 *>(from)[i];
+  for (int64_t i = q * 4 + (int64_t)blockIdx.x * BS + threadIdx.x; i < n; i += (int64_t)gridDim.x * BS) to[i] = from[i];
+}
+
 // -------------------------------------------------------------- launch ----
 
 static inline unsigned grid_for(int64_t items, unsigned cap) {
@@ -1218,6 +1228,11 @@ hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls) {
 
 hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize, dim3(grid_for(w.n, 4096)), dim3(BS), 0, s, w, labels);
+  return hipGetLastError();
+}
+
+hipError_t launch_deliver(const int32_t *from, int32_t *to, int64_t n, const int *error, hipStream_t s) {
+  hipLaunchKernelGGL(k_deliver, dim3(grid_for((n + 3) / 4, 4096)), dim3(BS), 0, s, from, to, n, error);
   return hipGetLastError();
 }
 
