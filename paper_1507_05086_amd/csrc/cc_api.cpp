@@ -66,8 +66,8 @@ struct SchedKey {
 Policy g_policy;
 std::mutex g_policy_mu;
 
-// A captured group of k rounds (kernels only), keyed by the bytes of the
-// run's kernel arguments and the phase it was captured for.
+// The graph of k rounds (kernels only), keyed by the bytes of the
+// run's kernel arguments and the phase it was built for.
 struct RoundGraph {
   unsigned char key[sizeof(Ws)];
   int exact = -1;
@@ -126,7 +126,6 @@ struct Workspace {
   long long *cost_acc = nullptr;
   int *dev_err = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around a run's rounds
-  hipStream_t cap = nullptr;  // private stream the round groups are captured on
   std::vector<RoundGraph> graphs;
 };
 
@@ -191,7 +190,6 @@ void free_ws(Workspace &w) {
   if (w.progress) (void)hipHostFree(w.progress);
   for (RoundGraph &g : w.graphs)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (w.cap) (void)hipStreamDestroy(w.cap);
   w = Workspace();
 }
 
@@ -305,25 +303,39 @@ int32_t run_batch(cc_graph *g, int algo, const int32_t *order, double eps, int32
 // behind it, large enough that the host stays ahead of the device.
 constexpr int64_t kRoundGroup = 4;
 
-// Queues k rounds on s as one graph launch: the round's kernels are captured
-// once per (arguments, phase, k) and replayed; the host then issues one call
-// per group instead of ~16 launches per round.
+// Queues k rounds on s as one graph launch: the graph of the rounds' kernels
+// is built once per (arguments, phase, k) and replayed, so the host issues
+// one call per group instead of ~16 launches per round.  Its nodes are added
+// one by one: a stream capture would make other threads' calls on the null
+// stream fail while it lasts.
 int32_t launch_rounds(Workspace &ws, const Ws &w, const LaunchShape &ls, int64_t k, hipStream_t s) {
   for (RoundGraph &g : ws.graphs)
     if (g.k == k && g.exact == ls.exact_seen && std::memcmp(g.key, &w, sizeof(Ws)) == 0) {
       HIP_TRY(hipGraphLaunch(g.exec, s));
       return CC_OK;
     }
-  if (!ws.cap) HIP_TRY(hipStreamCreateWithFlags(&ws.cap, hipStreamNonBlocking));
-  HIP_TRY(hipStreamBeginCapture(ws.cap, hipStreamCaptureModeThreadLocal));
-  hipError_t e = hipSuccess;
-  for (int64_t r = 0; r < k && e == hipSuccess; r++) e = launch_round(w, ws.cap, ls);
   hipGraph_t graph = nullptr;
-  const hipError_t e2 = hipStreamEndCapture(ws.cap, &graph);
-  if (e == hipSuccess) e = e2;
+  HIP_TRY(hipGraphCreate(&graph, 0));
+  RoundStep steps[ROUND_STEPS];
+  const int count = round_steps(w, ls, steps);
+  Ws arg = w;
+  void *args[] = {&arg};
+  hipGraphNode_t last = nullptr;
+  hipError_t e = hipSuccess;
+  for (int64_t r = 0; r < k; r++)
+    for (int i = 0; i < count && e == hipSuccess; i++) {
+      hipKernelNodeParams np{};
+      np.func = reinterpret_cast<void *>(steps[i].kernel);
+      np.gridDim = dim3(steps[i].grid);
+      np.blockDim = dim3(steps[i].block);
+      np.kernelParams = args;  // copied into the node
+      hipGraphNode_t node = nullptr;
+      e = hipGraphAddKernelNode(&node, graph, last ? &last : nullptr, last ? 1 : 0, &np);
+      last = node;
+    }
   hipGraphExec_t exec = nullptr;
   if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (graph) (void)hipGraphDestroy(graph);
+  (void)hipGraphDestroy(graph);
   HIP_TRY(e);
   if (ws.graphs.size() >= 24) {  // keep the cache small: drop the oldest
     (void)hipGraphExecDestroy(ws.graphs.front().exec);
@@ -410,7 +422,7 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     HIP_TRY(hipMemcpyAsync(ws.mlp, pol.mlp.data(), sizeof(float) * CC_MLP_PARAMS, hipMemcpyHostToDevice, s));
 
   Ws w;
-  std::memset(&w, 0, sizeof(w));  // the bytes (padding included) key the captured round graphs
+  std::memset(&w, 0, sizeof(w));  // the bytes (padding included) key the round graphs
   w.off = g->roff;
   w.rend = g->roff + 1;
   w.col = g->rcol;

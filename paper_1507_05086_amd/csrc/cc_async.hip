@@ -86,16 +86,6 @@ __device__ inline int owner_lane(int incl, int e) {
   return j;
 }
 
-__device__ inline int wave_incl_scan32(int x) {
-  const int l = lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(x, d, 64);
-    if (l >= d) x += y;
-  }
-  return x;
-}
-
 // f(u, j): AS_K neighbours of this lane (u[k] < 0: none) and the lanes whose
 // rows they are in, for the rows [start, start + deg) of the lanes in `rows`;
 // stop(mask) says whether the rows of those lanes need no further look.
@@ -107,7 +97,7 @@ __device__ inline void wave_rows(const int32_t *col, unsigned long long rows, in
   int jj[AS_K];
   const unsigned long long longs = __ballot((rows >> lane & 1) && deg > AS_LONG);
   const int sdeg = (rows >> lane & 1) && deg <= AS_LONG ? deg : 0;
-  const int incl = wave_incl_scan32(sdeg);
+  const int incl = wave_incl_scan(sdeg);
   const int total = __shfl(incl, 63, 64);
   const int64_t base = start - (incl - sdeg);  // of entry e of this lane's row: col[base + e]
   const unsigned long long shorts = rows & ~longs;

@@ -54,7 +54,7 @@ template <int G, bool SUB = false>
 struct Grp {
   static constexpr int size = G;
   int tid;      // 0 .. G-1
-  int64_t *sh;  // G/64 + 1 slots of scratch
+  int *sh;      // G/64 slots of scratch
   SubBar *bar;  // SUB only
   int wave0;    // first wave of the group in the workgroup
   __device__ __forceinline__ int wave() const { return G == 64 ? 0 : wave_id() - wave0; }
@@ -70,33 +70,33 @@ struct Grp {
     }
   }
   // exclusive scan; *tot = sum over the group
-  __device__ __forceinline__ int64_t scan(int64_t x, int64_t *tot) const {
-    const int64_t inc = wave_incl_scan(x);
+  __device__ __forceinline__ int scan(int x, int *tot) const {
+    const int inc = wave_incl_scan(x);
     if (G == 64) {
-      *tot = __shfl(inc, 63, 64);
+      *tot = lane_value(inc, 63);
       return inc - x;
     }
     if (lane_id() == 63) sh[wave()] = inc;
     sync();
-    int64_t base = 0, t = 0;
+    int base = 0, t = 0;
+#pragma unroll
     for (int w = 0; w < G / 64; w++) {
-      if (w < wave()) base += sh[w];
-      t += sh[w];
+      const int y = sh[w];
+      if (w < wave()) base += y;
+      t += y;
     }
     sync();
     *tot = t;
     return base + inc - x;
   }
-  __device__ __forceinline__ int64_t max(int64_t x) const {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const int64_t y = __shfl_xor(x, d, 64);
-      x = y > x ? y : x;
-    }
+  // maximum of values >= 0
+  __device__ __forceinline__ int max(int x) const {
+    x = wave_max(x);
     if (G == 64) return x;
     if (lane_id() == 0) sh[wave()] = x;
     sync();
-    int64_t m = sh[0];
+    int m = sh[0];
+#pragma unroll
     for (int i = 1; i < G / 64; i++) m = sh[i] > m ? sh[i] : m;
     sync();
     return m;
@@ -193,10 +193,10 @@ __device__ __forceinline__ int rows_pass(const GR &g, const int16_t *list, int c
       const int32_t v = list[i];
       d = s.rstart[v + 1] - s.rstart[v];
     }
-    int64_t tot;
-    const int pre = (int)g.scan(d, &tot);
+    int tot;
+    const int pre = g.scan(d, &tot);
     if (i < cnt) s.pref[i] = carry + pre;
-    carry += (int)tot;
+    carry += tot;
   }
   const int total = carry;
   if (g.tid == 0) s.pref[cnt] = total;
@@ -250,19 +250,14 @@ __device__ __forceinline__ int rows_pass(const GR &g, const int16_t *list, int c
         const int bj = j <= cnt ? s.pref[j] : 0x7fffffff;
         const bool in = bj <= e0 + 63;
         const bool full = __ballot(in) == ~0ull;
-        int wend = full ? __shfl(bj, 63, 64) : e0 + 64;
+        int wend = full ? lane_value(bj, 63) : e0 + 64;
         if (wend > c1) wend = c1;
         rs[lane] = 0;
         wave_sync();
         const int bn = __shfl_down(bj, 1, 64);
         if (in && (lane == 63 || bn != bj)) rs[bj - e0] = lane + 1;
         wave_sync();
-        int r = rs[lane];
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const int t = __shfl_up(r, d, 64);
-          if (lane >= d) r = t > r ? t : r;
-        }
+        const int r = wave_incl_max(rs[lane]);
         if (e0 + lane < wend) {
           rowk[k] = lo + r;
           ek[k] = e0 + lane;
@@ -339,9 +334,9 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
   int n_rem = n, cur = 0, rounds = 0;
   while (n_rem > 0 && rounds <= n) {
     // Delta over the unclustered vertices
-    int64_t m = 0;
+    int m = 0;
     for (int v = g.tid; v < n; v += G) {
-      const int64_t d = (int64_t)(s.lw[v] & 0xFFFFu);
+      const int d = (int)(s.lw[v] & 0xFFFFu);
       if ((s.fl[v] & F_UNC) && d > m) m = d;
     }
     const long long delta = g.max(m);
@@ -356,20 +351,20 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
         v = s.ordl[p];
         un = (s.fl[v] & F_UNC) != 0;
       }
-      int64_t tot;
-      const int64_t pre = g.scan(un ? 1 : 0, &tot);
+      int tot;
+      const int pre = g.scan(un ? 1 : 0, &tot);
       if (un && na + pre < B) {
         s.alist[na + pre] = (int16_t)v;
         s.fl[v] |= F_ACT;
       }
       // position of the B-th unclustered vertex, if in this chunk
-      const int64_t last = g.max((un && na + pre == B - 1) ? (int64_t)p + 1 : 0);
+      const int last = g.max((un && na + pre == B - 1) ? p + 1 : 0);
       if (last > 0) {
-        cur = (int)last;
+        cur = last;
         na = B;
       } else {
         cur += G;
-        na += (int)tot;
+        na += tot;
       }
     }
     g.sync();
@@ -398,10 +393,10 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
             const int32_t av = s.alist[i];
             und = !(s.fl[av] & (F_CEN | F_NON));
           }
-          int64_t tot;
-          const int64_t pre = g.scan(und ? 1 : 0, &tot);
+          int tot;
+          const int pre = g.scan(und ? 1 : 0, &tot);
           if (und) s.nlist[nb + pre] = s.alist[i];
-          nb += (int)tot;
+          nb += tot;
         }
         g.sync();
         if (nb == 0) break;
@@ -433,10 +428,10 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
           av = s.alist[i];
           cen = (s.fl[av] & F_CEN) != 0;
         }
-        int64_t tot;
-        const int64_t pre = g.scan(cen ? 1 : 0, &tot);
+        int tot;
+        const int pre = g.scan(cen ? 1 : 0, &tot);
         if (cen) s.alist[nc + pre] = av;
-        nc += (int)tot;
+        nc += tot;
       }
     } else {
       for (int i = g.tid; i < B; i += G) s.fl[s.alist[i]] |= F_CEN;
@@ -499,8 +494,8 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
   BStats st{0, 0, 0, 0};
   constexpr int NQ = T / QG > 0 ? T / QG : 1;
   __shared__ int s_gi[NQ];
-  __shared__ int64_t sh[T / 64 + 1];
-  __shared__ int64_t shq[NQ][QG / 64 + 1];
+  __shared__ int sh[T / 64];
+  __shared__ int shq[NQ][QG / 64];
   __shared__ SubBar sbar[NQ];
   __shared__ int rsb[T / 64][64];
   int *rs = rsb[wave_id()];
@@ -557,12 +552,15 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
   // statistics: one reduction per workgroup, one atomic per counter
   __syncthreads();
   unsigned long long v4[4] = {st.elect, st.claim, st.peel, st.atom};
+  __shared__ unsigned long long s_stat[4];
+  if (threadIdx.x < 4) s_stat[threadIdx.x] = 0;
+  __syncthreads();
   for (int k = 0; k < 4; k++) {
-    int64_t tot;
-    const int64_t pre = gw.scan((int64_t)v4[k], &tot);
-    (void)pre;
-    if (threadIdx.x == 0 && tot) atomicAdd(&a.stat[k], (unsigned long long)tot);
+    const int64_t t = wave_sum((int64_t)v4[k]);
+    if (lane_id() == 0 && t) atomicAdd(&s_stat[k], (unsigned long long)t);
   }
+  __syncthreads();
+  if (threadIdx.x < 4 && s_stat[threadIdx.x]) atomicAdd(&a.stat[threadIdx.x], s_stat[threadIdx.x]);
 }
 
 // Kernels with more than 64 KB of dynamic LDS must say so before launch.

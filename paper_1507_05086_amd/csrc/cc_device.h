@@ -329,36 +329,68 @@ __device__ inline unsigned long long lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// Inclusive wave64 scan of 64-bit values.
-__device__ inline int64_t wave_incl_scan(int64_t x) {
-  const int l = lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int64_t y = __shfl_up(x, d, 64);
-    if (l >= d) x += y;
-  }
+// Wave64 scans and reductions by data-parallel moves inside the vector unit:
+// a step takes a few cycles, where a shuffle goes through the LDS unit and
+// takes about sixty.  Every lane of the wave takes part.
+template <int CTRL, int ROWS>
+__device__ inline int dpp_mov(int old, int x) {
+  return __builtin_amdgcn_update_dpp(old, x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ inline int dpp_add(int x) {
+  return x + dpp_mov<CTRL, ROWS>(0, x);
+}
+template <int CTRL, int ROWS>
+__device__ inline int64_t dpp_add(int64_t x) {
+  const unsigned lo = (unsigned)dpp_mov<CTRL, ROWS>(0, (int)x), hi = (unsigned)dpp_mov<CTRL, ROWS>(0, (int)(x >> 32));
+  return x + (int64_t)((unsigned long long)hi << 32 | lo);
+}
+// Inclusive scan.
+template <class T>
+__device__ inline T wave_incl_scan(T x) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32 or 64 bits");
+  x = dpp_add<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8 within rows of 16 lanes
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  x = dpp_add<0x118, 0xf>(x);
+  x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+  x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
   return x;
 }
-__device__ inline int64_t wave_sum(int64_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+__device__ inline int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+__device__ inline int64_t lane_value(int64_t x, int lane) {
+  return (int64_t)((unsigned long long)(unsigned)lane_value((int)(x >> 32), lane) << 32 | (unsigned)lane_value((int)x, lane));
+}
+template <class T>
+__device__ inline T wave_sum(T x) {
+  return lane_value(wave_incl_scan(x), 63);
+}
+// Inclusive prefix maximum, and the maximum, of values >= 0.
+__device__ inline int wave_incl_max(int x) {
+  x = max(x, dpp_mov<0x111, 0xf>(0, x));
+  x = max(x, dpp_mov<0x112, 0xf>(0, x));
+  x = max(x, dpp_mov<0x114, 0xf>(0, x));
+  x = max(x, dpp_mov<0x118, 0xf>(0, x));
+  x = max(x, dpp_mov<0x142, 0xa>(0, x));
+  x = max(x, dpp_mov<0x143, 0xc>(0, x));
   return x;
 }
-__device__ inline int wave_max(int x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x = max(x, __shfl_xor(x, d, 64));
-  return x;
+__device__ inline int wave_max(int x) { return lane_value(wave_incl_max(x), 63); }
+// x of a lane whose number is the same in the whole wave.
+template <class T>
+__device__ inline T from_lane(T x, int lane) {
+  return lane_value(x, __builtin_amdgcn_readfirstlane(lane));
 }
 
-// Workgroup exclusive scan of 64-bit values for NT threads; *total receives
+// Workgroup exclusive scan of 32- or 64-bit values for NT threads; *total receives
 // the sum.  Uses `sh` (NT/64 + 1 slots of shared memory); two barriers.
-template <int NT = BS>
-__device__ inline int64_t wg_excl_scan(int64_t x, int64_t *total, int64_t *sh) {
+template <int NT = BS, class T = int64_t>
+__device__ inline T wg_excl_scan(T x, T *total, T *sh) {
   constexpr int NW = NT / 64;
-  const int64_t inc = wave_incl_scan(x);
+  const T inc = wave_incl_scan(x);
   if (lane_id() == 63) sh[wave_id()] = inc;
   __syncthreads();
-  int64_t base = 0, tot = 0;
+  T base = 0, tot = 0;
 #pragma unroll
   for (int w = 0; w < NW; w++) {
     if (w < wave_id()) base += sh[w];
@@ -377,11 +409,11 @@ __device__ inline void wave_append(bool pred, int32_t v, int64_t weight, unsigne
   if (m == 0) return;
   const int64_t w = pred ? weight : 0;
   const int64_t winc = wave_incl_scan(w);
-  const int64_t wtot = __shfl(winc, 63, 64);
+  const int64_t wtot = lane_value(winc, 63);
   const int leader = __ffsll((long long)m) - 1;
   unsigned long long base = 0;
   if (lane_id() == leader) base = atomicAdd(packc, pk(wtot, __popcll(m)));
-  base = __shfl(base, leader, 64);
+  base = (unsigned long long)from_lane((int64_t)base, leader);
   if (pred) {
     const int64_t slot = pk_cnt(base) + __popcll(m & lanemask_lt());
     list[slot] = v;
@@ -396,11 +428,11 @@ __device__ inline void wave_append_info(bool pred, int32_t v, RowInfo ri, unsign
   if (m == 0) return;
   const int64_t w = pred ? (ri.deg > 0 ? ri.deg : 1) : 0;
   const int64_t winc = wave_incl_scan(w);
-  const int64_t wtot = __shfl(winc, 63, 64);
+  const int64_t wtot = lane_value(winc, 63);
   const int leader = __ffsll((long long)m) - 1;
   unsigned long long base = 0;
   if (lane_id() == leader) base = atomicAdd(packc, pk(wtot, __popcll(m)));
-  base = __shfl(base, leader, 64);
+  base = (unsigned long long)from_lane((int64_t)base, leader);
   if (pred) {
     const int64_t slot = pk_cnt(base) + __popcll(m & lanemask_lt());
     list[slot] = v;

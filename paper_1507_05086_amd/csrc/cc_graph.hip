@@ -372,7 +372,7 @@ __device__ inline void flush_acc(long long *acc, int slot, int g, long long x) {
   if (s_mixed) {
     if (x) atomicAdd((unsigned long long *)&acc[2 * g + slot], (unsigned long long)x);
   } else {
-    const long long ws = wave_sum(x);
+    const int64_t ws = wave_sum((int64_t)x);
     if (lane_id() == 0 && ws) atomicAdd((unsigned long long *)&s_sum, (unsigned long long)ws);
     __syncthreads();
     if (threadIdx.x == 0 && s_sum) atomicAdd((unsigned long long *)&acc[2 * g + slot], (unsigned long long)s_sum);

@@ -15,7 +15,14 @@ struct LaunchShape {
 };
 
 hipError_t launch_init(const Ws &w, const unsigned *lvl_init_cnt, hipStream_t s);
-hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls);
+// The kernels of one round, in order; each takes the run's Ws.
+struct RoundStep {
+  void (*kernel)(Ws);
+  unsigned grid, block;
+};
+constexpr int ROUND_STEPS = 20;  // at most
+int round_steps(const Ws &w, const LaunchShape &ls, RoundStep *out);
+RoundStep team_step(const Ws &w);
 // Rounds on one XCD (cc_team.hip) until one is for the whole device; w.team set.
 hipError_t launch_team(const Ws &w, hipStream_t s);
 hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s);

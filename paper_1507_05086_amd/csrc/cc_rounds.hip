@@ -364,7 +364,7 @@ __device__ inline long long lookback(const Ws &w, unsigned t) {
       continue;
     }
     const long long val = (l <= first) ? (long long)(s & ((1ull << 62) - 1)) : 0;
-    excl += wave_sum(val);
+    excl += wave_sum((int64_t)val);
     if (first < 64) break;
     j -= 64;
   }
@@ -413,10 +413,11 @@ __device__ inline void activate(const Ws &w, Ctrl *c, const int32_t vv[SIPT], un
   }
   int64_t wtot, ctot;
   const int64_t wpre = wg_excl_scan<SEL_BS>(wsum, &wtot, sh);
-  // listed count in the low 32 bits, settled count above (a tile holds < 2^32)
-  const int64_t cpre = wg_excl_scan<SEL_BS>((int64_t)cnt | ((int64_t)lone << 32), &ctot, sh) & 0xFFFFFFFFll;
-  const int64_t ltot = ctot >> 32;
-  ctot &= 0xFFFFFFFFll;
+  // listed count in the low half, settled count above (a tile holds fewer than 2^16 of both)
+  int both;
+  const int cpre = wg_excl_scan<SEL_BS>(cnt | lone << 16, &both, (int *)sh) & 0xFFFF;
+  const int64_t ltot = both >> 16;
+  ctot = both & 0xFFFF;
   if (threadIdx.x == 0 && ctot > 0) *s_base = atomicAdd(&c->a_pack, pk(wtot, ctot));
   if (threadIdx.x == 0 && ltot > 0) atomicAdd(&c->spread_lone[blockIdx.x & 63], (unsigned long long)ltot);
   const int64_t wc = wave_sum((int64_t)clears);  // every lane takes part in the sum
@@ -496,7 +497,9 @@ __global__ void __launch_bounds__(SEL_BS) k_select(Ws w) {
     int32_t vv[SIPT];
     const unsigned un = load_slots(w, base, n, vv);
     int64_t agg;
-    const int64_t mine = wg_excl_scan<SEL_BS>(__popc(un), &agg, sh);
+    int found;
+    const int mine = wg_excl_scan<SEL_BS>((int)__popc(un), &found, (int *)sh);
+    agg = found;
     if (threadIdx.x < 64) {  // wave 0 publishes and looks back
       long long excl = 0;
       if (t == 0) {
@@ -1194,36 +1197,34 @@ hipError_t launch_init(const Ws &w, const unsigned *lvl_init_cnt, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_round(const Ws &w, hipStream_t s, const LaunchShape &ls) {
+int round_steps(const Ws &w, const LaunchShape &ls, RoundStep *out) {
+  int k = 0;
+  auto add = [&](void (*f)(Ws), unsigned grid, unsigned block) { out[k++] = RoundStep{f, grid, block}; };
   const bool binomial = w.policy == POL_BINOMIAL;
-  if (binomial) hipLaunchKernelGGL(k_select_range, dim3(ls.select_grid), dim3(SEL_BS), 0, s, w);
-  else hipLaunchKernelGGL(k_select, dim3(ls.select_grid), dim3(SEL_BS), 0, s, w);
+  add(binomial ? k_select_range : k_select, ls.select_grid, SEL_BS);
   if (w.algo == ALGO_C4) {
-    hipLaunchKernelGGL(k_elect, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_classify, dim3(ls.vertex_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_resolve, dim3(1), dim3(RBS), 0, s, w);
+    add(k_elect, ls.edge_grid, BS);
+    add(k_classify, ls.vertex_grid, BS);
+    add(k_resolve, 1, RBS);
   }
-  hipLaunchKernelGGL(k_claim, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-  hipLaunchKernelGGL(k_clear, dim3(ls.vertex_grid), dim3(BS), 0, s, w);
-  if (binomial) {
-    // Delta-hat needs no remaining degrees: no peel, no Delta search
-  } else if (ls.exact_seen) {
-    // the run has switched to exact degrees for good: no lazy search
-    hipLaunchKernelGGL(k_peel, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-  } else {
-    hipLaunchKernelGGL(k_peel, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_dscan<0>, dim3(ls.vertex_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_rescan<0>, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_dscan<1>, dim3(ls.vertex_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_rescan<1>, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_dscan<2>, dim3(ls.vertex_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_rescan<2>, dim3(ls.edge_grid), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_xlist, dim3(grid_for(w.n, ls.vertex_grid)), dim3(BS), 0, s, w);
-    hipLaunchKernelGGL(k_xcount, dim3(ls.edge_grid), dim3(BS), 0, s, w);
+  add(k_claim, ls.edge_grid, BS);
+  add(k_clear, ls.vertex_grid, BS);
+  if (!binomial) {  // Delta-hat needs no remaining degrees: no peel, no Delta search
+    add(k_peel, ls.edge_grid, BS);
+    if (!ls.exact_seen) {  // the run has not switched to exact degrees for good
+      add(k_dscan<0>, ls.vertex_grid, BS);
+      add(k_rescan<0>, ls.edge_grid, BS);
+      add(k_dscan<1>, ls.vertex_grid, BS);
+      add(k_rescan<1>, ls.edge_grid, BS);
+      add(k_dscan<2>, ls.vertex_grid, BS);
+      add(k_rescan<2>, ls.edge_grid, BS);
+      add(k_xlist, grid_for(w.n, ls.vertex_grid), BS);
+      add(k_xcount, ls.edge_grid, BS);
+    }
   }
-  hipLaunchKernelGGL(k_close, dim3(1), dim3(64), 0, s, w);
-  if (w.team) return launch_team(w, s);
-  return hipGetLastError();
+  add(k_close, 1, 64);
+  if (w.team) out[k++] = team_step(w);
+  return k;
 }
 
 hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s) {

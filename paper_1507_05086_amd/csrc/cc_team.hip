@@ -160,22 +160,6 @@ __device__ inline bool team_form(Team &tm, Lds &L, unsigned want) {
   return tm.n > 0;
 }
 
-// Inclusive wave scan by data-parallel moves inside the vector unit (a
-// shuffle goes through the LDS unit and takes ten times as long).
-template <int CTRL, int ROWS>
-__device__ inline int dpp_add(int x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
-}
-__device__ inline int wave_scan(int x) {
-  x = dpp_add<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8 within rows of 16 lanes
-  x = dpp_add<0x112, 0xf>(x);
-  x = dpp_add<0x114, 0xf>(x);
-  x = dpp_add<0x118, 0xf>(x);
-  x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
-  x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
-__device__ inline int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
 __device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ inline unsigned long long uni(unsigned long long x) {
   return (unsigned long long)(unsigned)uni((int)(x >> 32)) << 32 | (unsigned)uni((int)x);
@@ -185,7 +169,7 @@ __device__ inline long long uni(long long x) { return (long long)uni((unsigned l
 // Exclusive scan over the workgroup, one barrier; `sh` may be used again
 // after the next barrier.
 __device__ inline int wg_scan(int x, int *tot, int *sh) {
-  const int inc = wave_scan(x), l = lane_id(), w = uni(wave_id());
+  const int inc = wave_incl_scan(x), l = lane_id(), w = uni(wave_id());
   if (l == 63) sh[w] = inc;
   __syncthreads();
   int s = l < TNW ? sh[l] : 0;
@@ -199,7 +183,7 @@ __device__ inline int wg_scan(int x, int *tot, int *sh) {
 }
 // Two at once.
 __device__ inline void wg_scan2(int x, int y, int *px, int *py, int *tx, int *ty, int *sh, int *sh2) {
-  const int ix = wave_scan(x), iy = wave_scan(y), l = lane_id(), w = uni(wave_id());
+  const int ix = wave_incl_scan(x), iy = wave_incl_scan(y), l = lane_id(), w = uni(wave_id());
   if (l == 63) {
     sh[w] = ix;
     sh2[w] = iy;
@@ -661,7 +645,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
           if (!team_sync(tm, L)) return;
           const int l = lane_id();
           const int x = l < (int)tm.n ? (int)ld(&tm.t->tcnt[step & 1][l]) : 0;
-          const int inc = wave_scan(x);
+          const int inc = wave_incl_scan(x);
           all = __builtin_amdgcn_readlane(inc, 63);
           excl = tm.me > 0 ? __builtin_amdgcn_readlane(inc, tm.me - 1) : 0;
         }
@@ -1029,7 +1013,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
       const unsigned long long cp = uni(ld(&sl->c_pack));
       promoted = (int)pk_cnt(cp);
       if (tm.me == 0) {
-        sum_claim_x += wave_total(work_in) - wave_total(work_out);
+        sum_claim_x += wave_sum(work_in) - wave_sum(work_out);
         for (int i = tid; i < nb; i += TNT) w.flag[ld(&w.blist[i])] = 0;
       }
       if (promoted > 0) {
@@ -1054,7 +1038,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
       }
     }
     count();
-    if (nlong > 0) sum_long += wave_total(wlong);
+    if (nlong > 0) sum_long += wave_sum(wlong);
     // ---- the next Delta, lazy phase: band passes over stale bounds (dsearch)
     long long d_next = 0;
     bool to_device = false;
@@ -1077,7 +1061,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
             x = (int)ld(&c->lvl_cnt[tid]);
             x = x < cap ? x : cap;
           }
-          const int inc = wave_scan(x);
+          const int inc = wave_incl_scan(x);
           if (tid < NLVL) L.lbase[tid] = inc - x;
           if (tid == NLVL) L.lbase[NLVL] = inc;
         }
@@ -1328,16 +1312,16 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
   }
 }
 
-hipError_t launch_team(const Ws &w, hipStream_t s) {
-  if (w.solo) {
-    if (w.algo == ALGO_C4) hipLaunchKernelGGL((k_team<ALGO_C4, true>), dim3(1), dim3(TNT), 0, s, w);
-    else hipLaunchKernelGGL((k_team<ALGO_CW, true>), dim3(1), dim3(TNT), 0, s, w);
-    return hipGetLastError();
-  }
+RoundStep team_step(const Ws &w) {
+  const bool c4 = w.algo == ALGO_C4;
+  if (w.solo) return RoundStep{c4 ? k_team<ALGO_C4, true> : k_team<ALGO_CW, true>, 1, TNT};
   // one workgroup on every compute unit of the eight XCDs
-  const dim3 grid((unsigned)w.team_n * 8u);
-  if (w.algo == ALGO_C4) hipLaunchKernelGGL((k_team<ALGO_C4, false>), grid, dim3(TNT), 0, s, w);
-  else hipLaunchKernelGGL((k_team<ALGO_CW, false>), grid, dim3(TNT), 0, s, w);
+  return RoundStep{c4 ? k_team<ALGO_C4, false> : k_team<ALGO_CW, false>, (unsigned)w.team_n * 8u, TNT};
+}
+
+hipError_t launch_team(const Ws &w, hipStream_t s) {
+  const RoundStep t = team_step(w);
+  hipLaunchKernelGGL(t.kernel, dim3(t.grid), dim3(t.block), 0, s, w);
   return hipGetLastError();
 }
 

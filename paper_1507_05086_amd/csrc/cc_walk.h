@@ -4,8 +4,8 @@
 // into equal item ranges, one per workgroup, so a hub row of 10^6 entries is
 // shared by many workgroups while thousands of short rows share one.  Inside
 // a workgroup the items are processed in tiles of TW: the row weights of the
-// tile's rows are staged in LDS and each lane finds its row by binary search
-// there (load-balanced search), then reads the adjacency entry with coalesced
+// tile's rows are staged in LDS (as 32-bit items from the tile's start) and
+// each lane finds its row by binary search there (load-balanced search), then reads the adjacency entry with coalesced
 // loads along the row.
 #pragma once
 #include <type_traits>
@@ -27,15 +27,13 @@ struct Items {
   unsigned edge, vert;
 };
 
-// first index in a[0..len) with a[i] > x (a sorted; a[len-1] may be a sentinel)
-__device__ inline int lds_upper_bound(const int64_t *a, int len, int64_t x) {
-  int lo = 0, hi = len;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] <= x) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
+// last j < len with a[j] <= x (a sorted, a[0] <= x); one length for the workgroup
+__device__ inline int lds_last_le(const int32_t *a, int len, int32_t x) {
+  int j = 0, step = 1;
+  while (step * 2 < len) step *= 2;
+  for (; step > 0; step >>= 1)
+    if (j + step < len && a[j + step] <= x) j += step;
+  return j;
 }
 
 struct NoEpilogue {
@@ -60,9 +58,9 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
                         const int32_t *__restrict__ col,
                         const int32_t *__restrict__ vals, const RowInfo *__restrict__ info, F &&f, E &&ep = E(),
                         P &&post = P()) {
-  __shared__ int64_t lw[TW + 1];
+  __shared__ int32_t lw[TW + 1];    // first item of each row of the tile, from the tile's start (-1: before it)
   __shared__ int32_t lv[TW];
-  __shared__ int64_t loff[TW];
+  __shared__ int64_t loff[TW];      // where item 0 of the tile would be in col, were it in the row
   __shared__ int32_t ldeg[TW];
   __shared__ int32_t lval[TW];
   __shared__ int64_t s_ent;
@@ -102,20 +100,18 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
     const int64_t send = (s + TW) < s1 ? (s + TW) : s1;
     // the window is sorted, so counting its entries below a bound is the
     // upper-bound search: rows touched by this tile, and where the next starts
-    int c_rows = 0, c_next = 0;
+    int w_rows = 0, w_next = 0;
 #pragma unroll
     for (int q = 0; q < NPW; q++) {
       const int j = (int)threadIdx.x + q * BS;
-      if (j <= TW) {
-        lw[j] = pw[q];
-        c_rows += pw[q] <= send - 1;
-        c_next += pw[q] <= s + TW;
-      }
+      if (j <= TW) lw[j] = pw[q] < s ? -1 : pw[q] < s + TW ? (int32_t)(pw[q] - s) : TW;
+      if (j < TW) loff[j] = s - pw[q];
+      w_rows += __popcll(__ballot(j <= TW && pw[q] <= send - 1));
+      w_next += __popcll(__ballot(j <= TW && pw[q] <= s + TW));
     }
-    const int64_t w_rows = wave_sum((int64_t)c_rows), w_next = wave_sum((int64_t)c_next);
     if (lane_id() == 0) {
-      atomicAdd(&s_nent, (int)w_rows);
-      atomicAdd(&s_next, (int)w_next);
+      atomicAdd(&s_nent, w_rows);
+      atomicAdd(&s_next, w_next);
     }
     __syncthreads();
     const int nent = s_nent;
@@ -126,12 +122,12 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
       lv[j] = v;
       if (info) {  // row info carried by the list: no offset or rank lookups
         const RowInfo ri = info[ent0 + j];
-        loff[j] = ri.start;
+        loff[j] += ri.start;
         ldeg[j] = ri.deg;
         lval[j] = ri.rank;
       } else {
         const int64_t o = off[v];
-        loff[j] = o;
+        loff[j] += o;
         ldeg[j] = (int32_t)(end[v] - o);
         lval[j] = vals ? vals[v] : 0;
       }
@@ -145,9 +141,10 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
     it.edge = 0;
     it.vert = 0;
     int64_t epos[IPT];
+    const int items = (int)(send - s);
 #pragma unroll
     for (int k = 0; k < IPT; k++) {
-      const int64_t item = s + (int64_t)k * BS + threadIdx.x;
+      const int x = k * BS + (int)threadIdx.x;
       it.v[k] = 0;
       it.u[k] = 0;
       it.val[k] = 0;
@@ -155,17 +152,16 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
       it.pos[k] = -1;
       it.ent[k] = -1;
       epos[k] = -1;
-      if (item < send) {
-        const int j = lds_upper_bound(lw, nent, item) - 1;
-        const int64_t local = item - lw[j];
+      if (x < items) {
+        const int j = lds_last_le(lw, nent, x);
         it.ent[k] = j;
         it.v[k] = lv[j];
         it.val[k] = lval[j];
         it.deg[k] = ldeg[j];
-        if (local == 0) it.vert |= 1u << k;
-        if (local < ldeg[j]) {
+        if (x == lw[j]) it.vert |= 1u << k;
+        if (ldeg[j] > 0) {
           it.edge |= 1u << k;
-          epos[k] = loff[j] + local;
+          epos[k] = loff[j] + x;
           it.pos[k] = epos[k];
         }
       }
@@ -177,9 +173,8 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
     if constexpr (!std::is_same<typename std::decay<E>::type, NoEpilogue>::value) {
       __syncthreads();
       for (int j = threadIdx.x; j < nent; j += BS) {
-        const int64_t w0 = lw[j], w1 = w0 + (ldeg[j] > 0 ? ldeg[j] : 1);
-        const int64_t lo = w0 > s ? w0 : s, hi = w1 < send ? w1 : send;
-        ep(j, ent0 + j, lv[j], ldeg[j], hi - lo);
+        const int lo = lw[j] > 0 ? lw[j] : 0, hi = j + 1 < nent ? lw[j + 1] : items;
+        ep(j, ent0 + j, lv[j], ldeg[j], (int64_t)(hi - lo));
       }
     }
     if constexpr (!std::is_same<typename std::decay<P>::type, NoPost>::value) post();

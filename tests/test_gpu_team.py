@@ -130,7 +130,7 @@ def test_teams_of_several_threads_and_streams():
             with torch.cuda.stream(s):
                 gh = cc.cc_graph_from_csr(torch.from_numpy(g.off).cuda(), torch.from_numpy(g.col).cuda())
                 d = torch.from_numpy(order).cuda()
-                for _ in range(10):
+                for _ in range(10):  # the first builds the round graphs while others run
                     lab, _ = cc.cc_clusterwild(gh, d, 0.5)
                     assert np.array_equal(lab.cpu().numpy(), ref)
         except BaseException as e:  # reported by the main thread
