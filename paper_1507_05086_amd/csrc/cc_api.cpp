@@ -129,21 +129,29 @@ struct Workspace {
   std::vector<RoundGraph> graphs;
 };
 
+// Size class of a batch: log2 buckets of (graphs, largest graph, median graph).
+using SizeClass = std::tuple<int, int, int, int>;
+// What a batched launch counts, cleared and copied back in one piece; each
+// graph's rounds follow.
+struct BatchOut {
+  unsigned long long stat[4];
+  unsigned heads[3];
+  int err;
+  int32_t rounds[1];
+};
+size_t batch_out_bytes(int32_t graphs) { return offsetof(BatchOut, rounds) + sizeof(int32_t) * (size_t)graphs; }
+
 // Device buffers and launch shape of a batch.
 struct BatchState {
   int32_t *queue = nullptr;
-  unsigned *heads = nullptr;
-  int32_t *rounds = nullptr;
-  unsigned long long *stat = nullptr;
-  int *err = nullptr;
-  int q_block = 0, q_wave = -1, q_quad = -1;  // shape the uploaded queue was built for
-  int n_big = 0, n_quad = 0, cap_big = 0, cap_quad = 0, cap_wave = 0;
+  BatchOut *out = nullptr, *host = nullptr;  // device, and pinned
+  int q_block = 0, q_wave = -1, q_quad = -1;  // shape the uploaded queue was built (and checked) for
+  int n_big = 0, n_quad = 0, cap_big = 0, cap_quad = 0, cap_wave = 0, grid = 0;
   bool has_cfg = false;          // shape fixed by cc_batch_set_config / cc_batch_autotune
   cc_batch_config cfg{};
+  SizeClass cls{};               // computed once (a handle's graphs do not change)
 };
 
-// Size class of a batch: log2 buckets of (graphs, largest graph, median graph).
-using SizeClass = std::tuple<int, int, int, int>;
 std::map<SizeClass, cc_batch_config> g_tuned;
 std::mutex g_tuned_mu;
 
@@ -198,9 +206,10 @@ void free_graph(cc_graph *g) {
   free_ws(g->ws);
   {
     BatchState &b = g->bs;
-    void *ptrs[] = {b.queue, b.heads, b.rounds, b.stat, b.err};
+    void *ptrs[] = {b.queue, b.out};
     for (void *p : ptrs)
       if (p) (void)hipFree(p);
+    if (b.host) (void)hipHostFree(b.host);
   }
   if (!g->borrowed) {
     if (g->off) (void)hipFree(g->off);
@@ -801,23 +810,23 @@ int32_t check_shape(const cc_graph *g, const cc_batch_config &c) {
   return CC_OK;
 }
 
+// The shape of a handle that was not tuned.  The largest graph bounds the
+// launch unless there are many, and more threads finish it sooner, so the
+// block is 1024.  With more than four graphs per compute unit the middle ones
+// run four to a workgroup.  Planted-block batches, (256, 512, 0) before / this:
+// 16 graphs 0.61 / 0.31 ms, 301 0.89 / 0.44, 1000 2.52 / 0.71, 4096 3.60 / 1.17
+// (C4); at 4096 (1024, 256, 1024) takes 1.48 ms and at 301 (1024, 384, 1792) 0.51.
 cc_batch_config default_shape(const cc_graph *g) {
-  // one wave per graph while four wave slots fit beside the largest graph's slot
-  cc_batch_config c{256, 0, 0, 0, 0.0};
-  int64_t mx = 0;
-  for (int32_t i = 0; i < g->num_graphs; i++) mx = std::max(mx, graph_n(g, i));
-  c.wave_max_n = (int)std::min<int64_t>(512, std::max<int64_t>(64, mx / 4));
-  return c;
+  return g->num_graphs > 1024 ? cc_batch_config{1024, 384, 1792, 0, 0.0} : cc_batch_config{1024, 256, 1024, 0, 0.0};
 }
 
 int32_t ensure_batch(cc_graph *g) {
   BatchState &b = g->bs;
-  if (b.queue) return CC_OK;
-  HIP_TRY(dalloc(&b.queue, (size_t)g->num_graphs));
-  HIP_TRY(dalloc(&b.heads, 3));
-  HIP_TRY(dalloc(&b.rounds, (size_t)g->num_graphs));
-  HIP_TRY(dalloc(&b.stat, 4));
-  HIP_TRY(dalloc(&b.err, 1));
+  if (b.queue && b.host) return CC_OK;
+  if (!b.queue) HIP_TRY(dalloc(&b.queue, (size_t)g->num_graphs));
+  const size_t bytes = batch_out_bytes(g->num_graphs);
+  if (!b.out) HIP_TRY(dalloc((char **)&b.out, bytes));
+  if (!b.host) HIP_TRY(hipHostMalloc((void **)&b.host, bytes, hipHostMallocDefault));
   return CC_OK;
 }
 
@@ -827,6 +836,8 @@ int32_t ensure_batch(cc_graph *g) {
 int32_t build_queue(cc_graph *g, const cc_batch_config &c, hipStream_t s) {
   BatchState &b = g->bs;
   if (b.q_block == c.block && b.q_wave == c.wave_max_n && b.q_quad == c.quad_max_n) return CC_OK;
+  if (int32_t rc = check_shape(g, c)) return rc;
+  b.q_block = 0;
   std::vector<int32_t> part[3];
   for (int32_t i = 0; i < g->num_graphs; i++) part[tier_of(graph_n(g, i), c)].push_back(i);
   auto work = [&](int32_t i) { return 2 * g->m_per_graph[(size_t)i] + graph_n(g, i); };
@@ -838,7 +849,14 @@ int32_t build_queue(cc_graph *g, const cc_batch_config &c, hipStream_t s) {
   }
   HIP_TRY(hipMemcpyAsync(b.queue, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
-  shape_lds(g, c, &b.cap_big, &b.cap_quad, &b.cap_wave, &b.n_big, &b.n_quad);
+  const size_t lds = shape_lds(g, c, &b.cap_big, &b.cap_quad, &b.cap_wave, &b.n_big, &b.n_quad);
+  HIP_TRY(batched_max_grid(c.block, lds, &b.grid));
+  if (b.grid < 1) return fail(CC_ERR_DEVICE, "batched kernel does not fit on a compute unit");
+  const int waves = c.block / 64, quads = c.block / 256;
+  const int64_t nsmall = g->num_graphs - b.n_big - b.n_quad;
+  const int64_t need =
+      std::max<int64_t>(1, b.n_big + (b.n_quad + quads - 1) / quads + (nsmall + waves - 1) / waves);
+  if (need < b.grid) b.grid = (int)need;
   b.q_block = c.block;
   b.q_wave = c.wave_max_n;
   b.q_quad = c.quad_max_n;
@@ -850,20 +868,10 @@ int32_t launch_batch(cc_graph *g, int algo, const int32_t *d_order, int64_t eps_
                      const cc_batch_config &c, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   BatchState &b = g->bs;
   if (int32_t rc = build_queue(g, c, s)) return rc;
-  const size_t lds = batched_lds_bytes(c.block, b.cap_big, b.cap_quad, b.cap_wave);
-  int grid = 0;
-  HIP_TRY(batched_max_grid(c.block, lds, &grid));
-  if (grid < 1) return fail(CC_ERR_DEVICE, "batched kernel does not fit on a compute unit");
-  const int waves = c.block / 64, quads = c.block / 256;
-  const int64_t nsmall = g->num_graphs - b.n_big - b.n_quad;
-  const int64_t need =
-      std::max<int64_t>(1, b.n_big + (b.n_quad + quads - 1) / quads + (nsmall + waves - 1) / waves);
-  if (need < grid) grid = (int)need;
-  HIP_TRY(hipMemsetAsync(b.heads, 0, 3 * sizeof(unsigned), s));
-  HIP_TRY(hipMemsetAsync(b.stat, 0, 4 * sizeof(unsigned long long), s));
-  HIP_TRY(hipMemsetAsync(b.err, 0, sizeof(int), s));
+  HIP_TRY(hipMemsetAsync(b.out, 0, offsetof(BatchOut, rounds), s));
   BatchLaunch bl{g->off, g->col, g->vtx_ptr, d_order, d_labels, b.queue, b.n_big, b.n_quad, g->num_graphs,
-                 b.cap_big, b.cap_quad, b.cap_wave, b.heads, b.rounds, b.stat, b.err, algo, eps_q, c.block, grid};
+                 b.cap_big, b.cap_quad, b.cap_wave, b.out->heads, b.out->rounds, b.out->stat, &b.out->err, algo, eps_q,
+                 c.block, b.grid};
   if (ev0) HIP_TRY(hipEventRecord(ev0, s));
   HIP_TRY(launch_batched(bl, s));
   if (ev1) HIP_TRY(hipEventRecord(ev1, s));
@@ -907,39 +915,32 @@ int32_t run_batch(cc_graph *g, int algo, const int32_t *order, double eps, int32
   BatchState &b = g->bs;
   cc_batch_config c = b.cfg;
   if (!b.has_cfg) {
-    int arch = 0, max_lds = 0;
-    if (int32_t rc = device_arch(&arch, &max_lds)) return rc;
+    if (b.cls == SizeClass{}) {  // (num_graphs >= 2: never the empty class)
+      int arch = 0, max_lds = 0;
+      if (int32_t rc = device_arch(&arch, &max_lds)) return rc;
+      b.cls = size_class(g, arch);
+    }
     std::lock_guard<std::mutex> lk(g_tuned_mu);
-    auto it = g_tuned.find(size_class(g, arch));
+    auto it = g_tuned.find(b.cls);
     c = it != g_tuned.end() ? it->second : default_shape(g);
   }
-  if (int32_t rc = check_shape(g, c)) return rc;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  HIP_TRY(hipEventCreate(&ev0));
-  HIP_TRY(hipEventCreate(&ev1));
-  struct EvGuard {
-    hipEvent_t a, b;
-    ~EvGuard() {
-      (void)hipEventDestroy(a);
-      (void)hipEventDestroy(b);
-    }
-  } evg{ev0, ev1};
+  const hipEvent_t ev0 = g->ws.ev0, ev1 = g->ws.ev1;
   // labels go to the workspace first, so a failing graph leaves the caller's untouched
   if (int32_t rc = launch_batch(g, algo, d_order, eps_q, g->ws.label_buf, c, s, ev0, ev1)) return rc;
-  int herr = 0;
-  unsigned long long hst[4];
-  HIP_TRY(hipMemcpyAsync(&herr, b.err, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(hst, b.stat, sizeof(hst), hipMemcpyDeviceToHost, s));
-  std::vector<int32_t> rounds((size_t)g->num_graphs);
-  HIP_TRY(hipMemcpyAsync(rounds.data(), b.rounds, sizeof(int32_t) * rounds.size(), hipMemcpyDeviceToHost, s));
+  const bool on_dev = (flags & CC_OUTPUT_ON_DEVICE) != 0;
+  if (on_dev) HIP_TRY(launch_deliver(g->ws.label_buf, labels, g->n, &b.out->err, s));
+  HIP_TRY(hipMemcpyAsync(b.host, b.out, batch_out_bytes(g->num_graphs), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (herr) return batch_error(herr);
-  HIP_TRY(hipMemcpyAsync(labels, g->ws.label_buf, sizeof(int32_t) * (size_t)g->n,
-                         (flags & CC_OUTPUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  if (b.host->err) return batch_error(b.host->err);
+  if (!on_dev) {
+    HIP_TRY(hipMemcpyAsync(labels, g->ws.label_buf, sizeof(int32_t) * (size_t)g->n, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
+  const int32_t *rounds = b.host->rounds;
+  const unsigned long long *hst = b.host->stat;
   if (stats) {
     int64_t mx = 0;
-    for (int32_t r : rounds) mx = std::max<int64_t>(mx, r);
+    for (int32_t i = 0; i < g->num_graphs; i++) mx = std::max<int64_t>(mx, rounds[i]);
     stats->rounds = mx;
     stats->scanned_elect = (int64_t)hst[0];
     stats->scanned_claim = (int64_t)hst[1];
@@ -952,7 +953,7 @@ int32_t run_batch(cc_graph *g, int algo, const int32_t *order, double eps, int32
     stats->loop_ms = ms;
     stats->policy_fallback = 0;
     stats->truncated = 0;
-    if (stats->graph_rounds) std::memcpy(stats->graph_rounds, rounds.data(), sizeof(int32_t) * rounds.size());
+    if (stats->graph_rounds) std::memcpy(stats->graph_rounds, rounds, sizeof(int32_t) * (size_t)g->num_graphs);
   }
   return CC_OK;
 }
@@ -998,7 +999,7 @@ int32_t autotune_batch(cc_graph *g, int algo, const int32_t *order, double eps, 
         for (int rep = 0; rep < 3; rep++) {
           if (int32_t rc = launch_batch(g, algo, d_order, eps_q, g->ws.label_buf, c, s, ev0, ev1)) return rc;
           int herr = 0;
-          HIP_TRY(hipMemcpyAsync(&herr, g->bs.err, sizeof(int), hipMemcpyDeviceToHost, s));
+          HIP_TRY(hipMemcpyAsync(&herr, &g->bs.out->err, sizeof(int), hipMemcpyDeviceToHost, s));
           HIP_TRY(hipStreamSynchronize(s));
           if (herr) return batch_error(herr);
           float ms = 0.f;

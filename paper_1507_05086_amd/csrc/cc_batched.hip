@@ -13,6 +13,7 @@
 // boundaries inside mixed windows with one LDS scatter and a wave scan.
 #include "cc_device.h"
 #include "cc_launch.h"
+#include "cc_round.h"
 
 namespace ccd {
 
@@ -165,14 +166,10 @@ struct Slot {
   }
 };
 
-__device__ inline long long bt_batch(long long eps_q, long long n_rem, long long delta) {
-  if (delta <= 0) return n_rem;
-  const long long num = eps_q * n_rem, den = 1000000LL * delta;
-  long long b = (num + den - 1) / den;
-  if (b < 1) b = 1;
-  if (b > n_rem) b = n_rem;
-  return b;
-}
+// Four consecutive columns; rows start at any 4-byte address.
+struct __attribute__((packed, aligned(4))) Cols4 {
+  int32_t u[4];
+};
 
 // Edge-balanced pass over the rows of list[0..cnt): f(i, v, u) for every
 // entry u of row v = list[i]; row v is col0[rstart[v] .. rstart[v+1]).  `rs`
@@ -202,7 +199,7 @@ __device__ __forceinline__ int rows_pass(const GR &g, const int16_t *list, int c
   if (g.tid == 0) s.pref[cnt] = total;
   g.sync();
   if (total == 0) return 0;
-  constexpr int NW = G / 64;
+  constexpr int NW = G / 64, V = 2;
   const int lane = lane_id();
   const int w = NW == 1 ? 0 : g.wave();
   int chunk = (total + NW - 1) / NW;
@@ -226,10 +223,20 @@ __device__ __forceinline__ int rows_pass(const GR &g, const int16_t *list, int c
         const int end = min(b0, c1);
         const int32_t v = list[lo];
         const int32_t *cp = col0 + (s.rstart[v] - s.pref[lo]);
-        for (int e = e0 + lane; e < end; e += 64 * K) {
+        int e = e0;
+        for (; e + 256 * V <= end; e += 256 * V) {  // 16-byte loads, V in flight per lane
+          Cols4 q[V];
+#pragma unroll
+          for (int k = 0; k < V; k++) q[k] = *reinterpret_cast<const Cols4 *>(cp + e + 256 * k + 4 * lane);
+#pragma unroll
+          for (int k = 0; k < V; k++)
+#pragma unroll
+            for (int x = 0; x < 4; x++) f(lo, v, q[k].u[x]);
+        }
+        for (; e < end; e += 64 * K) {
           int32_t u[K];
 #pragma unroll
-          for (int k = 0; k < K; k++) u[k] = e + 64 * k < end ? cp[e + 64 * k] : -1;
+          for (int k = 0; k < K; k++) u[k] = e + 64 * k + lane < end ? cp[e + 64 * k + lane] : -1;
 #pragma unroll
           for (int k = 0; k < K; k++)
             if (u[k] >= 0) f(lo, v, u[k]);
@@ -340,7 +347,7 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
       if ((s.fl[v] & F_UNC) && d > m) m = d;
     }
     const long long delta = g.max(m);
-    const int B = (int)bt_batch(a.eps_q, n_rem, delta);
+    const int B = (int)fixed_batch(a.eps_q, n_rem, delta);
     // active set: the next B unclustered vertices of pi from the cursor
     int na = 0;
     while (na < B && cur < n) {
