@@ -122,9 +122,8 @@ struct Workspace {
   HostOut *host = nullptr;    // pinned: what the host reads when a run has ended
   unsigned long long *progress = nullptr;  // pinned, coherent: k_close's progress word
   unsigned long long *progress_dev = nullptr;  // the same word as the device addresses it
-  int32_t *cost_size = nullptr;
+  int32_t *cost_size = nullptr, *cost_lab = nullptr;  // cost_lab: bpos
   long long *cost_acc = nullptr;
-  int *dev_err = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around a run's rounds
   std::vector<RoundGraph> graphs;
 };
@@ -189,7 +188,7 @@ void free_ws(Workspace &w) {
   void *ptrs[] = {w.rank, w.lab, w.ub, w.unc, w.state, w.flag, w.alist, w.clist, w.nlist, w.blist,
                   w.awork, w.cwork, w.rlist, w.xlist, w.rwork, w.xwork, w.racc, w.lvl, w.hist, w.plist, w.pwork,
                   w.cedge, w.tstat, w.ctrl, w.team, w.trace, w.order_buf, w.label_buf, w.sched, w.mlp, w.ainfo, w.cinfo,
-                  w.iorder, w.cost_size, w.cost_acc, w.dev_err, w.bpos, w.bpend, w.bdec, w.bdep, w.bq, w.bradj, w.omap_buf, w.ccol, w.cend};
+                  w.iorder, w.cost_size, w.cost_acc, w.bpos, w.bpend, w.bdec, w.bdep, w.bq, w.bradj, w.omap_buf, w.ccol, w.cend};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (w.host) (void)hipHostFree(w.host);
@@ -286,8 +285,8 @@ int32_t ensure_ws(cc_graph *g) {
   }
   HIP_TRY(dalloc(&w.mlp, CC_MLP_PARAMS));
   HIP_TRY(dalloc(&w.cost_size, n));
-  HIP_TRY(dalloc(&w.cost_acc, 2 * (size_t)g->num_graphs));
-  HIP_TRY(dalloc(&w.dev_err, 1));
+  w.cost_lab = w.bpos;
+  HIP_TRY(dalloc(&w.cost_acc, 2 * (size_t)g->num_graphs + 1));  // and the error word
   HIP_TRY(hipHostMalloc((void **)&w.host, sizeof(HostOut), hipHostMallocDefault));
   HIP_TRY(hipEventCreate(&w.ev0));
   HIP_TRY(hipEventCreate(&w.ev1));
@@ -1266,15 +1265,18 @@ int32_t cc_cost(const cc_graph *gc, const int32_t *labels, int64_t *cost, uint32
     HIP_TRY(hipMemcpyAsync(ws.label_buf, labels, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
     d_lab = ws.label_buf;
   }
-  const int none = 0x7fffffff;
-  HIP_TRY(hipMemcpyAsync(ws.dev_err, &none, sizeof(int), hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_cost(g->off, g->col, g->wall, n, g->vtx_ptr, g->gid, d_lab, ws.cost_size, ws.cost_acc,
-                      g->num_graphs, ws.dev_err, s));
-  std::vector<long long> acc(2 * (size_t)g->num_graphs);
-  int herr = none;
+  // the error word lies behind the sums, so one copy brings both back
+  const int none = 0x7f7f7f7f;  // above every code report() leaves
+  int *d_err = reinterpret_cast<int *>(ws.cost_acc + 2 * (size_t)g->num_graphs);
+  HIP_TRY(hipMemsetAsync(d_err, 0x7f, sizeof(int), s));
+  const CostGraph cg{g->off, g->col, g->wall, n, g->vtx_ptr, g->gid, g->num_graphs, g->roff, g->rcol, g->iperm, g->iso_start,
+                     g->nnz};
+  HIP_TRY(launch_cost(cg, d_lab, ws.cost_size, ws.cost_lab, ws.cost_acc, d_err, s));
+  std::vector<long long> acc(2 * (size_t)g->num_graphs + 1);
   HIP_TRY(hipMemcpyAsync(acc.data(), ws.cost_acc, sizeof(long long) * acc.size(), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&herr, ws.dev_err, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  int herr = none;
+  std::memcpy(&herr, &acc.back(), sizeof(int));
   if (herr != none) return fail(herr & 0xFF, "a label lies outside its graph");
   for (int32_t i = 0; i < g->num_graphs; i++)
     cost[i] = (int64_t)acc[2 * (size_t)i] + g->m_per_graph[(size_t)i] - (int64_t)acc[2 * (size_t)i + 1];

@@ -136,9 +136,22 @@ hipError_t launch_mlp_train_step(float *p, float *m, float *v, const float *x, c
                                  float lr, float *partial, int nblk, float *grad, float *loss, hipStream_t s);
 
 // Disagreement cost per graph: acc[2g] = pairs inside clusters, acc[2g+1] =
-// same-label adjacency entries (2 m_in); size is scratch [n].
-hipError_t launch_cost(const int64_t *off, const int32_t *col, const int64_t *wall, int64_t n,
-                       const int64_t *vtx_ptr, const int32_t *gid, const int32_t *labels, int32_t *size,
-                       long long *acc, int32_t num_graphs, int *err, hipStream_t s);
+// same-label adjacency entries (2 m_in).  A single graph (iperm set) is
+// scored on its renumbered rows, of which iso_start have entries; size and
+// lab are scratch [n].
+struct CostGraph {
+  const int64_t *off;
+  const int32_t *col;
+  const int64_t *wall;
+  int64_t n;
+  const int64_t *vtx_ptr;
+  const int32_t *gid;
+  int32_t num_graphs;
+  const int64_t *roff;
+  const int32_t *rcol, *iperm;
+  int64_t iso_start, nnz;
+};
+hipError_t launch_cost(const CostGraph &g, const int32_t *labels, int32_t *size, int32_t *lab, long long *acc, int *err,
+                       hipStream_t s);
 
 }  // namespace ccd
