@@ -84,9 +84,35 @@ struct HostOut {
   RoundRec trace[kHostTrace];
 };
 
-// Device workspace of a run (allocated on the first run of a graph).
+// Arrays cut from one allocation: an allocation and a free of their own per
+// array cost a graph's set-up and release more than its kernels (61 frees of
+// power law 1 M: 6.7 ms).  A layout runs twice, without a base to find the
+// size, then with it.
+struct Slab {
+  char *base = nullptr;
+  size_t used = 0;
+  template <class T>
+  void take(T *&p, size_t count) {
+    if (base) p = reinterpret_cast<T *>(base + used);
+    used += (sizeof(T) * (count > 0 ? count : 1) + 255) & ~(size_t)255;
+  }
+};
+template <class Layout>
+hipError_t slab_alloc(char **mem, Layout &&layout) {
+  Slab size;
+  layout(size);
+  const hipError_t e = hipMalloc((void **)mem, size.used);
+  if (e != hipSuccess) return e;
+  Slab cut{*mem, 0};
+  layout(cut);
+  return hipSuccess;
+}
+
+// Device workspace of a run (allocated on the first run of a graph; a batch
+// has no use for the round loop's arrays).
 struct Workspace {
   bool ready = false;
+  char *mem = nullptr;  // holds every device array but sched
   int32_t *rank = nullptr, *lab = nullptr, *ub = nullptr;
   uint32_t *unc = nullptr;
   uint8_t *state = nullptr, *flag = nullptr;
@@ -154,12 +180,20 @@ struct BatchState {
 std::map<SizeClass, cc_batch_config> g_tuned;
 std::mutex g_tuned_mu;
 
+// Where the bound bucket of each level starts, its first internal id, and its
+// vertices at the start of a run.
+struct LevelTab {
+  int64_t off[NLVL + 1], first[NLVL];
+  unsigned cnt[NLVL];
+};
+
 }  // namespace
 
 struct cc_graph {
   int64_t n = 0, nnz = 0;
   int32_t num_graphs = 1;
   bool borrowed = false;
+  char *mem = nullptr;         // holds the device arrays below (not off and col of a borrowed graph)
   int64_t *off = nullptr;
   int32_t *col = nullptr;
   int64_t *vtx_ptr = nullptr;  // device, batches only
@@ -172,9 +206,7 @@ struct cc_graph {
   int64_t low_start = 0;       // single graphs: internal ids >= low_start have degree < DSW,
   int64_t iso_start = 0;       // and those >= iso_start degree 0
   int64_t n_hi = 0;            // vertices with degree >= DSW
-  int32_t *lvl_init = nullptr; // device: initial bound buckets
-  int64_t *lvl_off = nullptr;  // device [NLVL+1]
-  unsigned *lvl_cnt0 = nullptr;  // device [NLVL]: initial entries per level
+  LevelTab *lvl = nullptr;     // device
   int64_t lvl_total = 0;
   std::vector<int64_t> h_vtx_ptr;
   std::vector<int64_t> m_per_graph;
@@ -185,12 +217,8 @@ struct cc_graph {
 namespace {
 
 void free_ws(Workspace &w) {
-  void *ptrs[] = {w.rank, w.lab, w.ub, w.unc, w.state, w.flag, w.alist, w.clist, w.nlist, w.blist,
-                  w.awork, w.cwork, w.rlist, w.xlist, w.rwork, w.xwork, w.racc, w.lvl, w.hist, w.plist, w.pwork,
-                  w.cedge, w.tstat, w.ctrl, w.team, w.trace, w.order_buf, w.label_buf, w.sched, w.mlp, w.ainfo, w.cinfo,
-                  w.iorder, w.cost_size, w.cost_acc, w.bpos, w.bpend, w.bdec, w.bdep, w.bq, w.bradj, w.omap_buf, w.ccol, w.cend};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
+  if (w.mem) (void)hipFree(w.mem);
+  if (w.sched) (void)hipFree(w.sched);
   if (w.host) (void)hipHostFree(w.host);
   if (w.ev0) (void)hipEventDestroy(w.ev0);
   if (w.ev1) (void)hipEventDestroy(w.ev1);
@@ -210,21 +238,7 @@ void free_graph(cc_graph *g) {
       if (p) (void)hipFree(p);
     if (b.host) (void)hipHostFree(b.host);
   }
-  if (!g->borrowed) {
-    if (g->off) (void)hipFree(g->off);
-    if (g->col) (void)hipFree(g->col);
-  }
-  if (g->vtx_ptr) (void)hipFree(g->vtx_ptr);
-  if (g->gid) (void)hipFree(g->gid);
-  if (g->wall) (void)hipFree(g->wall);
-  {
-    void *ptrs[] = {g->perm, g->iperm, g->rcol, g->roff};
-    for (void *p : ptrs)
-      if (p) (void)hipFree(p);
-  }
-  if (g->lvl_init) (void)hipFree(g->lvl_init);
-  if (g->lvl_off) (void)hipFree(g->lvl_off);
-  if (g->lvl_cnt0) (void)hipFree(g->lvl_cnt0);
+  if (g->mem) (void)hipFree(g->mem);
   delete g;
 }
 
@@ -232,65 +246,67 @@ int32_t ensure_ws(cc_graph *g) {
   Workspace &w = g->ws;
   if (w.ready) return CC_OK;
   const int64_t n = g->n > 0 ? g->n : 1;
-  HIP_TRY(dalloc(&w.rank, n));
-  HIP_TRY(dalloc(&w.lab, n));
-  HIP_TRY(dalloc(&w.ub, n));
-  HIP_TRY(dalloc(&w.unc, (size_t)(n + 31) / 32));
-  HIP_TRY(dalloc(&w.state, n));
-  HIP_TRY(dalloc(&w.flag, n + 3));  // marked by whole words
-  HIP_TRY(dalloc(&w.alist, n));
-  HIP_TRY(dalloc(&w.clist, n));
-  HIP_TRY(dalloc(&w.nlist, n));
-  HIP_TRY(dalloc(&w.blist, n));
-  HIP_TRY(dalloc(&w.awork, n));
-  HIP_TRY(dalloc(&w.cwork, n));
-  HIP_TRY(dalloc(&w.ainfo, n));
-  HIP_TRY(dalloc(&w.cinfo, n));
+  const bool single = g->num_graphs == 1;
   w.rcap = g->n_hi + 1;
-  HIP_TRY(dalloc(&w.rlist, (size_t)(DITER * w.rcap)));
-  HIP_TRY(dalloc(&w.rwork, (size_t)(DITER * w.rcap)));
-  HIP_TRY(dalloc(&w.racc, (size_t)(DITER * w.rcap)));
-  HIP_TRY(dalloc(&w.xlist, n));
-  HIP_TRY(dalloc(&w.xwork, n));
-  HIP_TRY(dalloc(&w.plist, n));
-  HIP_TRY(dalloc(&w.pwork, n));
-  HIP_TRY(dalloc(&w.lvl, (size_t)(g->lvl_total > 0 ? g->lvl_total : 1)));
   w.hist_len = g->max_deg + 2;
-  HIP_TRY(dalloc(&w.hist, (size_t)w.hist_len));
   w.cedge_cap = n > (1 << 20) ? n : (1 << 20);
-  HIP_TRY(dalloc(&w.cedge, (size_t)w.cedge_cap));
-  HIP_TRY(dalloc(&w.bpos, n));
-  HIP_TRY(dalloc(&w.bpend, n));
-  HIP_TRY(dalloc(&w.bdec, n));
-  HIP_TRY(dalloc(&w.bdep, n + 1));
-  HIP_TRY(dalloc(&w.bq, n));
-  HIP_TRY(dalloc(&w.bradj, (size_t)w.cedge_cap));
   w.tstat_cap = n / TSEL + 4096 + 2;
-  HIP_TRY(dalloc(&w.tstat, (size_t)w.tstat_cap));
-  HIP_TRY(hipMemset(w.tstat, 0, sizeof(unsigned long long) * (size_t)w.tstat_cap));
-  HIP_TRY(dalloc(&w.ctrl, 1));
-  HIP_TRY(dalloc(&w.team, 1));
   w.trace_cap = 1 << 16;
-  HIP_TRY(dalloc(&w.trace, (size_t)w.trace_cap));
-  HIP_TRY(dalloc(&w.order_buf, n));
-  HIP_TRY(dalloc(&w.label_buf, n));
-  HIP_TRY(dalloc(&w.iorder, n));
-  if (order_map_applies(n)) {
-    HIP_TRY(dalloc(&w.omap_buf, order_map_bytes(n)));
-    w.omap = order_map_layout(n, w.omap_buf);
-  }
-  if (g->num_graphs == 1) {  // the round loop's compacted rows (written at its switch to exact degrees)
-    HIP_TRY(dalloc(&w.ccol, (size_t)(g->nnz > 0 ? g->nnz : 1)));
-    HIP_TRY(dalloc(&w.cend, n));
-  }
-  HIP_TRY(dalloc(&w.mlp, CC_MLP_PARAMS));
-  HIP_TRY(dalloc(&w.cost_size, n));
+  const bool omap = single && order_map_applies(n);
+  const auto layout = [&](Slab &m) {
+    m.take(w.order_buf, n);
+    m.take(w.label_buf, n);
+    m.take(w.mlp, CC_MLP_PARAMS);
+    m.take(w.cost_size, n);
+    m.take(w.cost_acc, 2 * (size_t)g->num_graphs + 1);  // and the error word
+    if (!single) return;
+    m.take(w.rank, n);
+    m.take(w.lab, n);
+    m.take(w.ub, n);
+    m.take(w.unc, (size_t)(n + 31) / 32);
+    m.take(w.state, n);
+    m.take(w.flag, n + 3);  // marked by whole words
+    m.take(w.alist, n);
+    m.take(w.clist, n);
+    m.take(w.nlist, n);
+    m.take(w.blist, n);
+    m.take(w.awork, n);
+    m.take(w.cwork, n);
+    m.take(w.ainfo, n);
+    m.take(w.cinfo, n);
+    m.take(w.rlist, (size_t)(DITER * w.rcap));
+    m.take(w.rwork, (size_t)(DITER * w.rcap));
+    m.take(w.racc, (size_t)(DITER * w.rcap));
+    m.take(w.xlist, n);
+    m.take(w.xwork, n);
+    m.take(w.plist, n);
+    m.take(w.pwork, n);
+    m.take(w.lvl, (size_t)g->lvl_total);
+    m.take(w.hist, (size_t)w.hist_len);
+    m.take(w.cedge, (size_t)w.cedge_cap);
+    m.take(w.bpos, n);
+    m.take(w.bpend, n);
+    m.take(w.bdec, n);
+    m.take(w.bdep, n + 1);
+    m.take(w.bq, n);
+    m.take(w.bradj, (size_t)w.cedge_cap);
+    m.take(w.tstat, (size_t)w.tstat_cap);
+    m.take(w.ctrl, 1);
+    m.take(w.team, 1);
+    m.take(w.trace, (size_t)w.trace_cap);
+    m.take(w.iorder, n);
+    if (omap) m.take(w.omap_buf, order_map_bytes(n));
+    m.take(w.ccol, (size_t)g->nnz);  // the round loop's compacted rows (written at its switch to exact degrees)
+    m.take(w.cend, n);
+  };
+  if (!w.mem) HIP_TRY(slab_alloc(&w.mem, layout));
+  if (omap) w.omap = order_map_layout(n, w.omap_buf);
   w.cost_lab = w.bpos;
-  HIP_TRY(dalloc(&w.cost_acc, 2 * (size_t)g->num_graphs + 1));  // and the error word
-  HIP_TRY(hipHostMalloc((void **)&w.host, sizeof(HostOut), hipHostMallocDefault));
-  HIP_TRY(hipEventCreate(&w.ev0));
-  HIP_TRY(hipEventCreate(&w.ev1));
-  HIP_TRY(hipHostMalloc((void **)&w.progress, sizeof(unsigned long long), hipHostMallocCoherent | hipHostMallocMapped));
+  if (single) HIP_TRY(hipMemset(w.tstat, 0, sizeof(unsigned long long) * (size_t)w.tstat_cap));
+  if (!w.host) HIP_TRY(hipHostMalloc((void **)&w.host, sizeof(HostOut), hipHostMallocDefault));
+  if (!w.ev0) HIP_TRY(hipEventCreate(&w.ev0));
+  if (!w.ev1) HIP_TRY(hipEventCreate(&w.ev1));
+  if (!w.progress) HIP_TRY(hipHostMalloc((void **)&w.progress, sizeof(unsigned long long), hipHostMallocCoherent | hipHostMallocMapped));
   HIP_TRY(hipHostGetDevicePointer((void **)&w.progress_dev, w.progress, 0));
   w.ready = true;
   return CC_OK;
@@ -469,7 +485,9 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
   w.plist = ws.plist;
   w.pwork = ws.pwork;
   w.lvl = ws.lvl;
-  w.lvl_off = g->lvl_off;
+  w.lvl_off = g->lvl->off;
+  w.lvl_first = g->lvl->first;
+  w.lvl_cnt0 = g->lvl->cnt;
   w.hist = ws.hist;
   w.cedge = ws.cedge;
   w.cedge_cap = ws.cedge_cap;
@@ -527,9 +545,7 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
       HIP_TRY(hipMemsetAsync(ws.state, 0, (size_t)n, s));  // k_check_order marks the vertices pi names
     }
     HIP_TRY(hipMemsetAsync(ws.hist, 0, sizeof(int) * (size_t)ws.hist_len, s));
-    if (g->lvl_total > 0)
-      HIP_TRY(hipMemcpyAsync(ws.lvl, g->lvl_init, sizeof(int32_t) * (size_t)g->lvl_total, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_init(w, g->lvl_cnt0, s));
+    HIP_TRY(launch_init(w, s));
   }
 
   LaunchShape ls{512, 1024, 512, 0, w.start_exact};
@@ -1066,16 +1082,57 @@ int32_t cc_graph_from_csr(int32_t num_graphs, const int64_t *vtx_ptr, int64_t n_
     hv = {0, n_total};
   }
   int64_t nnz = 0;
-  if (on_dev) HIP_TRY(hipMemcpy(&nnz, offsets + n_total, sizeof(int64_t), hipMemcpyDeviceToHost));
-  else nnz = offsets[n_total];
-  if (nnz < 0 || nnz >= ((int64_t)1 << 33)) return fail(CC_ERR_INVALID_ARG, "offsets[n] must lie in [0, 2^33)");
-  if (nnz > 0 && !cols) return fail(CC_ERR_INVALID_ARG, "cols is NULL");
+  const auto check_nnz = [&]() -> int32_t {
+    if (nnz < 0 || nnz >= ((int64_t)1 << 33)) return fail(CC_ERR_INVALID_ARG, "offsets[n] must lie in [0, 2^33)");
+    if (nnz > 0 && !cols) return fail(CC_ERR_INVALID_ARG, "cols is NULL");
+    return CC_OK;
+  };
+  if (!on_dev) {
+    nnz = offsets[n_total];
+    if (int32_t rc = check_nnz()) return rc;
+  }
+  // scratch of the set-up, freed at its end
+  struct Scratch {
+    char *mem = nullptr;
+    int64_t *blocksum, *found, *ends, *binoff, *rdeg;
+    unsigned *bins;
+    int *err;
+    unsigned long long *above;
+    ~Scratch() {
+      if (mem) (void)hipFree(mem);
+    }
+  } t;
+  HIP_TRY(slab_alloc(&t.mem, [&](Slab &m) {
+    m.take(t.blocksum, (size_t)(n_total / (4 * BS) + 4));
+    m.take(t.found, 3);
+    m.take(t.ends, (size_t)num_graphs + 1);
+    m.take(t.err, 1);
+    m.take(t.above, 1);
+    if (num_graphs > 1) return;
+    m.take(t.bins, 2 * RELABEL_BINS + 1);
+    m.take(t.binoff, RELABEL_BINS);
+    m.take(t.rdeg, (size_t)n_total);
+  }));
+  // offsets must start at 0 and never decrease: checked on the device, before
+  // anything there uses them
+  int64_t found[3];
+  const auto check_offsets = [&](const int64_t *off) {
+    hipError_t e = launch_offsets_check(off, n_total, t.found, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(found, t.found, sizeof(found), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  };
+  if (on_dev) {
+    HIP_TRY(check_offsets(offsets));
+    nnz = found[0];
+    if (int32_t rc = check_nnz()) return rc;
+  }
 
   cc_graph *g = new cc_graph();
   g->n = n_total;
   g->nnz = nnz;
   g->num_graphs = num_graphs;
   g->h_vtx_ptr = hv;
+  g->borrowed = (flags & CC_BORROW) != 0;
   auto bail = [&](int32_t rc) {
     free_graph(g);
     return rc;
@@ -1088,115 +1145,84 @@ int32_t cc_graph_from_csr(int32_t num_graphs, const int64_t *vtx_ptr, int64_t n_
                        std::string(#expr) + ": " + hipGetErrorString(e_)));            \
   } while (0)
 
-  if (flags & CC_BORROW) {
-    g->borrowed = true;
+  const auto layout = [&](Slab &m) {
+    if (!g->borrowed) {
+      m.take(g->off, (size_t)n_total + 1);
+      m.take(g->col, (size_t)nnz);
+    }
+    m.take(g->wall, (size_t)n_total + 1);
+    if (num_graphs > 1) {
+      m.take(g->vtx_ptr, (size_t)num_graphs + 1);
+      m.take(g->gid, (size_t)n_total);
+      return;
+    }
+    m.take(g->lvl, 1);
+    m.take(g->perm, (size_t)n_total);
+    m.take(g->iperm, (size_t)n_total);
+    m.take(g->roff, (size_t)n_total + 1);
+    m.take(g->rcol, (size_t)nnz);
+  };
+  G_TRY(slab_alloc(&g->mem, layout));
+  if (g->borrowed) {
     g->off = const_cast<int64_t *>(offsets);
     g->col = const_cast<int32_t *>(cols);
   } else {
-    G_TRY(dalloc(&g->off, (size_t)n_total + 1));
-    G_TRY(dalloc(&g->col, (size_t)nnz));
     const hipMemcpyKind kind = on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     G_TRY(hipMemcpyAsync(g->off, offsets, sizeof(int64_t) * ((size_t)n_total + 1), kind, s));
     if (nnz > 0) G_TRY(hipMemcpyAsync(g->col, cols, sizeof(int32_t) * (size_t)nnz, kind, s));
   }
-  // offsets must start at 0 and never decrease (checked on the host copy)
-  {
-    std::vector<int64_t> ho;
-    const int64_t *po = offsets;
-    if (on_dev) {
-      ho.resize((size_t)n_total + 1);
-      G_TRY(hipMemcpyAsync(ho.data(), g->off, sizeof(int64_t) * ho.size(), hipMemcpyDeviceToHost, s));
-      G_TRY(hipStreamSynchronize(s));
-      po = ho.data();
-    }
-    if (po[0] != 0) return bail(fail(CC_ERR_INVALID_ARG, "offsets[0] must be 0"));
-    for (int64_t v = 0; v < n_total; v++)
-      if (po[v + 1] < po[v]) return bail(fail(CC_ERR_INVALID_ARG, "offsets must not decrease"));
-    g->m_per_graph.resize((size_t)num_graphs);
-    for (int32_t i = 0; i < num_graphs; i++)
-      g->m_per_graph[(size_t)i] = (po[hv[(size_t)i + 1]] - po[hv[(size_t)i]]) / 2;
-  }
+  if (!on_dev) G_TRY(check_offsets(g->off));
+  if (found[1]) return bail(fail(CC_ERR_INVALID_ARG, "offsets[0] must be 0"));
+  if (found[2]) return bail(fail(CC_ERR_INVALID_ARG, "offsets must not decrease"));
+  g->m_per_graph.assign((size_t)num_graphs, nnz / 2);
   if (num_graphs > 1) {
-    G_TRY(dalloc(&g->vtx_ptr, (size_t)num_graphs + 1));
     G_TRY(hipMemcpyAsync(g->vtx_ptr, hv.data(), sizeof(int64_t) * hv.size(), hipMemcpyHostToDevice, s));
-    G_TRY(dalloc(&g->gid, (size_t)n_total));
+    std::vector<int64_t> ends(hv.size());
+    G_TRY(launch_gather64(g->off, g->vtx_ptr, num_graphs + 1, t.ends, s));
+    G_TRY(hipMemcpyAsync(ends.data(), t.ends, sizeof(int64_t) * ends.size(), hipMemcpyDeviceToHost, s));
+    G_TRY(hipStreamSynchronize(s));
+    for (size_t i = 0; i < (size_t)num_graphs; i++) g->m_per_graph[i] = (ends[i + 1] - ends[i]) / 2;
   }
-  G_TRY(dalloc(&g->wall, (size_t)n_total + 1));
-  int64_t *blocksum = nullptr;
-  int *derr = nullptr;
-  const int64_t nb = (n_total + (int64_t)BS * 4 - 1) / ((int64_t)BS * 4);
-  G_TRY(dalloc(&blocksum, (size_t)nb + 2));
-  G_TRY(dalloc(&derr, 1));
   const int none = 0x7fffffff;
-  hipError_t e = hipMemcpyAsync(derr, &none, sizeof(int), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = launch_graph_setup(g->off, g->col, n_total, g->vtx_ptr, num_graphs, g->gid, g->wall, blocksum,
-                           (flags & CC_VALIDATE) ? 1 : 0, derr, s);
   int herr = none;
-  if (e == hipSuccess) e = hipMemcpyAsync(&herr, derr, sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(blocksum);
-  (void)hipFree(derr);
-  G_TRY(e);
-  if (herr == none && n_total > 0 && num_graphs == 1) {
-    G_TRY(dalloc(&g->perm, (size_t)n_total));
-    G_TRY(dalloc(&g->iperm, (size_t)n_total));
-    G_TRY(dalloc(&g->roff, (size_t)n_total + 1));
-    G_TRY(dalloc(&g->rcol, (size_t)nnz));
-    unsigned *cnt = nullptr;
-    int64_t *binoff = nullptr, *rdeg = nullptr, *bsum = nullptr;
-    hipError_t re = dalloc(&cnt, 2 * (NLVL + 1));
-    if (re == hipSuccess) re = dalloc(&binoff, NLVL + 1);
-    if (re == hipSuccess) re = dalloc(&rdeg, (size_t)n_total);
-    if (re == hipSuccess) re = dalloc(&bsum, (size_t)(n_total / (4 * BS) + 4));
-    if (re == hipSuccess)
-      re = launch_relabel(g->off, g->col, g->wall, n_total, cnt, binoff, g->perm, g->iperm, rdeg, g->roff, bsum,
-                          g->rcol, &g->low_start, &g->iso_start, s);
-    if (re == hipSuccess) re = hipStreamSynchronize(s);
-    void *tmp[] = {cnt, binoff, rdeg, bsum};
-    for (void *p : tmp)
-      if (p) (void)hipFree(p);
-    G_TRY(re);
+  CheckArgs check{g->off, g->col, g->wall, n_total, g->vtx_ptr, g->gid, (flags & CC_VALIDATE) ? 1 : 0, t.err, t.above};
+  const auto read_check = [&] {
+    const hipError_t e = hipMemcpyAsync(&herr, t.err, sizeof(int), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  };
+  G_TRY(hipMemcpyAsync(t.err, &none, sizeof(int), hipMemcpyHostToDevice, s));
+  G_TRY(hipMemsetAsync(t.above, 0, sizeof(*t.above), s));
+  G_TRY(launch_graph_setup(check, num_graphs, g->gid, g->wall, t.blocksum, s));
+  G_TRY(read_check());
+  if (herr == CHECK_AGAIN) {
+    check.validate = 2;
+    G_TRY(hipMemcpyAsync(t.err, &none, sizeof(int), hipMemcpyHostToDevice, s));
+    G_TRY(launch_graph_check(check, s));
+    G_TRY(read_check());
   }
-  if (herr == none && n_total > 0) {
+  if (herr == none && num_graphs == 1) {
+    unsigned bins[RELABEL_BINS];
+    G_TRY(launch_relabel(g->off, g->col, g->wall, n_total, t.bins, t.binoff, g->perm, g->iperm, t.rdeg, g->roff,
+                         t.blocksum, g->rcol, bins, &g->max_deg, s));
     // bound buckets: capacity of level k = vertices of degree >= 2^k (internal ids)
-    const int64_t *xoff = g->roff ? g->roff : g->off;
-    unsigned *dcnt = nullptr;
-    int *dmax = nullptr;
-    G_TRY(dalloc(&dcnt, NLVL));
-    G_TRY(dalloc(&dmax, 1));
-    G_TRY(hipMemsetAsync(dcnt, 0, sizeof(unsigned) * NLVL, s));
-    G_TRY(hipMemsetAsync(dmax, 0, sizeof(int), s));
-    G_TRY(launch_level_count(xoff, n_total, dcnt, dmax, s));
-    unsigned hcnt[NLVL];
-    int hmax = 0;
-    G_TRY(hipMemcpyAsync(hcnt, dcnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
-    G_TRY(hipMemcpyAsync(&hmax, dmax, sizeof(int), hipMemcpyDeviceToHost, s));
-    G_TRY(hipStreamSynchronize(s));
-    g->max_deg = hmax;
-    int64_t hoff[NLVL + 1];
-    int64_t acc = 0, hi = 0;
-    for (int k = 0; k < NLVL; k++) {
-      int64_t cap = 0;
-      if (k >= LVL_MIN)
-        for (int j = k; j < NLVL; j++) cap += hcnt[j];
-      hoff[k] = acc;
-      acc += cap;
-      hi += hcnt[k];
+    LevelTab tab{};
+    int64_t above = 0;
+    for (int b = 0; b < NLVL; b++) {  // bin b: level NLVL - 1 - b
+      const int k = NLVL - 1 - b;
+      tab.first[k] = above;
+      above += bins[b];
+      if (k >= LVL_MIN) {
+        tab.cnt[k] = bins[b];
+        tab.off[k + 1] = above;  // its capacity, summed below
+        g->low_start = above;
+      }
     }
-    hoff[NLVL] = acc;
-    g->lvl_total = acc;
-    g->n_hi = hi;
-    G_TRY(dalloc(&g->lvl_off, NLVL + 1));
-    G_TRY(dalloc(&g->lvl_cnt0, NLVL));
-    G_TRY(dalloc(&g->lvl_init, (size_t)(acc > 0 ? acc : 1)));
-    G_TRY(hipMemcpyAsync(g->lvl_off, hoff, sizeof(hoff), hipMemcpyHostToDevice, s));
-    G_TRY(hipMemcpyAsync(g->lvl_cnt0, hcnt, sizeof(hcnt), hipMemcpyHostToDevice, s));
-    G_TRY(hipMemsetAsync(dcnt, 0, sizeof(unsigned) * NLVL, s));
-    G_TRY(launch_level_fill(xoff, n_total, g->lvl_off, dcnt, g->lvl_init, s));
+    g->iso_start = above;
+    g->n_hi = g->low_start;
+    for (int k = 0; k < NLVL; k++) tab.off[k + 1] += tab.off[k];
+    g->lvl_total = tab.off[NLVL];
+    G_TRY(hipMemcpyAsync(g->lvl, &tab, sizeof(tab), hipMemcpyHostToDevice, s));
     G_TRY(hipStreamSynchronize(s));
-    (void)hipFree(dcnt);
-    (void)hipFree(dmax);
   }
   if (herr != none) {
     herr &= 0xFF;

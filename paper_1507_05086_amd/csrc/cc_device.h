@@ -256,6 +256,8 @@ struct Ws {
   // bound buckets
   int32_t *lvl;         // entries of all levels
   const int64_t *lvl_off;  // [NLVL+1] start of each level in lvl (device)
+  const int64_t *lvl_first;  // [NLVL] a level's first internal id (ids are grouped by level), and
+  const unsigned *lvl_cnt0;  // [NLVL] its vertices, at the start of a run (levels from LVL_MIN on)
   int *hist;            // exact phase: vertices per remaining degree, [max_deg + 1]
   Ctrl *ctrl;
   RoundRec *trace;
@@ -287,12 +289,7 @@ struct Ws {
 constexpr int PROGRESS_DONE = 32, PROGRESS_EXACT = 33, PROGRESS_ERROR = 34, PROGRESS_LEFT = 35, PROGRESS_RAN = 36;
 
 __host__ __device__ inline int level_of(int64_t x) {  // floor(log2(x)), x >= 1
-  int l = 0;
-  while ((x >> 1) > 0) {
-    x >>= 1;
-    l++;
-  }
-  return l;
+  return 63 - __builtin_clzll((unsigned long long)x);
 }
 
 // ------------------------------------------------------------- atomics ----

@@ -83,35 +83,29 @@ hipError_t launch_row_weights(const int64_t *off, int64_t n, int64_t *wall, int6
 
 // ---------------------------------------------------------------- checks --
 
-struct CheckArgs {
-  const int64_t *off;
-  const int32_t *col;
-  const int64_t *wall;
-  int64_t n;
-  const int64_t *vtx_ptr;  // device, or null
-  const int32_t *gid;      // device per-row graph id, or null
-  int validate;
-  int *err;                // (priority << 8 | cc_status code) of the worst failure, 0x7fffffff = none
-};
-
 // A column outside its graph outranks every other finding (the others may be
 // its consequences); then the smallest code wins.
 __device__ inline void report(int *err, int code) { atomicMin(err, ((code == 10 ? 0 : 1) << 8) | code); }
 
-__device__ inline bool row_contains(const int64_t *off, const int32_t *col, int64_t row, int32_t x) {
-  int64_t lo = off[row], hi = off[row + 1];
-  while (lo < hi) {
-    const int64_t mid = lo + ((hi - lo) >> 1);
-    if (col[mid] < x) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo < off[row + 1] && col[lo] == x;
-}
-
+// Every entry: its column's range and, validating, self-loops, the order in
+// its row, and its mirror entry by binary search.  Validate == 1 searches for
+// one entry of each pair only, the one in the longer row, so the search is
+// in the shorter one; the entries of both kinds are counted (*above: searched
+// minus not searched).  Rows without repeats, every searched entry mirrored
+// and equal counts make the mirror map one-to-one and onto, so the graph is
+// symmetric.  Anything else found is reported as CHECK_AGAIN, and validate
+// == 2 (every entry searched) names it.  Power law 1 M, 40 M entries, dependent
+// cold reads of the search: 4.1 ms with every entry searched, 2.0 ms with
+// half of them, and those in the shorter row.
 __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
+  long long above = 0;
   lb_walk(nullptr, a.wall, a.n, a.wall[a.n], a.off, a.off + 1, a.col, nullptr, nullptr, [&](Items &it) {
+    int32_t x[IPT];                      // x[k] >= 0: look for it in a row, whose
+    int64_t lo[IPT], hi[IPT], end[IPT];  // entries from lo on are not smaller
 #pragma unroll
     for (int k = 0; k < IPT; k++) {
+      lo[k] = hi[k] = end[k] = 0;
+      x[k] = -1;
       if (!(it.edge >> k & 1)) continue;
       const int32_t v = it.v[k], u = it.u[k];
       int64_t base = 0, ng = a.n;
@@ -126,12 +120,88 @@ __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
       }
       if (!a.validate) continue;
       const int32_t vl = (int32_t)(v - base);
-      if (u == vl) report(a.err, 3);  // CC_ERR_SELF_LOOP
       const int64_t e = it.pos[k];
-      if (e + 1 < a.off[v + 1] && a.col[e + 1] <= u) report(a.err, 4);  // CC_ERR_DUPLICATE_EDGE
-      if (!row_contains(a.off, a.col, base + u, vl)) report(a.err, 2);   // CC_ERR_NOT_SYMMETRIC
+      const bool loop = u == vl, disorder = e + 1 < a.off[v + 1] && a.col[e + 1] <= u;
+      if (a.validate == 2) {
+        if (loop) report(a.err, 3);      // CC_ERR_SELF_LOOP
+        if (disorder) report(a.err, 4);  // CC_ERR_DUPLICATE_EDGE
+      } else if (loop || disorder) {
+        atomicMin(a.err, CHECK_AGAIN);
+      }
+      const int64_t r0 = a.off[base + u], r1 = a.off[base + u + 1];
+      const int64_t du = r1 - r0, dv = it.deg[k];
+      const bool search = a.validate == 2 || du < dv || (du == dv && u < vl);
+      above += search ? 1 : -1;
+      if (search) {
+        lo[k] = r0;
+        hi[k] = end[k] = r1;
+        x[k] = vl;
+      }
     }
+    if (!a.validate) return;
+    // the searches of this thread's entries step together
+    bool more = true;
+    while (more) {
+      more = false;
+      int32_t c[IPT];
+#pragma unroll
+      for (int k = 0; k < IPT; k++)
+        if (lo[k] < hi[k]) c[k] = a.col[lo[k] + ((hi[k] - lo[k]) >> 1)];
+#pragma unroll
+      for (int k = 0; k < IPT; k++)
+        if (lo[k] < hi[k]) {
+          const int64_t mid = lo[k] + ((hi[k] - lo[k]) >> 1);
+          if (c[k] < x[k]) lo[k] = mid + 1;
+          else hi[k] = mid;
+          more |= lo[k] < hi[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < IPT; k++)
+      if (x[k] >= 0 && !(lo[k] < end[k] && a.col[lo[k]] == x[k])) {
+        if (a.validate == 2) report(a.err, 2);  // CC_ERR_NOT_SYMMETRIC
+        else atomicMin(a.err, CHECK_AGAIN);
+      }
   });
+  if (a.validate == 1) {
+    const int64_t t = wave_sum((int64_t)above);
+    if (lane_id() == 0 && t) atomicAdd(a.above, (unsigned long long)t);
+  }
+}
+
+__global__ void __launch_bounds__(64) k_check_counts(CheckArgs a) {
+  if (threadIdx.x == 0 && *a.above) atomicMin(a.err, CHECK_AGAIN);
+}
+
+__global__ void __launch_bounds__(BS) k_offsets_check(const int64_t *off, int64_t n, int64_t *out) {
+  bool bad = false;
+  for (int64_t v = (int64_t)blockIdx.x * BS + threadIdx.x; v < n; v += (int64_t)gridDim.x * BS) bad |= off[v + 1] < off[v];
+  if (bad) out[2] = 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    out[0] = off[n];
+    if (off[0] != 0) out[1] = 1;
+  }
+}
+
+__global__ void __launch_bounds__(BS) k_gather64(const int64_t *off, const int64_t *at, int64_t count, int64_t *out) {
+  for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < count; i += (int64_t)gridDim.x * BS) out[i] = off[at[i]];
+}
+
+static unsigned blocks_for(int64_t n, int64_t most) {
+  const int64_t g = (n + BS - 1) / BS;
+  return (unsigned)(g < 1 ? 1 : g < most ? g : most);
+}
+
+hipError_t launch_offsets_check(const int64_t *off, int64_t n, int64_t *out, hipStream_t s) {
+  const hipError_t e = hipMemsetAsync(out, 0, 3 * sizeof(int64_t), s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_offsets_check, dim3(blocks_for(n, 2048)), dim3(BS), 0, s, off, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather64(const int64_t *off, const int64_t *at, int64_t count, int64_t *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_gather64, dim3(blocks_for(count, 1024)), dim3(BS), 0, s, off, at, count, out);
+  return hipGetLastError();
 }
 
 __global__ void k_gid(const int64_t *vtx_ptr, int32_t num_graphs, int32_t *gid) {
@@ -139,83 +209,20 @@ __global__ void k_gid(const int64_t *vtx_ptr, int32_t num_graphs, int32_t *gid) 
     for (int64_t v = vtx_ptr[g] + threadIdx.x; v < vtx_ptr[g + 1]; v += blockDim.x) gid[v] = g;
 }
 
-hipError_t launch_graph_setup(const int64_t *off, const int32_t *col, int64_t n, const int64_t *vtx_ptr,
-                              int32_t num_graphs, int32_t *gid, int64_t *wall, int64_t *blocksum,
-                              int validate, int *err, hipStream_t s) {
-  hipError_t e = launch_row_weights(off, n, wall, blocksum, s);
+hipError_t launch_graph_check(const CheckArgs &a, hipStream_t s) {
+  if (a.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_check, dim3(4096), dim3(BS), 0, s, a);
+  if (a.validate == 1) hipLaunchKernelGGL(k_check_counts, dim3(1), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_graph_setup(const CheckArgs &a, int32_t num_graphs, int32_t *gid, int64_t *wall, int64_t *blocksum,
+                              hipStream_t s) {
+  const hipError_t e = launch_row_weights(a.off, a.n, wall, blocksum, s);
   if (e != hipSuccess) return e;
-  if (gid) hipLaunchKernelGGL(k_gid, dim3(num_graphs < 4096 ? num_graphs : 4096), dim3(BS), 0, s, vtx_ptr,
+  if (gid) hipLaunchKernelGGL(k_gid, dim3(num_graphs < 4096 ? num_graphs : 4096), dim3(BS), 0, s, a.vtx_ptr,
                               num_graphs, gid);
-  if (n > 0) {
-    CheckArgs a{off, col, wall, n, vtx_ptr, gid, validate, err};
-    hipLaunchKernelGGL(k_check, dim3(4096), dim3(BS), 0, s, a);
-  }
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------ bound buckets ----
-
-__global__ void __launch_bounds__(BS) k_level_count(const int64_t *off, int64_t n, unsigned *count, int *max_deg) {
-  __shared__ unsigned s_cnt[NLVL];
-  __shared__ int s_max;
-  if (threadIdx.x < NLVL) s_cnt[threadIdx.x] = 0;
-  if (threadIdx.x == 0) s_max = 0;
-  __syncthreads();
-  int mx = 0;
-  for (int64_t v = (int64_t)blockIdx.x * BS + threadIdx.x; v < n; v += (int64_t)gridDim.x * BS) {
-    const int64_t d = off[v + 1] - off[v];
-    if (d > mx) mx = (int)d;
-    if (d >= DSW) atomicAdd(&s_cnt[level_of(d)], 1u);
-  }
-  mx = wave_max(mx);
-  if (lane_id() == 0) atomicMax(&s_max, mx);
-  __syncthreads();
-  if (threadIdx.x < NLVL && s_cnt[threadIdx.x]) atomicAdd(&count[threadIdx.x], s_cnt[threadIdx.x]);
-  if (threadIdx.x == 0 && s_max) atomicMax(max_deg, s_max);
-}
-
-// Each workgroup takes a contiguous chunk: counts per level in LDS, reserves
-// its ranges with one atomic per level, then writes.
-__global__ void __launch_bounds__(BS) k_level_fill(const int64_t *off, int64_t n, const int64_t *lvl_off,
-                                                   unsigned *cursor, int32_t *lvl) {
-  __shared__ unsigned s_cnt[NLVL], s_base[NLVL];
-  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t v0 = (int64_t)blockIdx.x * per, v1 = v0 + per < n ? v0 + per : n;
-  if (threadIdx.x < NLVL) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-  for (int64_t v = v0 + threadIdx.x; v < v1; v += BS) {
-    const int64_t d = off[v + 1] - off[v];
-    if (d >= DSW) atomicAdd(&s_cnt[level_of(d)], 1u);
-  }
-  __syncthreads();
-  if (threadIdx.x < NLVL) {
-    s_base[threadIdx.x] = s_cnt[threadIdx.x] ? atomicAdd(&cursor[threadIdx.x], s_cnt[threadIdx.x]) : 0u;
-    s_cnt[threadIdx.x] = 0;
-  }
-  __syncthreads();
-  for (int64_t v = v0 + threadIdx.x; v < v1; v += BS) {
-    const int64_t d = off[v + 1] - off[v];
-    if (d >= DSW) {
-      const int k = level_of(d);
-      const unsigned p = s_base[k] + atomicAdd(&s_cnt[k], 1u);
-      lvl[lvl_off[k] + p] = (int32_t)v;
-    }
-  }
-}
-
-hipError_t launch_level_count(const int64_t *off, int64_t n, unsigned *count, int *max_deg, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  const int64_t g = (n + BS - 1) / BS < 2048 ? (n + BS - 1) / BS : 2048;
-  hipLaunchKernelGGL(k_level_count, dim3((unsigned)g), dim3(BS), 0, s, off, n, count, max_deg);
-  return hipGetLastError();
-}
-
-hipError_t launch_level_fill(const int64_t *off, int64_t n, const int64_t *lvl_off, unsigned *cursor,
-                             int32_t *lvl, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  const int64_t g = (n + BS - 1) / BS < 4096 ? (n + BS - 1) / BS : 4096;
-  hipLaunchKernelGGL(k_level_fill, dim3((unsigned)g), dim3(BS), 0, s, off, n, lvl_off, cursor, lvl);
-  return hipGetLastError();
+  return launch_graph_check(a, s);
 }
 
 // ----------------------------------------------------------- renumbering --
@@ -225,16 +232,26 @@ hipError_t launch_level_fill(const int64_t *off, int64_t n, const int64_t *lvl_o
 // most (that of the hubs) sits in a few contiguous lines that stay cached.
 // Within a level the order is whatever the atomics give: no result depends
 // on internal ids (labels and every record are mapped back or id-free).
-constexpr int RBINS = NLVL + 1;
+constexpr int RBINS = RELABEL_BINS;
 __device__ inline int relabel_bin(int64_t d) { return d > 0 ? NLVL - 1 - level_of(d) : NLVL; }
 
+// count[0, RBINS): vertices per bin; count[2 RBINS]: the largest degree.
 __global__ void __launch_bounds__(BS) k_relabel_count(const int64_t *off, int64_t n, unsigned *count) {
   __shared__ unsigned s_cnt[RBINS];
+  __shared__ int s_max;
   if (threadIdx.x < RBINS) s_cnt[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_max = 0;
   __syncthreads();
-  for (int64_t v = (int64_t)blockIdx.x * BS + threadIdx.x; v < n; v += (int64_t)gridDim.x * BS)
-    atomicAdd(&s_cnt[relabel_bin(off[v + 1] - off[v])], 1u);
+  int mx = 0;
+  for (int64_t v = (int64_t)blockIdx.x * BS + threadIdx.x; v < n; v += (int64_t)gridDim.x * BS) {
+    const int64_t d = off[v + 1] - off[v];
+    mx = (int)d > mx ? (int)d : mx;
+    atomicAdd(&s_cnt[relabel_bin(d)], 1u);
+  }
+  mx = wave_max(mx);
+  if (lane_id() == 0) atomicMax(&s_max, mx);
   __syncthreads();
+  if (threadIdx.x == 0 && s_max) atomicMax(&count[2 * RBINS], (unsigned)s_max);
   if (threadIdx.x < RBINS && s_cnt[threadIdx.x]) atomicAdd(&count[threadIdx.x], s_cnt[threadIdx.x]);
 }
 
@@ -308,26 +325,25 @@ __global__ void __launch_bounds__(BS) k_relabel_cols(const int64_t *off, const i
 
 hipError_t launch_relabel(const int64_t *off, const int32_t *col, const int64_t *wall, int64_t n, unsigned *count,
                           int64_t *bin_off_dev, int32_t *perm, int32_t *iperm, int64_t *rdeg, int64_t *roff,
-                          int64_t *blocksum, int32_t *rcol, int64_t *first_low, int64_t *first_isolated,
-                          hipStream_t s) {
-  *first_low = n;
-  *first_isolated = n;
+                          int64_t *blocksum, int32_t *rcol, unsigned *bins, int64_t *max_deg, hipStream_t s) {
+  for (int b = 0; b < RBINS; b++) bins[b] = 0;
+  *max_deg = 0;
   if (n == 0) return hipMemsetAsync(roff, 0, sizeof(int64_t), s);
-  const unsigned g = (unsigned)((n + BS - 1) / BS < 4096 ? (n + BS - 1) / BS : 4096);
-  hipError_t e = hipMemsetAsync(count, 0, sizeof(unsigned) * 2 * RBINS, s);
+  const unsigned g = blocks_for(n, 4096);
+  hipError_t e = hipMemsetAsync(count, 0, sizeof(unsigned) * (2 * RBINS + 1), s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_relabel_count, dim3(g), dim3(BS), 0, s, off, n, count);
-  unsigned hc[RBINS];
+  unsigned hc[2 * RBINS + 1];
   e = hipMemcpyAsync(hc, count, sizeof(hc), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
+  *max_deg = hc[2 * RBINS];
   int64_t hb[RBINS], acc = 0;
   for (int b = 0; b < RBINS; b++) {
+    bins[b] = hc[b];
     hb[b] = acc;
     acc += hc[b];
   }
-  *first_isolated = hb[RBINS - 1];
-  *first_low = hb[NLVL - 1 - level_of(DSW - 1)];  // the bin of degree DSW - 1
   e = hipMemcpyAsync(bin_off_dev, hb, sizeof(hb), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_relabel_assign, dim3(g), dim3(BS), 0, s, off, n, bin_off_dev, count + RBINS, perm, iperm);

@@ -14,7 +14,7 @@ struct LaunchShape {
   int exact_seen;        // the host saw the run switch to exact degrees
 };
 
-hipError_t launch_init(const Ws &w, const unsigned *lvl_init_cnt, hipStream_t s);
+hipError_t launch_init(const Ws &w, hipStream_t s);
 // The kernels of one round, in order; each takes the run's Ws.
 struct RoundStep {
   void (*kernel)(Ws);
@@ -29,20 +29,33 @@ hipError_t launch_finalize(const Ws &w, int32_t *labels, hipStream_t s);
 // Copies n labels (device memory, any alignment) unless *error is set.
 hipError_t launch_deliver(const int32_t *from, int32_t *to, int64_t n, const int *error, hipStream_t s);
 
+// Offsets of a graph on the device: out[0] = offsets[n], out[1] != 0 if they
+// do not start at 0, out[2] != 0 if they decrease somewhere.
+hipError_t launch_offsets_check(const int64_t *off, int64_t n, int64_t *out, hipStream_t s);
+// out[i] = off[at[i]], i < count.
+hipError_t launch_gather64(const int64_t *off, const int64_t *at, int64_t count, int64_t *out, hipStream_t s);
+
 // Graph set-up: row-weight prefix wall[n+1] (the "all rows" list of the
 // edge-balanced walk), per-row graph ids (batches), column-range check and,
 // with validate, the symmetry / self-loop / duplicate checks.  *err receives
-// the smallest failing cc_status code (it must hold 0x7fffffff beforehand).
-hipError_t launch_graph_setup(const int64_t *off, const int32_t *col, int64_t n, const int64_t *vtx_ptr,
-                              int32_t num_graphs, int32_t *gid, int64_t *wall, int64_t *blocksum,
-                              int validate, int *err, hipStream_t s);
-
-// Bucket levels of the degree bounds: count[k] = vertices with
-// floor(log2(deg)) == k (k >= LVL_MIN), and the maximum degree.
-hipError_t launch_level_count(const int64_t *off, int64_t n, unsigned *count, int *max_deg, hipStream_t s);
-// Places every vertex with deg >= DSW at lvl[lvl_off[k] + i], k = its level.
-hipError_t launch_level_fill(const int64_t *off, int64_t n, const int64_t *lvl_off, unsigned *cursor,
-                             int32_t *lvl, hipStream_t s);
+// the smallest failing cc_status code (it must hold 0x7fffffff beforehand),
+// or CHECK_AGAIN when the checks of `validate` == 1 cannot tell which: then
+// launch_graph_check with 2 finds it.  above: zeroed scratch word.
+constexpr int CHECK_AGAIN = (1 << 8) | 0xFF;
+struct CheckArgs {
+  const int64_t *off;
+  const int32_t *col;
+  const int64_t *wall;
+  int64_t n;
+  const int64_t *vtx_ptr;  // device, or null
+  const int32_t *gid;      // device per-row graph id, or null
+  int validate;
+  int *err;                // (priority << 8 | cc_status code) of the worst failure, 0x7fffffff = none
+  unsigned long long *above;
+};
+hipError_t launch_graph_setup(const CheckArgs &a, int32_t num_graphs, int32_t *gid, int64_t *wall, int64_t *blocksum,
+                              hipStream_t s);
+hipError_t launch_graph_check(const CheckArgs &a, hipStream_t s);
 
 // Batched C4 / ClusterWild!: one persistent launch over many small graphs.
 struct BatchLaunch {
@@ -67,14 +80,14 @@ hipError_t batched_max_grid(int block, size_t lds, int *grid);
 
 // Internal renumbering of a single graph (hubs first): perm (input id ->
 // internal id), iperm, and the renumbered CSR roff / rcol.  count: 2 x
-// (NLVL + 1) unsigned scratch, bin_off: NLVL + 1 int64, rdeg: n int64,
-// blocksum: n / (4 BS) + 2 int64.  On the host: *first_low = the first
-// internal id of degree below DSW, *first_isolated = the first of degree 0
-// (degrees fall with the id level by level, so each is the start of a range).
+// RELABEL_BINS + 1 unsigned scratch, bin_off: RELABEL_BINS int64, rdeg: n
+// int64, blocksum: n / (4 BS) + 2 int64.  On the host: vertices per bin (bin
+// b < NLVL: degree level NLVL - 1 - b; the last: degree 0) and the largest
+// degree; the ids of a bin follow those of the bins before it.
+constexpr int RELABEL_BINS = NLVL + 1;
 hipError_t launch_relabel(const int64_t *off, const int32_t *col, const int64_t *wall, int64_t n, unsigned *count,
                           int64_t *bin_off_dev, int32_t *perm, int32_t *iperm, int64_t *rdeg, int64_t *roff,
-                          int64_t *blocksum, int32_t *rcol, int64_t *first_low, int64_t *first_isolated,
-                          hipStream_t s);
+                          int64_t *blocksum, int32_t *rcol, unsigned *bins, int64_t *max_deg, hipStream_t s);
 
 // pi mapped into internal ids and checked as a permutation, in bucketed
 // passes (cc_order.hip) for OM_MIN_N < n <= OM_MAX_BUCKETS * OM_SIZE; other

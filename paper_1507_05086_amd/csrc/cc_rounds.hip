@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(BS) k_check_order(Ws w) {
 // flag or bound, and k_select settles it by its id alone, so only a partial
 // run (whose k_finalize reads its label) and the direct check of pi (which
 // reads its mark) visit those ids.
-__global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt) {
+__global__ void __launch_bounds__(BS) k_init(Ws w) {
   const int64_t n = w.n;
   const int64_t end = (w.order_mapped && w.max_rounds == 0) ? w.iso_start : n;
   __shared__ int s_hist[HLDS];
@@ -74,6 +74,10 @@ __global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt)
     w.flag[v] = 0;
     w.ub[v] = (int32_t)(w.off[v + 1] - w.off[v]);
     if (w.start_exact) hist_add(s_hist, w.hist, w.ub[v], 1);
+    if (v < w.low_start) {  // degree >= DSW: a bound bucket entry
+      const int k = level_of(w.ub[v]);
+      w.lvl[w.lvl_off[k] + (v - w.lvl_first[k])] = (int32_t)v;
+    }
   }
   __syncthreads();
   if (w.start_exact)
@@ -86,7 +90,7 @@ __global__ void __launch_bounds__(BS) k_init(Ws w, const unsigned *lvl_init_cnt)
   }
   Ctrl *c = w.ctrl;
   if (blockIdx.x == 0) {
-    if (threadIdx.x < NLVL) c->lvl_cnt[threadIdx.x] = lvl_init_cnt[threadIdx.x];
+    if (threadIdx.x < NLVL) c->lvl_cnt[threadIdx.x] = w.lvl_cnt0[threadIdx.x];
     if (threadIdx.x == 0) {
       c->n_rem = n;
       c->n_start = n;
@@ -1190,9 +1194,9 @@ static inline unsigned grid_for(int64_t items, unsigned cap) {
   return (unsigned)g;
 }
 
-hipError_t launch_init(const Ws &w, const unsigned *lvl_init_cnt, hipStream_t s) {
+hipError_t launch_init(const Ws &w, hipStream_t s) {
   if (!w.order_mapped) hipLaunchKernelGGL(k_check_order, dim3(grid_for(w.n, 4096)), dim3(BS), 0, s, w);
-  hipLaunchKernelGGL(k_init, dim3(grid_for(w.n, 4096)), dim3(BS), 0, s, w, lvl_init_cnt);
+  hipLaunchKernelGGL(k_init, dim3(grid_for(w.n, 4096)), dim3(BS), 0, s, w);
   hipLaunchKernelGGL(k_close, dim3(1), dim3(64), 0, s, w);
   return hipGetLastError();
 }
