@@ -605,7 +605,8 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
       launched += per;
     } while (launched - finished < depth * per);
     if (int32_t rc = wait_slots(launched - (depth - 1) * per)) return rc;
-    if (!done && launched > round_limit + 4 * kRoundGroup) {  // a backstop: the device stops a runaway loop itself
+    // a backstop (the device stops a runaway loop itself): a round takes a slot, or one per Delta pass and the switch's
+    if (!done && launched > (DITER + 1) * round_limit + 4 * kRoundGroup) {
       (void)hipStreamSynchronize(s);
       return fail(CC_ERR_NO_PROGRESS, "round loop exceeded its round limit");
     }

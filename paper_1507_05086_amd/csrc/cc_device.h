@@ -69,7 +69,8 @@ struct RoundRec {  // mirrors cc_round_record
 struct CtrlHead {
   int done;                  // the run is finished (or failed)
   int16_t phase;             // PHASE_LAZY (upper bounds) or PHASE_EXACT (exact degrees)
-  int16_t stage;             // ST_*: where the round kernels take up the round
+  int8_t stage;              // ST_*: where the round kernels take up the round
+  int8_t pass;               // lazy Delta search: passes that are behind
   unsigned int n_blocked;    // C4: blocked active vertices of this round
   unsigned int n_cedges;     // C4: conflict edges listed this round
   long long delta;           // Delta_i of the current round
@@ -86,7 +87,8 @@ struct CtrlHead {
 struct Ctrl {
   // ---- the head (same layout as CtrlHead) ----
   int done;
-  int16_t phase, stage;
+  int16_t phase;
+  int8_t stage, pass;
   unsigned int n_blocked, n_cedges;
   long long delta;
   long long b;
@@ -125,7 +127,7 @@ struct Ctrl {
 };
 static_assert(sizeof(CtrlHead) == 128, "the head is one 128-byte line");
 static_assert(offsetof(Ctrl, done) == offsetof(CtrlHead, done) && offsetof(Ctrl, phase) == offsetof(CtrlHead, phase) &&
-                  offsetof(Ctrl, stage) == offsetof(CtrlHead, stage) &&
+                  offsetof(Ctrl, stage) == offsetof(CtrlHead, stage) && offsetof(Ctrl, pass) == offsetof(CtrlHead, pass) &&
                   offsetof(Ctrl, n_blocked) == offsetof(CtrlHead, n_blocked) &&
                   offsetof(Ctrl, n_cedges) == offsetof(CtrlHead, n_cedges) &&
                   offsetof(Ctrl, delta) == offsetof(CtrlHead, delta) && offsetof(Ctrl, b) == offsetof(CtrlHead, b) &&

@@ -20,7 +20,7 @@ struct RoundStep {
   void (*kernel)(Ws);
   unsigned grid, block;
 };
-constexpr int ROUND_STEPS = 20;  // at most
+constexpr int ROUND_STEPS = 12;  // at most
 int round_steps(const Ws &w, const LaunchShape &ls, RoundStep *out);
 RoundStep team_step(const Ws &w);
 // Rounds on one XCD (cc_team.hip) until one is for the whole device; w.team set.

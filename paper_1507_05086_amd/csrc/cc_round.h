@@ -146,7 +146,9 @@ __device__ inline DSearch dsearch(const C *c, int done) {
   DSearch s{0, 0, -1, 0, 0};
   if (c->phase != PHASE_LAZY) return s;
   long long T = c->delta;
-  for (int j = 0; j < done; j++) {
+#pragma unroll
+  for (int j = 0; j < DITER; j++) {  // (a fixed count, so that no index of d_max is one of a register array)
+    if (j >= done) break;
     const long long L = band_floor(j, T);
     if (L < SWL) {  // pass j never ran: the search switched before it
       s.switching = 1;

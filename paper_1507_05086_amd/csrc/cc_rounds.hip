@@ -104,174 +104,197 @@ __global__ void __launch_bounds__(BS) k_init(Ws w) {
   }
 }
 
-// Candidates of pass IT: live entries with bound >= L, found in the levels
-// level(L) .. top (a bound can be stale above the current Delta).
-template <int IT>
-__global__ void __launch_bounds__(BS) k_dscan(Ws w) {
+// ------------------------------------------------------- remaining degrees --
+// After the claims a round is in one of three states, and the same two kernels
+// serve them: the lazy Delta search has a pass to run (dsearch), the run
+// switches to exact degrees, or it keeps exact degrees and peels.  A slot
+// runs one pass; where the search needs another, k_close leaves the round
+// open and the next slot's earlier kernels return at once.  R-MAT 26 needs a
+// second pass in 6 of 96 lazy rounds, a third in none, and switches once: as
+// kernels of their own these returned idle in nearly every round, at 5 us
+// each, and peeling too until the switch: 7 of a round's 13 launches and 36
+// of its 95 us.
+
+// Pass h.pass: the live entries with bound >= L, found in the levels level(L)
+// .. top (a bound can be stale above the current Delta).  At the switch: the
+// unclustered rows of degree >= DSW (their accumulators live in the
+// active-list weights, free at this point of the round).
+__global__ void __launch_bounds__(BS) k_candidates(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
-  if (idle(h, ST_DELTA)) return;
-  const DSearch s = dsearch(&h, IT);
-  if (!s.pending) return;
-  const int kL = level_of(s.L < DSW ? DSW : s.L), kT = NLVL - 1;
-  int64_t base[NLVL + 1];
-  int64_t tot = 0;
-  for (int k = kL; k <= kT; k++) {
-    base[k] = tot;
-    const int64_t cap = w.lvl_off[k + 1] - w.lvl_off[k];
-    const int64_t cnt = c->lvl_cnt[k];
-    tot += cnt < cap ? cnt : cap;
+  if (idle(h, ST_DELTA) || h.phase != PHASE_LAZY) return;
+  const int pass = h.pass;
+  const DSearch s = dsearch(&h, pass);
+  constexpr int PER = 4;  // entries of a thread in flight: each is a chain of three dependent reads
+  __shared__ StageBuf<(PER + 1) * BS> sb;
+  __shared__ int64_t s_base[NLVL + 1];
+  if (s.switching) {
+    unsigned long long *xacc = (unsigned long long *)w.awork;
+    stage_init(sb);
+    const int64_t n = w.low_start;  // lower-degree rows are counted by id in count_exact
+    const int64_t per = ((n + gridDim.x - 1) / gridDim.x + BS - 1) / BS * BS;
+    const int64_t v0 = (int64_t)blockIdx.x * per, v1 = v0 + per < n ? v0 + per : n;
+    for (int64_t vb = v0; vb < v1; vb += BS) {
+      const int64_t v = vb + threadIdx.x;
+      if (v < v1 && unc_bit(w.unc, (int32_t)v)) {
+        const int64_t d = w.off[v + 1] - w.off[v];
+        w.xend[v] = w.off[v];  // count_exact appends the row's unclustered neighbours
+        if (d > 0) stage_push(sb, (int32_t)v, (int32_t)d);
+      }
+      __syncthreads();
+      if (sb.cnt > BS) stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
+    }
+    stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
+    return;
   }
-  base[kT + 1] = tot;
-  __shared__ StageBuf<2 * BS> sb;
+  if (!s.pending) return;
+  const int kL = level_of(s.L < DSW ? DSW : s.L);
+  if (threadIdx.x < 64) {  // where each level's entries start among those of kL and above
+    const int k = threadIdx.x;
+    int64_t cnt = 0;
+    if (k >= kL && k < NLVL) {
+      const int64_t cap = w.lvl_off[k + 1] - w.lvl_off[k], have = c->lvl_cnt[k];
+      cnt = have < cap ? have : cap;
+    }
+    const int64_t inc = wave_incl_scan(cnt);
+    if (k < NLVL) s_base[k] = inc - cnt;
+    if (k == NLVL) s_base[k] = inc;
+  }
   stage_init(sb);
+  const int64_t tot = s_base[NLVL];
+  int32_t *list = w.rlist + pass * w.rcap;
+  int64_t *work = w.rwork + pass * w.rcap;
+  unsigned long long *acc = w.racc + pass * w.rcap;
   // a contiguous share of the entries per workgroup
   const int64_t per = ((tot + gridDim.x - 1) / gridDim.x + BS - 1) / BS * BS;
   const int64_t e0 = (int64_t)blockIdx.x * per, e1 = e0 + per < tot ? e0 + per : tot;
-  for (int64_t i0 = e0; i0 < e1; i0 += BS) {
-    const int64_t i = i0 + threadIdx.x;
-    if (i < e1) {
-      int k = kL;
-      while (k < kT && i >= base[k + 1]) k++;
-      const int32_t v = w.lvl[w.lvl_off[k] + (i - base[k])];
-      const int32_t x = w.ub[v];
-      if (x >= s.L && level_of(x) == k && unc_bit(w.unc, v))  // live entry, inside the band
-        stage_push(sb, v, (int32_t)(w.rend[v] - w.off[v]));
+  for (int64_t i0 = e0; i0 < e1; i0 += PER * BS) {
+    int32_t v[PER], x[PER];
+    int lv[PER];
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+      const int64_t i = i0 + q * BS + threadIdx.x;
+      v[q] = -1;
+      lv[q] = kL;
+      if (i < e1) {
+        while (lv[q] < NLVL - 1 && i >= s_base[lv[q] + 1]) lv[q]++;
+        v[q] = w.lvl[w.lvl_off[lv[q]] + (i - s_base[lv[q]])];
+      }
     }
+#pragma unroll
+    for (int q = 0; q < PER; q++) x[q] = v[q] >= 0 ? w.ub[v[q]] : 0;
+#pragma unroll
+    for (int q = 0; q < PER; q++)
+      if (v[q] >= 0 && x[q] >= s.L && level_of(x[q]) == lv[q] && unc_bit(w.unc, v[q]))  // live entry, inside the band
+        stage_push(sb, v[q], (int32_t)(w.rend[v[q]] - w.off[v[q]]));
     __syncthreads();
-    if (sb.cnt > BS) stage_flush(sb, &c->r_pack[IT], w.rlist + IT * w.rcap, w.rwork + IT * w.rcap, w.racc + IT * w.rcap);
+    if (sb.cnt > BS) stage_flush(sb, &c->r_pack[pass], list, work, acc);
   }
-  stage_flush(sb, &c->r_pack[IT], w.rlist + IT * w.rcap, w.rwork + IT * w.rcap, w.racc + IT * w.rcap);
+  stage_flush(sb, &c->r_pack[pass], list, work, acc);
 }
+
+struct RescanLds {
+  int cnt[TW];
+  int32_t mv[TW];
+  int8_t mvk[TW];
+  int mvn[NLVL], mvbase[NLVL];
+  int mx, nmv;
+};
+struct ExactLds {
+  int cnt[TW];
+  int64_t base[TW];  // where this tile's share of its row j goes in xcol
+  int hist[HLDS];
+};
+struct PeelLds {
+  int hist[HLDS];
+  unsigned atom;
+};
 
 // Exact remaining degrees of the pass's candidates; the new bounds move
 // entries down the levels; the pass maximum goes to d_max.
-template <int IT>
-__global__ void __launch_bounds__(BS) k_rescan(Ws w) {
-  Ctrl *c = w.ctrl;
-  const CtrlHead h = ctrl_head(c);
-  if (idle(h, ST_DELTA)) return;
-  const DSearch s = dsearch(&h, IT);
-  if (!s.pending) return;
-  __shared__ int lcnt[TW];
-  __shared__ int s_max, s_nmv;
-  __shared__ int s_mvn[NLVL], s_mvbase[NLVL];
-  __shared__ int32_t s_mv[TW];
-  __shared__ int8_t s_mvk[TW];
-  for (int i = threadIdx.x; i < TW; i += BS) lcnt[i] = 0;
-  if (threadIdx.x < NLVL) s_mvn[threadIdx.x] = 0;
+__device__ __forceinline__ void rescan(const Ws &w, Ctrl *c, const CtrlHead &h, WalkLds &wl, RescanLds &L) {
+  for (int i = threadIdx.x; i < TW; i += BS) L.cnt[i] = 0;
+  if (threadIdx.x < NLVL) L.mvn[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
-    s_max = 0;
-    s_nmv = 0;
+    L.mx = 0;
+    L.nmv = 0;
   }
   __syncthreads();
-  const unsigned long long rp = h.r_pack[IT];
+  const int pass = h.pass;
+  unsigned long long rp = 0;
+#pragma unroll
+  for (int j = 0; j < DITER; j++) rp |= j == pass ? h.r_pack[j] : 0;  // (no index of a register array)
   const int64_t cnt = pk_cnt(rp) < w.rcap ? pk_cnt(rp) : w.rcap;
-  unsigned long long *ra = w.racc + IT * w.rcap;
+  unsigned long long *ra = w.racc + pass * w.rcap;
   auto finalize = [&](int32_t v, int r) {
     const int32_t old = w.ub[v];
     w.ub[v] = r;
-    atomicMax(&s_max, r);
+    atomicMax(&L.mx, r);
     const int kn = r >= DSW ? level_of(r) : -1;
     if (kn >= 0 && kn != level_of(old)) {
-      const int p = atomicAdd(&s_nmv, 1);
-      s_mv[p] = v;
-      s_mvk[p] = (int8_t)kn;
-      atomicAdd(&s_mvn[kn], 1);
+      const int p = atomicAdd(&L.nmv, 1);
+      L.mv[p] = v;
+      L.mvk[p] = (int8_t)kn;
+      atomicAdd(&L.mvn[kn], 1);
     }
   };
-  lb_walk(
-      w.rlist + IT * w.rcap, w.rwork + IT * w.rcap, cnt, pk_work(rp), w.off, w.rend, w.col, nullptr, nullptr,
+  lb_walk_in(
+      wl, w.rlist + pass * w.rcap, w.rwork + pass * w.rcap, cnt, pk_work(rp), w.off, w.rend, w.col, nullptr, nullptr,
       [&](Items &it) {
 #pragma unroll
         for (int k = 0; k < IPT; k++)
-          if ((it.edge >> k & 1) && unc_bit(w.unc, it.u[k])) atomicAdd(&lcnt[it.ent[k]], 1);
+          if ((it.edge >> k & 1) && unc_bit(w.unc, it.u[k])) atomicAdd(&L.cnt[it.ent[k]], 1);
       },
       [&](int j, int64_t slot, int32_t v, int32_t deg, int64_t covered) {
-        const int cj = lcnt[j];
-        lcnt[j] = 0;
+        const int cj = L.cnt[j];
+        L.cnt[j] = 0;
         int total = cj;
         if (covered == deg || row_combine(ra, slot, cj, covered, deg, &total)) finalize(v, total);
       },
       [&]() {
         // this tile's level moves: one reservation per level, then the writes
         __syncthreads();
-        if (threadIdx.x < NLVL && s_mvn[threadIdx.x]) {
+        if (threadIdx.x < NLVL && L.mvn[threadIdx.x]) {
           const int k = threadIdx.x;
-          s_mvbase[k] = (int)atomicAdd(&c->lvl_cnt[k], (unsigned)s_mvn[k]);
+          L.mvbase[k] = (int)atomicAdd(&c->lvl_cnt[k], (unsigned)L.mvn[k]);
         }
         __syncthreads();
-        const int nmv = s_nmv;
+        const int nmv = L.nmv;
         for (int p = threadIdx.x; p < nmv; p += BS) {
-          const int k = s_mvk[p];
+          const int k = L.mvk[p];
           int q = 0;  // rank among this tile's earlier moves to the same level
-          for (int x = 0; x < p; x++) q += (s_mvk[x] == k);
-          const int64_t pos = (int64_t)s_mvbase[k] + q;
-          if (pos < w.lvl_off[k + 1] - w.lvl_off[k]) w.lvl[w.lvl_off[k] + pos] = s_mv[p];
+          for (int x = 0; x < p; x++) q += (L.mvk[x] == k);
+          const int64_t pos = (int64_t)L.mvbase[k] + q;
+          if (pos < w.lvl_off[k + 1] - w.lvl_off[k]) w.lvl[w.lvl_off[k] + pos] = L.mv[p];
           else set_error(c, ERR_OVERFLOW);
         }
         __syncthreads();
-        if (threadIdx.x < NLVL) s_mvn[threadIdx.x] = 0;
-        if (threadIdx.x == 0) s_nmv = 0;
+        if (threadIdx.x < NLVL) L.mvn[threadIdx.x] = 0;
+        if (threadIdx.x == 0) L.nmv = 0;
       });
   __syncthreads();
-  if (threadIdx.x == 0 && s_max > 0) atomicMax(&c->d_max[IT], s_max);
+  if (threadIdx.x == 0 && L.mx > 0) atomicMax(&c->d_max[pass], L.mx);
 }
 
-// Switch to exact degrees: list the unclustered rows of degree >= DSW (their
-// accumulators live in the active-list weights, free at this point of the
-// round) ...
-__global__ void __launch_bounds__(BS) k_xlist(Ws w) {
-  Ctrl *c = w.ctrl;
-  const CtrlHead h = ctrl_head(c);
-  if (idle(h, ST_DELTA)) return;
-  const DSearch s = dsearch(&h, DITER);
-  if (!s.switching) return;
-  unsigned long long *xacc = (unsigned long long *)w.awork;
-  __shared__ StageBuf<2 * BS> sb;
-  stage_init(sb);
-  const int64_t n = w.low_start;  // lower-degree rows are counted by id in k_xcount
-  const int64_t per = ((n + gridDim.x - 1) / gridDim.x + BS - 1) / BS * BS;
-  const int64_t v0 = (int64_t)blockIdx.x * per, v1 = v0 + per < n ? v0 + per : n;
-  for (int64_t vb = v0; vb < v1; vb += BS) {
-    const int64_t v = vb + threadIdx.x;
-    if (v < v1 && unc_bit(w.unc, (int32_t)v)) {
-      const int64_t d = w.off[v + 1] - w.off[v];
-      w.xend[v] = w.off[v];  // k_xcount appends the row's unclustered neighbours
-      if (d > 0) stage_push(sb, (int32_t)v, (int32_t)d);
-    }
-    __syncthreads();
-    if (sb.cnt > BS) stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
-  }
-  stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
-}
-
-// ... and count their unclustered neighbours into ub and the histogram: the
-// listed rows edge-balanced, the rows of degree below DSW (ids low_start ..
-// iso_start, by falling level) one lane per row, so a wave's rows are of
-// about one length and no search or barrier is needed.  The unclustered
-// neighbours found are also written to the compacted rows (xcol, from the
-// start of each row's slot; xend = where the row ends): every vertex the
-// exact rounds walk is unclustered now, and its neighbours clustered before
-// now can never count again.  A listed row's tiles reserve their shares of
-// the slot with one atomic each, so its entries are in no particular order.
-__global__ void __launch_bounds__(BS) k_xcount(Ws w) {
-  Ctrl *c = w.ctrl;
-  const CtrlHead h = ctrl_head(c);
-  if (idle(h, ST_DELTA)) return;
-  const DSearch s = dsearch(&h, DITER);
-  if (!s.switching) return;
-  __shared__ int lcnt[TW];
-  __shared__ int64_t lbase[TW];  // where this tile's share of its row j goes in xcol
-  __shared__ int s_hist[HLDS];
-  for (int i = threadIdx.x; i < TW; i += BS) lcnt[i] = 0;
-  for (int i = threadIdx.x; i < HLDS; i += BS) s_hist[i] = 0;
+// The switch: every unclustered vertex's unclustered neighbours are counted
+// into ub and the histogram: the listed rows edge-balanced, the rows of
+// degree below DSW (ids low_start .. iso_start, by falling level) one lane per
+// row, so a wave's rows are of about one length and no search or barrier is
+// needed.  The unclustered neighbours found are also written to the compacted
+// rows (xcol, from the start of each row's slot; xend = where the row ends):
+// every vertex the exact rounds walk is unclustered now, and its neighbours
+// clustered before now can never count again.  A listed row's tiles reserve
+// their shares of the slot with one atomic each, so its entries are in no
+// particular order.
+__device__ __forceinline__ void count_exact(const Ws &w, Ctrl *c, const CtrlHead &h, WalkLds &wl, ExactLds &L) {
+  for (int i = threadIdx.x; i < TW; i += BS) L.cnt[i] = 0;
+  for (int i = threadIdx.x; i < HLDS; i += BS) L.hist[i] = 0;
   __syncthreads();
   unsigned long long *xacc = (unsigned long long *)w.awork;
   const unsigned long long xp = h.x_pack;
   auto finalize = [&](int32_t v, int r) {
     w.ub[v] = r;
-    if (r > 0 && r < HLDS) atomicAdd(&s_hist[r], 1);
+    if (r > 0 && r < HLDS) atomicAdd(&L.hist[r], 1);
     else if (r >= HLDS) atomicAdd(&w.hist[r], 1);
   };
   // this thread's unclustered neighbours in the current tile: the neighbour,
@@ -279,8 +302,8 @@ __global__ void __launch_bounds__(BS) k_xcount(Ws w) {
   int32_t pu[IPT];
   int pj[IPT], pl[IPT];
   unsigned pending = 0;
-  lb_walk(
-      w.xlist, w.xwork, pk_cnt(xp), pk_work(xp), w.off, w.off + 1, w.col, nullptr, nullptr,
+  lb_walk_in(
+      wl, w.xlist, w.xwork, pk_cnt(xp), pk_work(xp), w.off, w.off + 1, w.col, nullptr, nullptr,
       [&](Items &it) {
         pending = 0;
 #pragma unroll
@@ -288,14 +311,14 @@ __global__ void __launch_bounds__(BS) k_xcount(Ws w) {
           if ((it.edge >> k & 1) && unc_bit(w.unc, it.u[k])) {
             pu[k] = it.u[k];
             pj[k] = it.ent[k];
-            pl[k] = atomicAdd(&lcnt[it.ent[k]], 1);
+            pl[k] = atomicAdd(&L.cnt[it.ent[k]], 1);
             pending |= 1u << k;
           }
       },
       [&](int j, int64_t slot, int32_t v, int32_t deg, int64_t covered) {
-        const int cj = lcnt[j];
-        lcnt[j] = 0;
-        lbase[j] = cj > 0 ? (int64_t)atomicAdd((unsigned long long *)&w.xend[v], (unsigned long long)cj) : 0;
+        const int cj = L.cnt[j];
+        L.cnt[j] = 0;
+        L.base[j] = cj > 0 ? (int64_t)atomicAdd((unsigned long long *)&w.xend[v], (unsigned long long)cj) : 0;
         int total = cj;
         if (covered == deg || row_combine(xacc, slot, cj, covered, deg, &total)) finalize(v, total);
       },
@@ -303,7 +326,7 @@ __global__ void __launch_bounds__(BS) k_xcount(Ws w) {
         __syncthreads();  // every row of the tile has its share reserved
 #pragma unroll
         for (int k = 0; k < IPT; k++)
-          if (pending >> k & 1) w.xcol[lbase[pj[k]] + pl[k]] = pu[k];
+          if (pending >> k & 1) w.xcol[L.base[pj[k]] + pl[k]] = pu[k];
       });
   static_assert(DSW <= HLDS, "a lower-degree row's count fits the LDS histogram");
   int64_t scanned = 0;
@@ -324,13 +347,64 @@ __global__ void __launch_bounds__(BS) k_xcount(Ws w) {
     scanned += d;
     w.ub[v] = r;
     w.xend[v] = s0 + r;
-    if (r > 0) atomicAdd(&s_hist[r], 1);
+    if (r > 0) atomicAdd(&L.hist[r], 1);
   }
   const int64_t wsc = wave_sum(scanned);
   if (lane_id() == 0 && wsc) atomicAdd(&c->x_low[(blockIdx.x * (BS / 64) + wave_id()) & 63], (unsigned long long)wsc);
   __syncthreads();
   for (int i = threadIdx.x; i < HLDS; i += BS)
-    if (s_hist[i]) atomicAdd(&w.hist[i], s_hist[i]);
+    if (L.hist[i]) atomicAdd(&w.hist[i], L.hist[i]);
+}
+
+// Exact phase: every unclustered neighbour of a newly clustered vertex loses
+// one remaining degree; the degree histogram follows (low bins per workgroup).
+__device__ __forceinline__ void peel(const Ws &w, Ctrl *c, const CtrlHead &h, WalkLds &wl, PeelLds &L) {
+  for (int i = threadIdx.x; i < HLDS; i += BS) L.hist[i] = 0;
+  if (threadIdx.x == 0) L.atom = 0;
+  __syncthreads();
+  const unsigned long long pp = h.p_pack;
+  lb_walk_in(wl, w.plist, w.pwork, pk_cnt(pp), pk_work(pp), w.off, round_end(w, h.phase), round_col(w, h.phase),
+             nullptr, nullptr, [&](Items &it) {
+#pragma unroll
+    for (int k = 0; k < IPT; k++)
+      if (it.vert >> k & 1) hist_add(L.hist, w.hist, w.ub[it.v[k]], -1);  // the vertex leaves
+    bool un[IPT];
+#pragma unroll
+    for (int k = 0; k < IPT; k++) un[k] = (it.edge >> k & 1) && unc_bit(w.unc, it.u[k]);
+    unsigned dec = 0;
+#pragma unroll
+    for (int k = 0; k < IPT; k++)
+      if (un[k]) {
+        const int32_t old = atomicSub(&w.ub[it.u[k]], 1);
+        hist_add(L.hist, w.hist, old, -1);
+        hist_add(L.hist, w.hist, old - 1, 1);
+        dec++;
+      }
+    if (dec) atomicAdd(&L.atom, dec);
+  });
+  __syncthreads();
+  for (int i = threadIdx.x; i < HLDS; i += BS)
+    if (L.hist[i]) atomicAdd(&w.hist[i], L.hist[i]);
+  if (threadIdx.x == 0 && L.atom) atomicAdd(&c->spread_atom[blockIdx.x & 63], (unsigned long long)L.atom);
+}
+
+__global__ void __launch_bounds__(BS) k_degrees(Ws w) {
+  Ctrl *c = w.ctrl;
+  const CtrlHead h = ctrl_head(c);
+  __shared__ WalkLds wl;
+  __shared__ union {
+    RescanLds rescan;
+    ExactLds exact;
+    PeelLds peel;
+  } L;
+  if (h.phase == PHASE_EXACT) {
+    if (!idle(h, ST_CLASSIFY)) peel(w, c, h, wl, L.peel);
+    return;
+  }
+  if (idle(h, ST_DELTA)) return;
+  const DSearch s = dsearch(&h, h.pass);
+  if (s.pending) rescan(w, c, h, wl, L.rescan);
+  else if (s.switching) count_exact(w, c, h, wl, L.exact);
 }
 
 // ------------------------------------------------------------- select -----
@@ -926,43 +1000,14 @@ __global__ void __launch_bounds__(BS) k_clear(Ws w) {
   }
 }
 
-// --------------------------------------------------------------- peel -----
-// Exact phase: every unclustered neighbour of a newly clustered vertex loses
-// one remaining degree; the degree histogram follows (low bins per workgroup).
-
+// Peeling alone, once the run keeps exact degrees for good.
 __global__ void __launch_bounds__(BS) k_peel(Ws w) {
   Ctrl *c = w.ctrl;
   const CtrlHead h = ctrl_head(c);
   if (idle(h, ST_CLASSIFY) || h.phase != PHASE_EXACT) return;
-  __shared__ int s_hist[HLDS];
-  __shared__ unsigned s_atom;
-  for (int i = threadIdx.x; i < HLDS; i += BS) s_hist[i] = 0;
-  if (threadIdx.x == 0) s_atom = 0;
-  __syncthreads();
-  const unsigned long long pp = h.p_pack;
-  lb_walk(w.plist, w.pwork, pk_cnt(pp), pk_work(pp), w.off, round_end(w, h.phase), round_col(w, h.phase), nullptr,
-          nullptr, [&](Items &it) {
-#pragma unroll
-    for (int k = 0; k < IPT; k++)
-      if (it.vert >> k & 1) hist_add(s_hist, w.hist, w.ub[it.v[k]], -1);  // the vertex leaves
-    bool un[IPT];
-#pragma unroll
-    for (int k = 0; k < IPT; k++) un[k] = (it.edge >> k & 1) && unc_bit(w.unc, it.u[k]);
-    unsigned dec = 0;
-#pragma unroll
-    for (int k = 0; k < IPT; k++)
-      if (un[k]) {
-        const int32_t old = atomicSub(&w.ub[it.u[k]], 1);
-        hist_add(s_hist, w.hist, old, -1);
-        hist_add(s_hist, w.hist, old - 1, 1);
-        dec++;
-      }
-    if (dec) atomicAdd(&s_atom, dec);
-  });
-  __syncthreads();
-  for (int i = threadIdx.x; i < HLDS; i += BS)
-    if (s_hist[i]) atomicAdd(&w.hist[i], s_hist[i]);
-  if (threadIdx.x == 0 && s_atom) atomicAdd(&c->spread_atom[blockIdx.x & 63], (unsigned long long)s_atom);
+  __shared__ WalkLds wl;
+  __shared__ PeelLds L;
+  peel(w, c, h, wl, L);
 }
 
 // -------------------------------------------------------------- close -----
@@ -971,6 +1016,26 @@ __global__ void __launch_bounds__(BS) k_peel(Ws w) {
 __global__ void __launch_bounds__(64) k_close(Ws w) {
   Ctrl *c = w.ctrl;
   if (c->done) return;
+  if (c->has_round && c->phase == PHASE_LAZY && w.policy != POL_BINOMIAL && !c->error) {
+    const int pass = c->pass;  // run by this slot, unless it switched
+    if (dsearch(c, pass).pending) {
+      const DSearch s = dsearch(c, pass + 1);
+      if (s.pending || s.switching) {  // the round goes on in the next slot
+        if (threadIdx.x == 0) {
+          c->pass = (int8_t)(pass + 1);
+          c->stage = ST_DELTA;
+          if (!w.team) {
+            const int slots = c->slots + 1;
+            c->slots = slots;
+            if (w.progress)
+              __hip_atomic_store(w.progress, (unsigned long long)(unsigned)slots, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_SYSTEM);
+          }
+        }
+        return;
+      }
+    }
+  }
   const long long now = (long long)wall_clock64();
   if (w.team) {  // the next k_team starts from zeroed counters
     unsigned *t = reinterpret_cast<unsigned *>(w.team);
@@ -1049,7 +1114,9 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
       if (w.policy == POL_BINOMIAL) {
         d = delta_hat(w, c->round);  // Delta-hat_{i+1}: no remaining degree is kept
       } else if (phase_run == PHASE_LAZY) {  // Delta_{i+1} (lazy search, or the exact histogram below)
-        const DSearch s = dsearch(c, DITER);
+        const int pass = c->pass;
+        DSearch s = dsearch(c, pass);
+        if (s.pending) s = dsearch(c, pass + 1);  // the pass this slot ran
         if (s.switching) {
           c->phase = PHASE_EXACT;
           c->rate = 1e30f;  // peeling starts: its first round is measured on the whole device
@@ -1072,6 +1139,7 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
       c->d_max[j] = 0;
     }
     c->x_pack = 0;
+    c->pass = 0;
     if (c->n_rem <= 0 || c->error || (w.max_rounds > 0 && c->round >= w.max_rounds)) c->done = 1;
     // the practical schedule ends by taking every remaining position, so it
     // cannot run out while vertices are left
@@ -1132,7 +1200,7 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
       if (fb) c->fallback = 1;
       c->n_start = n_rem;
       c->t_start = now;
-      c->stage = (int16_t)next_stage(w, b, c->cursor, n_rem, c->rate);
+      c->stage = (int8_t)next_stage(w, b, c->cursor, n_rem, c->rate);
     }
   }
   if (threadIdx.x == 0 && w.progress && (!w.team || done)) {
@@ -1214,16 +1282,11 @@ int round_steps(const Ws &w, const LaunchShape &ls, RoundStep *out) {
   add(k_claim, ls.edge_grid, BS);
   add(k_clear, ls.vertex_grid, BS);
   if (!binomial) {  // Delta-hat needs no remaining degrees: no peel, no Delta search
-    add(k_peel, ls.edge_grid, BS);
-    if (!ls.exact_seen) {  // the run has not switched to exact degrees for good
-      add(k_dscan<0>, ls.vertex_grid, BS);
-      add(k_rescan<0>, ls.edge_grid, BS);
-      add(k_dscan<1>, ls.vertex_grid, BS);
-      add(k_rescan<1>, ls.edge_grid, BS);
-      add(k_dscan<2>, ls.vertex_grid, BS);
-      add(k_rescan<2>, ls.edge_grid, BS);
-      add(k_xlist, grid_for(w.n, ls.vertex_grid), BS);
-      add(k_xcount, ls.edge_grid, BS);
+    if (ls.exact_seen) {  // the run has switched to exact degrees for good
+      add(k_peel, ls.edge_grid, BS);
+    } else {
+      add(k_candidates, ls.vertex_grid, BS);
+      add(k_degrees, ls.edge_grid, BS);
     }
   }
   add(k_close, 1, 64);

@@ -1050,7 +1050,8 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         int *d_max;
       } ds{PHASE_LAZY, delta, dm};
       DSearch sr = dsearch(&ds, 0);
-      for (int pass = 0; sr.pending; pass++) {
+      int pass = 0;
+      for (; sr.pending; pass++) {
         // candidates: live entries with bound >= L
         const int kL = level_of(sr.L < DSW ? DSW : sr.L);
         __syncthreads();
@@ -1105,11 +1106,11 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         if (!team_sync(tm, L)) return;
         const unsigned long long rp = uni(ld(&sl->r_pack[pass]));
         const int rcnt = (int)(pk_cnt(rp) < w.rcap ? pk_cnt(rp) : w.rcap), rwk = (int)pk_work(rp);
-        sum_rescan += (unsigned long long)rwk;
         if (!alone && rwk > TEAM_WORK) {
           to_device = true;
           break;
         }
+        sum_rescan += (unsigned long long)rwk;
         // their exact remaining degrees; new bounds move entries down the levels
         share_of(tm, rwk, &s0, &s1);
         if (tid == 0) L.smax = 0;
@@ -1161,6 +1162,12 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
       if (!to_device && sr.switching) to_device = true;
       d_next = sr.delta;
       if (to_device) {
+        if (lead) {  // the device goes on from this pass
+          c->pass = (int8_t)pass;
+#pragma unroll
+          for (int j = 0; j < DITER; j++)
+            if (j < pass) c->d_max[j] = dm[j];
+        }
         // every workgroup's counts are in: the barrier of the first pass, or here
         if (!team_sync(tm, L)) return;
       }
@@ -1182,7 +1189,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     const int claimed = (int)(clp & 0xFFFFFFFFull);
     const int conflicts = c4 ? nb : uni((int)ld(&sl->conflicts));
     const int listed = c4 ? na - nb + promoted : na;  // centers that were listed
-    if (to_device) {  // k_dscan and what follows finish the round
+    if (to_device) {  // k_candidates and what follows finish the round
       if (lead) {
         if (c4) c->c_pack = pk(0, listed);  // (their rows are counted here)
         else c->a_pack = pk(0, listed);
@@ -1299,7 +1306,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     c->sum_blocked += sum_blocked;
     atomicAdd(&c->sum_atomics, sum_atom);
     if (fallback) c->fallback = 1;
-    c->stage = (int16_t)(done ? ST_TEAM : stage);
+    c->stage = (int8_t)(done ? ST_TEAM : stage);
     if (done) c->done = 1;
     if (!SOLO) end_slot(w, c, done, rounds > 0, false, phase);
   }

@@ -43,6 +43,18 @@ struct NoPost {
   __device__ void operator()() const {}
 };
 
+// What a walk keeps in LDS.  A kernel that takes one of several walks hands
+// the same one to each (lb_walk_in).
+struct WalkLds {
+  int32_t lw[TW + 1];    // first item of each row of the tile, from the tile's start (-1: before it)
+  int32_t lv[TW];
+  int64_t loff[TW];      // where item 0 of the tile would be in col, were it in the row
+  int32_t ldeg[TW];
+  int32_t lval[TW];
+  int64_t ent;
+  int nent, next;
+};
+
 // Calls f(Items&) once per tile in every thread of the workgroup (uniformly,
 // so f may use wave-wide operations).  Row v is col[off[v] .. end[v]) (end =
 // off + 1 for a plain CSR).  `vals` (may be null) is gathered per row into
@@ -53,18 +65,13 @@ struct NoPost {
 // per-row partial results kept in LDS by f can be combined across tiles; then
 // post() runs in every thread (it may use barriers).
 template <class F, class E = NoEpilogue, class P = NoPost>
-__device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restrict__ work, int64_t cnt,
+__device__ __forceinline__ void lb_walk_in(WalkLds &L, const int32_t *__restrict__ list, const int64_t *__restrict__ work, int64_t cnt,
                         int64_t total, const int64_t *__restrict__ off, const int64_t *__restrict__ end,
                         const int32_t *__restrict__ col,
                         const int32_t *__restrict__ vals, const RowInfo *__restrict__ info, F &&f, E &&ep = E(),
                         P &&post = P()) {
-  __shared__ int32_t lw[TW + 1];    // first item of each row of the tile, from the tile's start (-1: before it)
-  __shared__ int32_t lv[TW];
-  __shared__ int64_t loff[TW];      // where item 0 of the tile would be in col, were it in the row
-  __shared__ int32_t ldeg[TW];
-  __shared__ int32_t lval[TW];
-  __shared__ int64_t s_ent;
-  __shared__ int s_nent, s_next;
+  int32_t *lw = L.lw, *lv = L.lv, *ldeg = L.ldeg, *lval = L.lval;
+  int64_t *loff = L.loff;
   if (total <= 0 || cnt <= 0) return;
   const int64_t ntiles = (total + TW - 1) / TW;
   const int64_t nwg = ntiles < (int64_t)gridDim.x ? ntiles : (int64_t)gridDim.x;
@@ -76,13 +83,13 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
   if (threadIdx.x < 64) {
     const int64_t e = wave_find_entry(work, cnt, s0);
     if (threadIdx.x == 0) {
-      s_ent = e;
-      s_nent = 0;
-      s_next = 0;
+      L.ent = e;
+      L.nent = 0;
+      L.next = 0;
     }
   }
   __syncthreads();
-  int64_t ent0 = s_ent;
+  int64_t ent0 = L.ent;
   // the tile's window of row prefixes, held in registers so that the next
   // tile's window is in flight while this tile is processed
   constexpr int NPW = (TW + 1 + BS - 1) / BS;
@@ -110,12 +117,12 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
       w_next += __popcll(__ballot(j <= TW && pw[q] <= s + TW));
     }
     if (lane_id() == 0) {
-      atomicAdd(&s_nent, w_rows);
-      atomicAdd(&s_next, w_next);
+      atomicAdd(&L.nent, w_rows);
+      atomicAdd(&L.next, w_next);
     }
     __syncthreads();
-    const int nent = s_nent;
-    const int next = (s + TW < s1) ? s_next - 1 : 0;
+    const int nent = L.nent;
+    const int next = (s + TW < s1) ? L.next - 1 : 0;
     if (s + TW < s1) load_window(ent0 + next);  // the next tile's window
     for (int j = threadIdx.x; j < nent; j += BS) {
       const int32_t v = list ? list[ent0 + j] : (int32_t)(ent0 + j);
@@ -134,8 +141,8 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
     }
     __syncthreads();
     if (threadIdx.x == 0) {  // every thread has read them; the next tile counts afresh
-      s_nent = 0;
-      s_next = 0;
+      L.nent = 0;
+      L.next = 0;
     }
     Items it;
     it.edge = 0;
@@ -181,6 +188,15 @@ __device__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restr
     ent0 += next;
     __syncthreads();
   }
+}
+
+template <class F, class E = NoEpilogue, class P = NoPost>
+__device__ __forceinline__ void lb_walk(const int32_t *__restrict__ list, const int64_t *__restrict__ work, int64_t cnt,
+                                        int64_t total, const int64_t *__restrict__ off, const int64_t *__restrict__ end,
+                                        const int32_t *__restrict__ col, const int32_t *__restrict__ vals,
+                                        const RowInfo *__restrict__ info, F &&f, E &&ep = E(), P &&post = P()) {
+  __shared__ WalkLds lds;
+  lb_walk_in(lds, list, work, cnt, total, off, end, col, vals, info, f, ep, post);
 }
 
 }  // namespace ccd
