@@ -25,7 +25,7 @@ constexpr int BS = 256;             // threads per workgroup (4 wave64s)
 constexpr int WAVES = BS / 64;
 constexpr int IPT = 4;              // adjacency items per thread per tile
 constexpr int TW = BS * IPT;        // adjacency items per tile
-constexpr int SIPT = 8;            // pi positions per thread in the active-set scan
+constexpr int SIPT = 4;            // pi positions per thread in the active-set scan (2 / 4 / 8: R-MAT 26 53.3 / 51.7 / 52.5 ms)
 constexpr int SEL_BS = 512;         // threads of an active-set scan workgroup
 constexpr int TSEL = SEL_BS * SIPT; // pi positions per scan tile
 constexpr int32_t INF = 0x7fffffff;

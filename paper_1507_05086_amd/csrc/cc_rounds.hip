@@ -559,9 +559,9 @@ __global__ void __launch_bounds__(SEL_BS) k_select(Ws w) {
   const long long ahead = n - cur0, n_i = h.n_rem > 0 ? h.n_rem : 1;
   const long long need_pos = (long long)((double)B * (double)ahead / (double)n_i) + TSEL;
   if ((long long)blockIdx.x > need_pos / TSEL) return;
-  for (;;) {
-    if (threadIdx.x == 0) {
-      s_stop = ld_rlx(&c->select_done);
+  for (bool first = true;; first = false) {
+    if (threadIdx.x == 0) {  // (a first tile is taken without a look at the flag: one dependent read less)
+      s_stop = first ? 0 : ld_rlx(&c->select_done);
       if (!s_stop) s_tile = atomicAdd(&c->tile_counter, 1u);
     }
     __syncthreads();
@@ -715,6 +715,103 @@ __device__ inline void mark_decided(Ws &w, int32_t i, unsigned *tail) {
   w.bq[q] = i;
 }
 
+// The blocked vertices as decided (1: center): centers join the center list.
+template <class F>
+__device__ __forceinline__ void promote_decided(const Ws &w, Ctrl *c, int64_t nb, const int64_t *rend, F &&decided) {
+  for (int64_t i0 = 0; i0 < nb; i0 += RBS) {
+    const int64_t i = i0 + threadIdx.x;
+    int32_t a = 0;
+    bool promote = false;
+    if (i < nb) {
+      a = w.blist[i];
+      const int d = decided(i);
+      if (d == 1) promote = true;
+      else w.state[a] = NONCENTER;
+      if (d == 0) set_error(c, ERR_NO_PROGRESS);  // every blocked vertex is decided by now
+    }
+    RowInfo ri{0, 0, 0};
+    if (promote) {
+      ri = RowInfo{w.off[a], (int32_t)(rend[a] - w.off[a]), w.rank[a]};
+      w.state[a] = CENTER;
+      w.lab[a] = ri.rank;
+    }
+    wave_append_info(promote, a, ri, &c->c_pack, w.clist, w.cwork, w.cinfo);
+  }
+}
+
+// Up to RES_EDGES conflict edges: every thread holds its share in registers
+// (the blocked vertex and the earlier one it waits for as indices of the
+// blocked list) and the decisions are in LDS, so a level of the dependence
+// costs two barriers and no memory, where the queue below pays a chain of six
+// reads and atomics in the L2.  R-MAT 22 under the learned policy 3.65 -> 3.52
+// ms, C4 7.64 -> 7.44 ms; the limit is what fits the registers.
+constexpr int RES_EPT = 32, RES_EDGES = RBS * RES_EPT;
+__device__ void resolve_swept(const Ws &w, Ctrl *c, int nb, int ne, const int64_t *rend) {
+  __shared__ uint8_t dec[RES_EDGES], wait[RES_EDGES];  // (a blocked vertex has an edge)
+  const int tid = threadIdx.x;
+  for (int i = tid; i < nb; i += RBS) {
+    w.bpos[w.blist[i]] = i;
+    dec[i] = 0;
+    wait[i] = 0;
+  }
+  __syncthreads();
+  unsigned ed[RES_EPT];  // vertex | (earlier one + 1, 0: a center) << 16
+  unsigned open = 0;     // edges of vertices that are not decided yet
+  static_assert(RES_EDGES <= 1 << 15, "an index and a zero fit 16 bits");
+  constexpr int CH = 8;  // in flight
+#pragma unroll
+  for (int k0 = 0; k0 < RES_EPT; k0 += CH) {
+    if (k0 * RBS >= ne) break;
+    int2 e[CH];
+    int32_t ia[CH], iu[CH];
+    uint8_t su[CH];
+#pragma unroll
+    for (int k = 0; k < CH; k++) {
+      const int x = (k0 + k) * RBS + tid;
+      e[k] = x < ne ? w.cedge[x] : make_int2(-1, -1);
+    }
+#pragma unroll
+    for (int k = 0; k < CH; k++) {
+      ia[k] = e[k].x >= 0 ? w.bpos[e[k].x] : 0;
+      su[k] = e[k].x >= 0 ? w.state[e[k].y] : (uint8_t)CENTER;
+      iu[k] = e[k].x >= 0 ? w.bpos[e[k].y] : 0;  // (not a position where y is a center)
+    }
+#pragma unroll
+    for (int k = 0; k < CH; k++) {
+      ed[k0 + k] = (unsigned)ia[k] | (su[k] == CENTER ? 0u : (unsigned)(iu[k] + 1) << 16);
+      open |= e[k].x >= 0 ? 1u << (k0 + k) : 0u;
+    }
+  }
+  for (int sweep = 0; sweep <= nb; sweep++) {
+#pragma unroll
+    for (int k = 0; k < RES_EPT; k++) {
+      if (k * RBS >= ne) break;
+      if (open >> k & 1) {
+        const int a = ed[k] & 0xFFFF, u = (int)(ed[k] >> 16) - 1;
+        const int du = u < 0 ? 1 : dec[u];
+        if (dec[a] != 0 || du != 0) open &= ~(1u << k);  // settled either way by what follows
+        if (dec[a] == 0) {
+          if (du == 1) dec[a] = 2;        // an earlier center
+          else if (du == 0) wait[a] = 1;  // an earlier neighbour is open
+        }
+      }
+    }
+    __syncthreads();
+    bool any = false;
+    for (int i = tid; i < nb; i += RBS)
+      if (dec[i] == 0) {
+        if (wait[i]) {
+          wait[i] = 0;
+          any = true;
+        } else {
+          dec[i] = 1;
+        }
+      }
+    if (!__syncthreads_or(any)) break;
+  }
+  promote_decided(w, c, nb, rend, [&](int64_t i) { return (int)dec[i]; });
+}
+
 // The conflict edges are listed: build the dependence graph among the blocked
 // vertices (edge (a, u): a waits for u) and settle it from the vertices whose
 // earlier neighbours are all decided, level by level.  Every blocked vertex
@@ -804,25 +901,7 @@ __device__ void resolve_listed(Ws &w, Ctrl *c, int64_t nb, int64_t ne, const int
     __syncthreads();
     h0 = h1;
   }
-  for (int64_t i0 = 0; i0 < nb; i0 += RBS) {
-    const int64_t i = i0 + threadIdx.x;
-    int32_t a = 0;
-    bool promote = false;
-    if (i < nb) {
-      a = w.blist[i];
-      const int d = w.bdec[i];
-      if (d == 1) promote = true;
-      else w.state[a] = NONCENTER;
-      if (d == 0) set_error(c, ERR_NO_PROGRESS);  // every blocked vertex is decided by now
-    }
-    RowInfo ri{0, 0, 0};
-    if (promote) {
-      ri = RowInfo{w.off[a], (int32_t)(rend[a] - w.off[a]), w.rank[a]};
-      w.state[a] = CENTER;
-      w.lab[a] = ri.rank;
-    }
-    wave_append_info(promote, a, ri, &c->c_pack, w.clist, w.cwork, w.cinfo);
-  }
+  promote_decided(w, c, nb, rend, [&](int64_t i) { return w.bdec[i]; });
 }
 
 // Too many conflict edges to list: sweep the rows of the blocked vertices
@@ -877,7 +956,8 @@ __global__ void __launch_bounds__(RBS) k_resolve(Ws w) {
   const int64_t nb = h.n_blocked;
   if (nb == 0) return;
   const int64_t ne = h.n_cedges;
-  if (ne <= w.cedge_cap) resolve_listed(w, c, nb, ne, round_end(w, h.phase));
+  if (ne <= RES_EDGES) resolve_swept(w, c, (int)nb, (int)ne, round_end(w, h.phase));
+  else if (ne <= w.cedge_cap) resolve_listed(w, c, nb, ne, round_end(w, h.phase));
   else resolve_rows(w, c, nb, round_end(w, h.phase), round_col(w, h.phase));
   __syncthreads();
   for (int64_t i = threadIdx.x; i < nb; i += RBS) w.flag[w.blist[i]] = 0;

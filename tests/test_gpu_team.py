@@ -30,6 +30,10 @@ CASES = {
     # more conflict edges than its LDS holds: the round kernels settle them
     "solo_conflicts": (lambda: _clique(200), 1000.0),
     "team_conflicts": (lambda: _clique(400), 1000.0),
+    # the most conflict edges k_resolve keeps in registers, one row more, and a long chain of them
+    "resolve_edge": (lambda: _clique(256), 1000.0),
+    "resolve_past": (lambda: _clique(257), 1000.0),
+    "chain_at_once": (lambda: graphgen.from_edges(30_000, [(i, i + 1) for i in range(29_999)]), 4.0),
     # rows longer than a workgroup keeps for itself, a chain of blocked vertices
     "long_rows": (lambda: _star_ring(30_000, 3), 2.0),
     "chain": (lambda: graphgen.from_edges(60_000, [(i, i + 1) for i in range(59_999)]), 0.05),
@@ -58,7 +62,7 @@ def test_team_against_oracle(name, algo):
     make, eps = CASES[name]
     g = make()
     gh = cc.cc_graph_from_csr(torch.from_numpy(g.off).cuda(), torch.from_numpy(g.col).cuda())
-    order = np.arange(g.n, dtype=np.int32) if name == "chain" else graphgen.permutation(g.n, 5)
+    order = np.arange(g.n, dtype=np.int32) if name.startswith("chain") else graphgen.permutation(g.n, 5)
     for _ in range(2):  # the workspace of the first run serves the second
         _check(cc, gh, g, order, eps, algo)
 
