@@ -95,8 +95,9 @@ __device__ inline void report(int *err, int code) { atomicMin(err, ((code == 10 
 // and equal counts make the mirror map one-to-one and onto, so the graph is
 // symmetric.  Anything else found is reported as CHECK_AGAIN, and validate
 // == 2 (every entry searched) names it.  Power law 1 M, 40 M entries, dependent
-// cold reads of the search: 4.1 ms with every entry searched, 2.0 ms with
-// half of them, and those in the shorter row.
+// reads of the search: 4.1 ms with every entry searched, 2.0 ms with
+// half of them and those in the shorter row, 1.5 ms where an equal entry ends
+// the search (2.4 ms by quarters: fewer steps but more reads).
 __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
   long long above = 0;
   lb_walk(nullptr, a.wall, a.n, a.wall[a.n], a.off, a.off + 1, a.col, nullptr, nullptr, [&](Items &it) {
@@ -151,8 +152,14 @@ __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
       for (int k = 0; k < IPT; k++)
         if (lo[k] < hi[k]) {
           const int64_t mid = lo[k] + ((hi[k] - lo[k]) >> 1);
-          if (c[k] < x[k]) lo[k] = mid + 1;
-          else hi[k] = mid;
+          if (c[k] == x[k] && a.validate == 1) {  // found (on a row out of order validate 2 asks for the first entry not below)
+            x[k] = -1;
+            hi[k] = lo[k];
+          } else if (c[k] < x[k]) {
+            lo[k] = mid + 1;
+          } else {
+            hi[k] = mid;
+          }
           more |= lo[k] < hi[k];
         }
     }
