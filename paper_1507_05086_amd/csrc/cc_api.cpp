@@ -808,8 +808,7 @@ size_t shape_lds(const cc_graph *g, const cc_batch_config &c, int *cap_big, int 
   return batched_lds_bytes(c.block, cap[0], cap[1], cap[2]);
 }
 
-// Static LDS of the batched kernel (graph id, scan scratch, 256 B of window
-// scratch per wave), with slack.
+// Static LDS of the batched kernel (graph id, scan scratch), with slack.
 constexpr int kBatchStaticLds = 4608;
 
 int32_t check_shape(const cc_graph *g, const cc_batch_config &c) {
@@ -829,9 +828,10 @@ int32_t check_shape(const cc_graph *g, const cc_batch_config &c) {
 // The shape of a handle that was not tuned.  The largest graph bounds the
 // launch unless there are many, and more threads finish it sooner, so the
 // block is 1024.  With more than four graphs per compute unit the middle ones
-// run four to a workgroup.  Planted-block batches, (256, 512, 0) before / this:
-// 16 graphs 0.61 / 0.31 ms, 301 0.89 / 0.44, 1000 2.52 / 0.71, 4096 3.60 / 1.17
-// (C4); at 4096 (1024, 256, 1024) takes 1.48 ms and at 301 (1024, 384, 1792) 0.51.
+// run four to a workgroup.  Planted-block batches, (256, 512, 0) / this, when
+// rows were walked edge-balanced: 16 graphs 0.61 / 0.31 ms, 301 0.89 / 0.44,
+// 1000 2.52 / 0.71, 4096 3.60 / 1.17 (C4); at 4096 (1024, 256, 1024) took 1.48
+// ms and at 301 (1024, 384, 1792) 0.51.
 cc_batch_config default_shape(const cc_graph *g) {
   return g->num_graphs > 1024 ? cc_batch_config{1024, 384, 1792, 0, 0.0} : cc_batch_config{1024, 256, 1024, 0, 0.0};
 }
@@ -887,7 +887,7 @@ int32_t launch_batch(cc_graph *g, int algo, const int32_t *d_order, int64_t eps_
   HIP_TRY(hipMemsetAsync(b.out, 0, offsetof(BatchOut, rounds), s));
   BatchLaunch bl{g->off, g->col, g->vtx_ptr, d_order, d_labels, b.queue, b.n_big, b.n_quad, g->num_graphs,
                  b.cap_big, b.cap_quad, b.cap_wave, b.out->heads, b.out->rounds, b.out->stat, &b.out->err, algo, eps_q,
-                 c.block, b.grid};
+                 c.block, b.grid, g->nnz};
   if (ev0) HIP_TRY(hipEventRecord(ev0, s));
   HIP_TRY(launch_batched(bl, s));
   if (ev1) HIP_TRY(hipEventRecord(ev1, s));

@@ -7,10 +7,8 @@
 // per workgroup).  Groups take graphs from two queues (large first, most work
 // first), so the launch is balanced by longest-processing-time order.
 // Inside a graph the remaining degrees are kept exactly (LDS atomics are
-// cheap), and the adjacency passes (election, claims, peeling) are
-// edge-balanced: each wave walks a contiguous range of the concatenated rows,
-// streaming long rows with several loads in flight and locating row
-// boundaries inside mixed windows with one LDS scatter and a wave scan.
+// cheap), and the adjacency passes (election, claims, peeling) give each row
+// to a few lanes (rows_pass).
 #include "cc_device.h"
 #include "cc_launch.h"
 #include "cc_round.h"
@@ -105,12 +103,6 @@ struct Grp {
   __device__ __forceinline__ bool any(bool p) const { return max(p ? 1 : 0) != 0; }
 };
 
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct BStats {
   unsigned long long elect, claim, peel, atom;
 };
@@ -132,12 +124,12 @@ struct BatchArgs {
   int *err;
   int algo;
   int64_t eps_q;
+  int64_t nnz;             // entries of col
 };
 
 // LDS slot of capacity N vertices (21 bytes per vertex plus a few words):
+//   row    start and end of each row in the graph's cols
 //   lw     packed clusterID | remaining degree
-//   pref   [N+1] prefix of row lengths of the list being walked
-//   rstart [N+1] start of each row in the graph's cols
 //   ctr    list counter
 //   fl     flag byte, padded to whole words (word atomics touch 4 flags)
 //   rank   pi^-1 (int16)
@@ -145,19 +137,18 @@ struct BatchArgs {
 //   alist  active vertices; compacted in place to the centers
 //   nlist  undecided actives during the election, then the newly clustered
 struct Slot {
+  int2 *row;
   uint32_t *lw;
-  int32_t *pref, *rstart;
   int *ctr;
   uint8_t *fl;
   int16_t *rank, *ordl, *alist, *nlist;
   __host__ __device__ static size_t bytes(int N) {
     return (((size_t)N * 20 + 12 + (((size_t)N + 3) & ~(size_t)3)) + 15) / 16 * 16;
   }
-  __device__ void carve(uint8_t *p, int N) {
-    lw = (uint32_t *)p;
-    pref = (int32_t *)(lw + N);
-    rstart = pref + N + 1;
-    ctr = rstart + N + 1;
+  __device__ void carve(uint8_t *p, int N) {  // p: a multiple of 16
+    row = (int2 *)p;
+    lw = (uint32_t *)(row + N);
+    ctr = (int *)(lw + N);
     fl = (uint8_t *)(ctr + 1);
     rank = (int16_t *)(fl + ((N + 3) & ~3));
     ordl = rank + N;
@@ -171,133 +162,137 @@ struct __attribute__((packed, aligned(4))) Cols4 {
   int32_t u[4];
 };
 
-// Edge-balanced pass over the rows of list[0..cnt): f(i, v, u) for every
-// entry u of row v = list[i]; row v is col0[rstart[v] .. rstart[v+1]).  `rs`
-// is the calling wave's 64 ints of LDS scratch.  Each wave walks a contiguous
-// range of the concatenated rows: a row covering the next 64 or more entries
-// is streamed with K loads in flight; otherwise up to W windows of 64 entries
-// have their rows located (LDS only) before their loads are issued together.
-// Returns the number of entries walked.
-template <class GR, int K, int W, class F>
-__device__ __forceinline__ int rows_pass(const GR &g, const int16_t *list, int cnt, Slot &s, const int32_t *col0,
-                                int *rs, F &&f) {
-  constexpr int G = GR::size;
-  int carry = 0;
-  for (int i0 = 0; i0 < cnt; i0 += G) {
-    const int i = i0 + g.tid;
-    int d = 0;
-    if (i < cnt) {
-      const int32_t v = list[i];
-      d = s.rstart[v + 1] - s.rstart[v];
-    }
-    int tot;
-    const int pre = g.scan(d, &tot);
-    if (i < cnt) s.pref[i] = carry + pre;
-    carry += tot;
-  }
-  const int total = carry;
-  if (g.tid == 0) s.pref[cnt] = total;
-  g.sync();
-  if (total == 0) return 0;
-  constexpr int NW = G / 64, V = 2;
+// How the rows of a graph are walked: W = 1 << lg lanes share a row, four
+// consecutive entries of it per lane and step.
+struct Walk {
+  const int32_t *col0;  // the graph's columns
+  int last4;            // entries from here on (of col0) cannot be read four at a time: the array ends
+  bool wide;            // four can be read at all
+  int lg;
+  int most;             // entries from which a row is walked by the whole group
+  bool longs;           // some row has as many
+};
+constexpr int LONG = 256, SEG = 512;  // a long row is dealt to the waves by segments
+
+// Pass over the rows of list[0..cnt): act(v, val(v), u) for every entry u of
+// row v whose flags pass test(flags of u); returns this lane's share of the
+// entries walked.  The kernel is bound by instruction issue (81 % of the
+// cycles had one, at 4 waves a SIMD), so a row goes to a few lanes that read
+// four or eight whole entries each: no prefix over the list and no search for
+// an entry's row, which took most of the 58 vector instructions per 64
+// entries that an edge-balanced walk had.  Rows far longer than the others
+// are walked by the whole group, so a hub does not leave it idle.  Planted
+// blocks, edge-balanced / this: 4096 graphs C4 1.22 / 0.86 ms, ClusterWild!
+// 0.96 / 0.73, 301 graphs 0.38 / 0.23; two rows of a sub-wave at once, their
+// ends tested entry by entry, took 1.34 and 0.34.  Stars, one row each that
+// counts, are what it costs: 95 -> 105 us for 16 of 5000 vertices.
+template <class GR, class Val, class Test, class Act>
+__device__ __forceinline__ unsigned rows_pass(const GR &g, const int16_t *list, int cnt, const Slot &s, const Walk &k,
+                                              Val &&val, Test &&test, Act &&act) {
+  constexpr int NW = GR::size / 64;
   const int lane = lane_id();
   const int w = NW == 1 ? 0 : g.wave();
-  int chunk = (total + NW - 1) / NW;
-  chunk = (chunk + 63) & ~63;
-  const int c0 = min(total, w * chunk), c1 = min(total, c0 + chunk);
-  if (c0 < c1) {
-    // lo: the last row whose prefix is <= c0 (the same search in every lane);
-    // row 0 already satisfies the invariant below when c0 = 0
-    int lo = 0, hi = c0 > 0 ? cnt : 1;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s.pref[mid] <= c0) lo = mid;
-      else hi = mid;
+  const int32_t *col0 = k.col0;
+  unsigned walked = 0;
+  if (k.longs) {
+    int turn = w;  // the wave whose segment comes first moves on from row to row
+    for (int i0 = 0; i0 < cnt; i0 += 64) {
+      int v = 0;
+      bool lg = false;
+      if (i0 + lane < cnt) {
+        v = list[i0 + lane];
+        lg = s.row[v].y - s.row[v].x >= k.most;
+      }
+      for (unsigned long long m = __ballot(lg); m; m &= m - 1) {
+        const int a = __builtin_amdgcn_readlane(v, __ffsll((long long)m) - 1);
+        const int2 r = s.row[a];
+        const int d = r.y - r.x, x = val(a);
+        const int32_t *cp = col0 + r.x;
+        for (int e = (turn++ & (NW - 1)) * SEG; e < d; e += NW * SEG) {
+          int32_t u[8];
+          if (e + SEG <= d) {
+            const Cols4 q0 = *reinterpret_cast<const Cols4 *>(cp + e + 4 * lane);
+            const Cols4 q1 = *reinterpret_cast<const Cols4 *>(cp + e + SEG / 2 + 4 * lane);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+              u[j] = q0.u[j];
+              u[4 + j] = q1.u[j];
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++) u[j] = e + 64 * j + lane < d ? cp[e + 64 * j + lane] : -1;
+          }
+          uint8_t f[8];
+#pragma unroll
+          for (int j = 0; j < 8; j++) f[j] = s.fl[u[j] < 0 ? 0 : u[j]];
+#pragma unroll
+          for (int j = 0; j < 8; j++)
+            if (u[j] >= 0 && test(f[j])) act(a, x, u[j]);
+        }
+        if (w == 0 && lane == 0) walked += (unsigned)d;
+      }
     }
-    // invariant: pref[lo] <= e0 <= pref[lo + 1] and lo < cnt
-    int e0 = c0;
-    while (e0 < c1) {
-      const int b0 = s.pref[lo + 1];
-      if (b0 >= e0 + 64) {
-        // row lo covers the next 64 or more entries: stream them
-        const int end = min(b0, c1);
-        const int32_t v = list[lo];
-        const int32_t *cp = col0 + (s.rstart[v] - s.pref[lo]);
-        int e = e0;
-        for (; e + 256 * V <= end; e += 256 * V) {  // 16-byte loads, V in flight per lane
-          Cols4 q[V];
+  }
+  int lg = k.lg;  // more lanes a row where the list has fewer rows than the group has places for
+  while (lg < 6 && cnt <= (NW << (5 - lg))) lg++;
+  const int gl = lane & ((1 << lg) - 1), rows = NW << (6 - lg), step = 4 << lg;
+  for (int i = (w << (6 - lg)) + (lane >> lg); i < cnt; i += rows) {
+    const int v = list[i], x = val(v);
+    const int2 r = s.row[v];
+    const int r0 = r.x, r1 = r.y;
+    if (r1 - r0 >= k.most) continue;  // walked above
+    if (gl == 0) walked += (unsigned)(r1 - r0);
+    for (int b = r0 + 4 * gl; b < r1;) {
+      if (__all(b + step + 4 <= r1)) {  // eight whole entries in every lane that is still at it
+        const Cols4 q0 = *reinterpret_cast<const Cols4 *>(col0 + b), q1 = *reinterpret_cast<const Cols4 *>(col0 + b + step);
+        uint8_t f[8];
 #pragma unroll
-          for (int k = 0; k < V; k++) q[k] = *reinterpret_cast<const Cols4 *>(cp + e + 256 * k + 4 * lane);
-#pragma unroll
-          for (int k = 0; k < V; k++)
-#pragma unroll
-            for (int x = 0; x < 4; x++) f(lo, v, q[k].u[x]);
+        for (int j = 0; j < 4; j++) {
+          f[j] = s.fl[q0.u[j]];
+          f[4 + j] = s.fl[q1.u[j]];
         }
-        for (; e < end; e += 64 * K) {
-          int32_t u[K];
 #pragma unroll
-          for (int k = 0; k < K; k++) u[k] = e + 64 * k + lane < end ? cp[e + 64 * k + lane] : -1;
-#pragma unroll
-          for (int k = 0; k < K; k++)
-            if (u[k] >= 0) f(lo, v, u[k]);
-        }
-        e0 = end;
-        if (e0 == b0) lo++;
+        for (int j = 0; j < 8; j++)
+          if (test(f[j])) act(v, x, j < 4 ? q0.u[j & 3] : q1.u[j & 3]);
+        b += 2 * step;
         continue;
       }
-      // up to W windows [e0, e0 + 64) holding row starts: the row of entry
-      // e0 + l is lo + #{j : pref[lo + 1 + j] <= e0 + l}
-      int rowk[W], ek[W];
+      // the row's last four may end behind it, and at the array's end they
+      // start before the lane's own first
+      int32_t u[4];
+      bool in[4];
+      if (k.wide) {
+        const int at = b < k.last4 ? b : k.last4;
+        const Cols4 q = *reinterpret_cast<const Cols4 *>(col0 + at);
 #pragma unroll
-      for (int k = 0; k < W; k++) {
-        rowk[k] = -1;
-        ek[k] = -1;
-        if (e0 >= c1 || (k > 0 && s.pref[lo + 1] >= e0 + 64)) continue;  // uniform
-        const int j = lo + 1 + lane;
-        const int bj = j <= cnt ? s.pref[j] : 0x7fffffff;
-        const bool in = bj <= e0 + 63;
-        const bool full = __ballot(in) == ~0ull;
-        int wend = full ? lane_value(bj, 63) : e0 + 64;
-        if (wend > c1) wend = c1;
-        rs[lane] = 0;
-        wave_sync();
-        const int bn = __shfl_down(bj, 1, 64);
-        if (in && (lane == 63 || bn != bj)) rs[bj - e0] = lane + 1;
-        wave_sync();
-        const int r = wave_incl_max(rs[lane]);
-        if (e0 + lane < wend) {
-          rowk[k] = lo + r;
-          ek[k] = e0 + lane;
+        for (int j = 0; j < 4; j++) {
+          u[j] = q.u[j];
+          in[j] = at + j >= b && at + j < r1;
         }
-        lo += __popcll(__ballot(bj <= wend));
-        e0 = wend;
-        wave_sync();
-      }
-      int32_t vk[W], ck[W], uk[W];
+      } else {
 #pragma unroll
-      for (int k = 0; k < W; k++) {
-        vk[k] = 0;
-        ck[k] = 0;
-        if (rowk[k] >= 0) {
-          vk[k] = list[rowk[k]];
-          ck[k] = s.rstart[vk[k]] + (ek[k] - s.pref[rowk[k]]);
+        for (int j = 0; j < 4; j++) {
+          in[j] = b + j < r1;
+          u[j] = in[j] ? col0[b + j] : 0;
         }
       }
+      uint8_t f[4];
 #pragma unroll
-      for (int k = 0; k < W; k++) uk[k] = rowk[k] >= 0 ? col0[ck[k]] : -1;
+      for (int j = 0; j < 4; j++) f[j] = s.fl[in[j] ? u[j] : 0];
 #pragma unroll
-      for (int k = 0; k < W; k++)
-        if (rowk[k] >= 0) f(rowk[k], vk[k], uk[k]);
+      for (int j = 0; j < 4; j++)
+        if (in[j] && test(f[j])) act(v, x, u[j]);
+      b += step;
     }
   }
   g.sync();
-  return total;
+  return walked;
 }
 
 // Inlined into the kernel so that every Slot pointer is known to address LDS
 // (an out-of-line call would turn them into generic pointers).
 template <class GR>
-__device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int gi, int cap, Slot &s, int *rs, BStats &st) {
+__device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int gi, int cap, Slot &s, BStats &st) {
   constexpr int G = GR::size;
   const int64_t v0 = a.vtx_ptr[gi];
   const int n = (int)(a.vtx_ptr[gi + 1] - v0);
@@ -310,16 +305,13 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
   const int32_t *col0 = a.col + obase;
   const int32_t *ord = a.order + v0;
   const bool c4 = a.algo == ALGO_C4;
-  constexpr int K = 4, W = 4;
   // init: row starts, packed words, pi in LDS; rank = pi^-1 with a permutation check
-  for (int v = g.tid; v <= n; v += G) {
-    const int64_t o = off[v];
-    s.rstart[v] = (int32_t)(o - obase);
-    if (v < n) {
-      s.lw[v] = lw_pack(INF16, (uint32_t)(off[v + 1] - o));
-      s.fl[v] = F_UNC;
-      s.rank[v] = -1;
-    }
+  for (int v = g.tid; v < n; v += G) {
+    const int64_t o = off[v], e = off[v + 1];
+    s.row[v] = make_int2((int32_t)(o - obase), (int32_t)(e - obase));
+    s.lw[v] = lw_pack(INF16, (uint32_t)(e - o));
+    s.fl[v] = F_UNC;
+    s.rank[v] = -1;
   }
   g.sync();
   bool bad = false;
@@ -338,6 +330,14 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
     if (g.tid == 0) atomicCAS(a.err, 0, ERR_PERM);
     return;
   }
+  // lanes of a row, by the mean length (a step takes four entries of a lane,
+  // then eight).  At most 8 / 16 / 32 / 64 lanes: planted blocks of 4096
+  // graphs 0.85 / 0.87 / 1.00 ms / -, 301 0.226 / 0.242 / 0.245; at most 4:
+  // 0.89 and 0.229
+  const int64_t tail = a.nnz - 4 - obase;
+  const int mean = n > 0 ? s.row[n - 1].y / n : 0;
+  Walk walk{col0, (int)(tail < 0x7fffffff ? tail : 0x7fffffff), a.nnz >= 4, mean <= 2 ? 0 : mean <= 24 ? 1 : mean <= 48 ? 2 : 3,
+            8 * mean > LONG ? 8 * mean : LONG, false};
   int n_rem = n, cur = 0, rounds = 0;
   while (n_rem > 0 && rounds <= n) {
     // Delta over the unclustered vertices
@@ -347,6 +347,7 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
       if ((s.fl[v] & F_UNC) && d > m) m = d;
     }
     const long long delta = g.max(m);
+    if (rounds == 0) walk.longs = delta >= walk.most;
     const int B = (int)fixed_batch(a.eps_q, n_rem, delta);
     // active set: the next B unclustered vertices of pi from the cursor
     int na = 0;
@@ -379,10 +380,11 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
     int nc = 0;
     if (c4) {
       // blocked: an earlier-ranked active neighbour
-      const int t_elect = rows_pass<GR, K, W>(g, s.alist, B, s, col0, rs, [&](int, int32_t av, int32_t u) {
-        if ((s.fl[u] & F_ACT) && s.rank[u] < s.rank[av]) s.fl[av] |= F_BLK;
+      const auto rank_of = [&](int v) { return (int)s.rank[v]; };
+      const auto active = [](uint8_t f) { return (f & F_ACT) != 0; };
+      st.elect += rows_pass(g, s.alist, B, s, walk, rank_of, active, [&](int av, int r, int32_t u) {
+        if (s.rank[u] < r) s.fl[av] |= F_BLK;
       });
-      if (g.tid == 0) st.elect += (unsigned long long)t_elect;
       for (int i = g.tid; i < B; i += G) {
         const int32_t av = s.alist[i];
         if (!(s.fl[av] & F_BLK)) s.fl[av] |= F_CEN;
@@ -407,14 +409,13 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
         }
         g.sync();
         if (nb == 0) break;
-        const int t_res = rows_pass<GR, K, W>(g, s.nlist, nb, s, col0, rs, [&](int, int32_t av, int32_t u) {
-          const uint8_t fu = s.fl[u];
-          if ((fu & F_ACT) && s.rank[u] < s.rank[av]) {
+        st.elect += rows_pass(g, s.nlist, nb, s, walk, rank_of, active, [&](int av, int r, int32_t u) {
+          if (s.rank[u] < r) {
+            const uint8_t fu = s.fl[u];
             const unsigned bit = (fu & F_CEN) ? (unsigned)F_MC : ((fu & F_NON) ? 0u : (unsigned)F_MU);
             if (bit) atomicOr((unsigned *)(s.fl + (av & ~3)), bit << (8 * (av & 3)));
           }
         });
-        if (g.tid == 0) st.elect += (unsigned long long)t_res;
         for (int i = g.tid; i < nb; i += G) {
           const int32_t av = s.nlist[i];
           const uint8_t f = s.fl[av];
@@ -455,31 +456,31 @@ __device__ __forceinline__ void solve_graph(const GR &g, const BatchArgs &a, int
       s.nlist[atomicAdd(nn_ptr, 1)] = (int16_t)cv;
     }
     g.sync();
-    const int t_claim = rows_pass<GR, K, W>(g, s.alist, nc, s, col0, rs, [&](int, int32_t cv, int32_t u) {
-      const uint8_t fu = s.fl[u];
-      if (!(fu & F_UNC) || (fu & F_CEN)) return;
-      if (!c4 && (fu & F_ACT)) return;  // ClusterWild! claims Gamma(c) \ A
-      const uint32_t rc = (uint32_t)s.rank[cv];
-      if (rc < (s.lw[u] >> 16)) {
-        const uint32_t old = atomicMin(&s.lw[u], lw_pack(rc, 0xFFFFu));
-        st.atom++;
-        if ((old >> 16) == INF16) s.nlist[atomicAdd(nn_ptr, 1)] = (int16_t)u;
-      }
-    });
-    if (g.tid == 0) st.claim += (unsigned long long)t_claim;
+    // ClusterWild! claims Gamma(c) \ A
+    const uint8_t unfit = c4 ? F_CEN : F_CEN | F_ACT;
+    st.claim += rows_pass(
+        g, s.alist, nc, s, walk, [&](int v) { return (int)s.rank[v]; },
+        [&](uint8_t f) { return (f & (F_UNC | unfit)) == F_UNC; },
+        [&](int, int r, int32_t u) {
+          const uint32_t rc = (uint32_t)r;
+          if (rc < (s.lw[u] >> 16)) {
+            const uint32_t old = atomicMin(&s.lw[u], lw_pack(rc, 0xFFFFu));
+            st.atom++;
+            if ((old >> 16) == INF16) s.nlist[atomicAdd(nn_ptr, 1)] = (int16_t)u;
+          }
+        });
     const int nn = *nn_ptr;
     // the newly clustered leave; the unclustered neighbours of the claimed
     // ones lose one degree.  Centers (nlist[0, nc)) have none left: every
     // unclustered neighbour of a center was claimed this round.
     for (int i = g.tid; i < nn; i += G) s.fl[s.nlist[i]] = 0;
     g.sync();
-    const int t_peel = rows_pass<GR, K, W>(g, s.nlist + nc, nn - nc, s, col0, rs, [&](int, int32_t, int32_t u) {
-      if (s.fl[u] & F_UNC) {
-        atomicSub(&s.lw[u], 1u);
-        st.atom++;
-      }
-    });
-    if (g.tid == 0) st.peel += (unsigned long long)t_peel;
+    st.peel += rows_pass(
+        g, s.nlist + nc, nn - nc, s, walk, [](int) { return 0; }, [](uint8_t f) { return (f & F_UNC) != 0; },
+        [&](int, int, int32_t u) {
+          atomicSub(&s.lw[u], 1u);
+          st.atom++;
+        });
     n_rem -= nn;
     rounds++;
     g.sync();
@@ -504,8 +505,6 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
   __shared__ int sh[T / 64];
   __shared__ int shq[NQ][QG / 64];
   __shared__ SubBar sbar[NQ];
-  __shared__ int rsb[T / 64][64];
-  int *rs = rsb[wave_id()];
   if (threadIdx.x < NQ) sbar[threadIdx.x] = SubBar{0, 0};
   __syncthreads();
   // phase 1: large graphs, one per workgroup
@@ -521,7 +520,7 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
     const int gi = s_gi[0];
     __syncthreads();
     if (gi < 0) break;
-    solve_graph(gw, a, gi, a.cap_big, sl, rs, st);
+    solve_graph(gw, a, gi, a.cap_big, sl, st);
     __syncthreads();
   }
   // phase 2: mid-size graphs, one per sub-group of 4 waves (workgroups of 512+)
@@ -539,7 +538,7 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
       const int gi = s_gi[sg];
       gq.sync();
       if (gi < 0) break;
-      solve_graph(gq, a, gi, a.cap_quad, sq, rs, st);
+      solve_graph(gq, a, gi, a.cap_quad, sq, st);
       gq.sync();
     }
     __syncthreads();
@@ -554,7 +553,7 @@ __global__ void __launch_bounds__(T) k_batched(BatchArgs a) {
     if (lane_id() == 0) q = (int)atomicAdd(&a.heads[1], 1u);
     q = __shfl(q, 0, 64);
     if (q >= nsmall) break;
-    solve_graph(gv, a, a.queue[n0 + q], a.cap_wave, sv, rs, st);
+    solve_graph(gv, a, a.queue[n0 + q], a.cap_wave, sv, st);
   }
   // statistics: one reduction per workgroup, one atomic per counter
   __syncthreads();
@@ -579,7 +578,7 @@ static hipError_t allow_lds(int block, size_t lds) {
 
 hipError_t launch_batched(const BatchLaunch &bl, hipStream_t s) {
   BatchArgs a{bl.off, bl.col, bl.vtx_ptr, bl.order, bl.labels, bl.queue, bl.n_big, bl.n_quad, bl.num_graphs,
-              bl.cap_big, bl.cap_quad, bl.cap_wave, bl.heads, bl.rounds, bl.stat, bl.err, bl.algo, bl.eps_q};
+              bl.cap_big, bl.cap_quad, bl.cap_wave, bl.heads, bl.rounds, bl.stat, bl.err, bl.algo, bl.eps_q, bl.nnz};
   const size_t lds = batched_lds_bytes(bl.block, bl.cap_big, bl.cap_quad, bl.cap_wave);
   hipError_t e = allow_lds(bl.block, lds);
   if (e != hipSuccess) return e;

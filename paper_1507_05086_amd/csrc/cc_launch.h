@@ -73,6 +73,7 @@ struct BatchLaunch {
   int algo;
   int64_t eps_q;
   int block, grid;
+  int64_t nnz;
 };
 hipError_t launch_batched(const BatchLaunch &bl, hipStream_t s);
 size_t batched_lds_bytes(int block, int cap_big, int cap_quad, int cap_wave);
