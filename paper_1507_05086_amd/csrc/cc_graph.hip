@@ -98,6 +98,9 @@ __device__ inline void report(int *err, int code) { atomicMin(err, ((code == 10 
 // reads of the search: 4.1 ms with every entry searched, 2.0 ms with
 // half of them and those in the shorter row, 1.5 ms where an equal entry ends
 // the search (2.4 ms by quarters: fewer steps but more reads).
+// Without validation (a kernel of its own: the searches' registers cost the
+// range check 3 of 10 ms on R-MAT 26) only the range is checked.
+template <bool VALIDATE>
 __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
   long long above = 0;
   lb_walk(nullptr, a.wall, a.n, a.wall[a.n], a.off, a.off + 1, a.col, nullptr, nullptr, [&](Items &it) {
@@ -119,7 +122,7 @@ __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
         report(a.err, 10);  // CC_ERR_OUT_OF_RANGE
         continue;
       }
-      if (!a.validate) continue;
+      if (!VALIDATE) continue;
       const int32_t vl = (int32_t)(v - base);
       const int64_t e = it.pos[k];
       const bool loop = u == vl, disorder = e + 1 < a.off[v + 1] && a.col[e + 1] <= u;
@@ -139,7 +142,7 @@ __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
         x[k] = vl;
       }
     }
-    if (!a.validate) return;
+    if (!VALIDATE) return;
     // the searches of this thread's entries step together
     bool more = true;
     while (more) {
@@ -170,7 +173,7 @@ __global__ void __launch_bounds__(BS) k_check(CheckArgs a) {
         else atomicMin(a.err, CHECK_AGAIN);
       }
   });
-  if (a.validate == 1) {
+  if (VALIDATE && a.validate == 1) {
     const int64_t t = wave_sum((int64_t)above);
     if (lane_id() == 0 && t) atomicAdd(a.above, (unsigned long long)t);
   }
@@ -218,7 +221,7 @@ __global__ void k_gid(const int64_t *vtx_ptr, int32_t num_graphs, int32_t *gid) 
 
 hipError_t launch_graph_check(const CheckArgs &a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check, dim3(4096), dim3(BS), 0, s, a);
+  hipLaunchKernelGGL(a.validate ? k_check<true> : k_check<false>, dim3(4096), dim3(BS), 0, s, a);
   if (a.validate == 1) hipLaunchKernelGGL(k_check_counts, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
