@@ -172,15 +172,16 @@ struct RowInfo {
 // What k_team takes (one XCD, an eighth of the device).  A round with more
 // positions to pass, or more to walk, is a matter of throughput and runs on
 // the whole device; so does the rest of a round whose Delta candidates or
-// level entries turn out longer.  A round costs 20 - 45 us on a team and 70 -
-// 100 us as kernels while it is short.  Measured (median call, team limits
-// varied): TEAM_ITEMS 2^17 / 2^18 / 2^19: power law 2 M ClusterWild! 6.3 /
-// 5.5 / 5.6 ms, R-MAT 22 under the learned policy 3.59 / 3.73 / 3.83 ms,
-// R-MAT 23 C4 11.6 / 11.1 / 11.0 ms; TEAM_WORK 2^20 / 2^22: R-MAT 23 C4 11.1 /
-// 11.8 ms; TEAM_POS 2^16 / 2^18 / 2^20: R-MAT 22 C4 9.1 / 7.65 / 7.65 ms,
+// level entries turn out longer.  A round costs 15 - 45 us on a team and 55 -
+// 90 us as kernels while it is short.  Measured (median call, team limits
+// varied): TEAM_ITEMS 2^17 / 2^18: power law 2 M ClusterWild! 6.1 / 5.7 ms,
+// R-MAT 22 C4 7.50 / 7.31, under the learned policy 3.29 / 3.47 ms, R-MAT 23 C4
+// 11.1 / 10.9 ms; with slots of 13 to 16 kernels, TEAM_ITEMS 2^19: 5.6, -,
+// 3.83, 11.0 (2^18: 5.5, -, 3.73, 11.1), TEAM_WORK 2^20 / 2^22: R-MAT 23 C4 11.1
+// / 11.8 ms, TEAM_POS 2^16 / 2^18 / 2^20: R-MAT 22 C4 9.1 / 7.65 / 7.65 ms,
 // learned 3.8 / 3.7 / 4.0 ms.  Graphs above TEAM_MAX_N vertices stay with the
-// kernels: R-MAT 23 C4 13.4 -> 11.1 ms, but R-MAT 24 14.1 -> 14.2 and R-MAT 26
-// (C4 + ClusterWild!) 56.6 -> 61 ms.
+// kernels: R-MAT 23 C4 11.1 -> 10.9 ms with a team, R-MAT 22 9.8 -> 7.3, but
+// R-MAT 24 14.1 -> 14.2 and R-MAT 26 (C4 + ClusterWild!) 56.6 -> 61 ms.
 constexpr int64_t TEAM_MAX_N = int64_t(1) << 23;
 constexpr long long TEAM_POS = 1 << 18;     // positions of pi to pass
 constexpr long long TEAM_ITEMS = 1 << 18;   // entries that claims and peeling are expected to walk
