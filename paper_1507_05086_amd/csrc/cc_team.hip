@@ -507,7 +507,9 @@ __device__ inline bool run_init(const Ws &w, Lds &L) {
 }
 
 // k_finalize by one workgroup: every label is looked at before the first is
-// written, so a failing run leaves the caller's buffer alone.
+// written, so a failing run leaves the caller's buffer alone.  The input id of
+// a center comes from the workspace, not from order_in: the caller may have
+// given one buffer as pi and as labels.
 __device__ inline void run_labels(const Ws &w, Ctrl *c) {
   const int n = (int)w.n, tid = threadIdx.x;
   const bool bounded = w.max_rounds > 0;
@@ -520,7 +522,7 @@ __device__ inline void run_labels(const Ws &w, Ctrl *c) {
       if (v < w.iso_start && !bit(w.unc, v)) return vin;
       return bounded ? -1 : -2;
     }
-    return l < 0 || l >= n ? -2 : w.order_in[l];
+    return l < 0 || l >= n ? -2 : w.iperm[w.iorder[l]];
   };
   bool bad = false;
   for (int v = tid; v < n; v += TNT) bad |= label(v) == -2;
