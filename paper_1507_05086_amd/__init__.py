@@ -69,6 +69,7 @@ class _RoundRecord(ctypes.Structure):
 
 
 _ROUND_DTYPE = np.dtype([(f, np.float64 if f == "eps_used" else np.int64) for f in TRACE_FIELDS])
+_RECORDS_KEPT = 1 << 16  # of a single graph's run; a batch records no rounds
 
 
 class _RunStats(ctypes.Structure):
@@ -243,8 +244,9 @@ def _run(fn, graph: Graph, order, eps, labels=None, trace_capacity=1 << 14, stre
     flags = (CC_INPUT_ON_DEVICE if odev else 0) | (CC_OUTPUT_ON_DEVICE if ldev else 0)
     st = _RunStats()
     rec = None
-    if trace_capacity > 0:
-        rec = np.empty(trace_capacity, dtype=_ROUND_DTYPE)  # only the rounds that ran are touched
+    if trace_capacity > 0 and graph.num_graphs == 1:
+        # only the rounds that ran are touched; rounds past the records kept stay zero
+        rec = (np.empty if trace_capacity <= _RECORDS_KEPT else np.zeros)(trace_capacity, dtype=_ROUND_DTYPE)
         st.trace = ctypes.cast(rec.ctypes.data, ctypes.POINTER(_RoundRecord))
         st.trace_capacity = trace_capacity
     st.max_rounds = int(max_rounds)
@@ -259,6 +261,8 @@ def _run(fn, graph: Graph, order, eps, labels=None, trace_capacity=1 << 14, stre
                    truncated=st.truncated, graph_rounds=gr)
     if rec is not None:
         out.trace = rec[:min(st.rounds, trace_capacity)].copy()
+    elif trace_capacity > 0:
+        out.trace = np.zeros(min(st.rounds, trace_capacity), dtype=_ROUND_DTYPE)
     return labels, out
 
 
