@@ -719,6 +719,8 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
       }
       lone += __popc(lst) << 16;  // a step adds at most 4 of each
       pos0 += (long long)tm.n * chunk;
+      // the next step scans in the same scratch (the count above parts the steps of the other rules)
+      if (binomial && pos0 < sel_end) __syncthreads();
     }
     {
       int lt, wt, x, y;
