@@ -1186,6 +1186,8 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         w.state[v] = CENTER;
         w.flag[v] = 0;
       }
+      // the next listing starts over in alist (the count exchange parts the two under the other rules)
+      if (binomial && nlong > 0 && !team_sync(tm, L)) return;
     }
     const long long now = (long long)wall_clock64();
     const int err = uni(ld(&sl->err));
