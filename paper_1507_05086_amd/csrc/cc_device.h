@@ -540,6 +540,16 @@ __device__ inline void stage_push(StageBuf<CAP> &b, int32_t v, int32_t weight) {
   b.wt[p] = weight;
 }
 
+// Whether the buffer holds more than a workgroup's worth.  Collective: every
+// thread has the same answer before any of them pushes again.
+template <int CAP>
+__device__ inline bool staged_over(const StageBuf<CAP> &b) {
+  __syncthreads();
+  const int cnt = b.cnt;
+  __syncthreads();
+  return cnt > BS;
+}
+
 // Collective: every thread of the workgroup calls it.
 template <int CAP>
 __device__ inline void stage_flush(StageBuf<CAP> &b, unsigned long long *packc, int32_t *list, int64_t *work,

@@ -141,8 +141,7 @@ __global__ void __launch_bounds__(BS) k_candidates(Ws w) {
         w.xend[v] = w.off[v];  // count_exact appends the row's unclustered neighbours
         if (d > 0) stage_push(sb, (int32_t)v, (int32_t)d);
       }
-      __syncthreads();
-      if (sb.cnt > BS) stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
+      if (vb + BS < v1 && staged_over(sb)) stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
     }
     stage_flush(sb, &c->x_pack, w.xlist, w.xwork, xacc);
     return;
@@ -187,8 +186,7 @@ __global__ void __launch_bounds__(BS) k_candidates(Ws w) {
     for (int q = 0; q < PER; q++)
       if (v[q] >= 0 && x[q] >= s.L && level_of(x[q]) == lv[q] && unc_bit(w.unc, v[q]))  // live entry, inside the band
         stage_push(sb, v[q], (int32_t)(w.rend[v[q]] - w.off[v[q]]));
-    __syncthreads();
-    if (sb.cnt > BS) stage_flush(sb, &c->r_pack[pass], list, work, acc);
+    if (i0 + PER * BS < e1 && staged_over(sb)) stage_flush(sb, &c->r_pack[pass], list, work, acc);
   }
   stage_flush(sb, &c->r_pack[pass], list, work, acc);
 }
@@ -698,8 +696,7 @@ __global__ void __launch_bounds__(BS) k_classify(Ws w) {
       base = __shfl(base, leader, 64);
       if (blocked) w.blist[base + __popcll(m & lanemask_lt())] = a;
     }
-    __syncthreads();
-    if (sb.cnt > BS) stage_flush(sb, &c->c_pack, w.clist, w.cwork, nullptr, w.cinfo, sb.info);
+    if (ib + BS < a1 && staged_over(sb)) stage_flush(sb, &c->c_pack, w.clist, w.cwork, nullptr, w.cinfo, sb.info);
   }
   stage_flush(sb, &c->c_pack, w.clist, w.cwork, nullptr, w.cinfo, sb.info);
 }
@@ -1061,8 +1058,7 @@ __global__ void __launch_bounds__(BS) k_clear(Ws w) {
         else if (d > 0) stage_push(sp, u, (int32_t)(rend[u] - w.off[u]));
       }
     }
-    __syncthreads();
-    if (sp.cnt > BS) stage_flush(sp, &c->p_pack, w.plist, w.pwork);
+    if (ib + BS < i1 && staged_over(sp)) stage_flush(sp, &c->p_pack, w.plist, w.pwork);
   }
   stage_flush(sp, &c->p_pack, w.plist, w.pwork);
   const int64_t tiles = (int64_t)h.tile_counter + 1;
