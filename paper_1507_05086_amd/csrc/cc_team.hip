@@ -848,9 +848,10 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     // round's label is below this round's ranks, so the label alone says
     // whether a neighbour can still be claimed (a vertex that k_select or the
     // selection above settled has no unclustered neighbour), and the newly
-    // clustered can leave while others still claim.
+    // clustered can leave while others still claim.  A root's own label may
+    // still be unset, so a row that holds its own vertex must not list it.
     int conf_n = 0;
-    auto claim = [&](const int32_t *u, const int32_t *rk, const bool *on, bool *broken) {
+    auto claim = [&](const int32_t *u, const int32_t *rk, const bool *on, bool *broken, auto &&row) {
       int32_t cur[TIPT];
       uint8_t su[TIPT];
 #pragma unroll
@@ -865,7 +866,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
           broken[k] = cur[k] < rk[k];  // rule 1 broken (lab = rank here)
         } else if (rk[k] < cur[k]) {
           atoms++;
-          if (atomicMin(&w.lab[u[k]], rk[k]) == INF) L.cl[atomicAdd(&L.ncl, 1)] = u[k];  // newly claimed
+          if (atomicMin(&w.lab[u[k]], rk[k]) == INF && u[k] != row(k)) L.cl[atomicAdd(&L.ncl, 1)] = u[k];  // newly claimed
         }
       }
     };
@@ -947,7 +948,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
             w.lab[a] = rk[k];
           }
         }
-        claim(u, rk, on, broken);
+        claim(u, rk, on, broken, [&](int k) { return L.lv[it.ent[k]]; });
 #pragma unroll
         for (int k = 0; k < TIPT; k++)
           if (broken[k]) {
@@ -967,7 +968,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         on[k] = ij[k] >= 0 && !(c4 && L.rmark[ij[k]]);
         rk[k] = ij[k] >= 0 ? L.rr[ij[k]] : -1;
       }
-      claim(iu, rk, on, broken);
+      claim(iu, rk, on, broken, [&](int k) { return L.rv[ij[k]]; });
       if (!c4) {
 #pragma unroll
         for (int k = 0; k < TIPT; k++)
