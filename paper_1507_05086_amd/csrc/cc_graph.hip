@@ -449,7 +449,8 @@ __global__ void __launch_bounds__(BS) k_cost_same(CostArgs a) {
 // A single graph is scored on its renumbered rows.  Every edge is stored
 // twice, and the entry whose neighbour has the lower internal id is the one
 // to look at: ids fall with the degree level, so the gathers (one per edge
-// instead of two) land mostly on the hubs' labels, which stay cached.
+// instead of two) land mostly on the hubs' labels, which stay cached.  A row's
+// own vertex (unvalidated rows may hold it) is one entry and counts as one.
 __global__ void __launch_bounds__(BS) k_cost_labels(CostArgs a, const int32_t *iperm, int32_t *lab) {
   for (int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * BS) {
     const int32_t l = a.labels[iperm[i]];
@@ -487,7 +488,7 @@ __global__ void __launch_bounds__(BS) k_cost_edges(CostArgs a, const int32_t *la
   }
   __syncthreads();
   int64_t row0 = s_row;  // the row that holds the tile's first entry
-  long long run = 0;
+  long long run = 0, loops = 0;
   for (int64_t t = t0; t < t1; t++) {
     const int64_t s = t * CE_TILE;
     const int items = (int)(nnz - s < CE_TILE ? nnz - s : CE_TILE);
@@ -532,7 +533,9 @@ __global__ void __launch_bounds__(BS) k_cost_edges(CostArgs a, const int32_t *la
 #pragma unroll
       for (int y = 0; y < 4; y++) {
         while (j + 1 < nrow && lw[j + 1] <= x + y) j++;
-        g[y] = u[k][y] < row0 + j ? lab[u[k][y]] : -1;
+        const int32_t v = (int32_t)row0 + j;
+        g[y] = u[k][y] < v ? lab[u[k][y]] : -1;
+        loops += u[k][y] == v;
         m[y] = ll[j];
       }
 #pragma unroll
@@ -543,7 +546,7 @@ __global__ void __launch_bounds__(BS) k_cost_edges(CostArgs a, const int32_t *la
     if (row0 + 1 < rows && a.off[row0 + 1] == s + CE_TILE) row0++;
     __syncthreads();
   }
-  flush_acc(a.acc, 1, 0, 2 * run);
+  flush_acc(a.acc, 1, 0, 2 * run + loops);
 }
 
 constexpr int PAIR_T = 64;  // consecutive label slots per thread

@@ -41,3 +41,18 @@ def test_c4_labels(name, every):
     order = graphgen.permutation(g.n, 5)
     lab, _ = cc.cc_c4(gh, torch.from_numpy(order).cuda(), eps)
     assert np.array_equal(lab.cpu().numpy(), oracle.kwikcluster(g.off, g.col, order))
+
+
+@pytest.mark.parametrize("every", [1, 7])
+@pytest.mark.parametrize("n", [1500, 30_011])
+def test_cost_counts_stored_entries(n, every):
+    """m and m_in are half the stored entries, a loop's one among them."""
+    import torch
+    import paper_1507_05086_amd as cc
+    g = graphgen.erdos_renyi(n, 9.0, n)
+    off, col = _with_loops(g, every)
+    gh = cc.cc_graph_from_csr(torch.from_numpy(off).cuda(), torch.from_numpy(col).cuda())
+    lab = np.random.default_rng(1).integers(0, n // 20, n).astype(np.int32)
+    size = np.bincount(lab).astype(np.int64)
+    same = int((np.repeat(lab, np.diff(off)) == lab[col]).sum())
+    assert int(cc.cc_cost(gh, torch.from_numpy(lab).cuda())[0]) == int((size * (size - 1) // 2).sum()) + len(col) // 2 - same
