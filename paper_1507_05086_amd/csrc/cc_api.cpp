@@ -530,7 +530,7 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
   w.solo = w.team_n == 1 && (w.start_exact || pol.kind == CC_EPS_BINOMIAL);
   if (w.team_n == 1 && !w.solo) w.team_n = TEAM_MAX;
   const bool solo = w.solo != 0;
-  w.labels_out = (flags & CC_OUTPUT_ON_DEVICE) ? labels : ws.label_buf;
+  if (solo) w.labels_out = (flags & CC_OUTPUT_ON_DEVICE) ? labels : ws.label_buf;
 
   // init.  The permutation check needs no host round trip: an entry out of
   // range is never used as an index, and a failed check sets the device
@@ -590,7 +590,10 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
   };
   if (w.team) {  // the first slot is a team alone
     HIP_TRY(launch_team(w, s));
-    w.solo = 0;  // what a solo run leaves (more conflict edges than fit its LDS) is for the device and a team
+    // what a solo run leaves (more conflict edges than fit its LDS) is for
+    // the device and a team, whose graphs are kept whatever the labels' buffer
+    w.solo = 0;
+    w.labels_out = nullptr;
     if (w.team_n == 1) w.team_n = TEAM_MAX;
     launched = 1;
     if (int32_t rc = wait_slots(1)) return rc;
@@ -634,7 +637,10 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     if (e == ERR_PERM) return fail(CC_ERR_NOT_PERMUTATION, "order is not a permutation of 0..n-1");
     if (e == ERR_NO_PROGRESS) return fail(CC_ERR_NO_PROGRESS, "round loop made no progress");
     if (e == ERR_OVERFLOW) return fail(CC_ERR_DEVICE, "a device work list overflowed");
-    if (e == ERR_INJECTED) return fail(CC_ERR_DEVICE, "device error injected by stats->fault_round");
+    if (e == ERR_INJECTED)  // (the test hook also tells what no result shows)
+      return fail(CC_ERR_DEVICE, "device error injected by stats->fault_round; round graphs kept: " +
+                                     std::to_string(ws.graphs.size()) + ", round slots queued: " + std::to_string(launched) +
+                                     ", counted: " + std::to_string(hc.slots));
     return fail(CC_ERR_DEVICE, "device error " + std::to_string(e) + " in the round loop");
   }
   if (out.error) return fail(CC_ERR_DEVICE, "device error " + std::to_string(out.error) + " while finishing");
