@@ -1092,6 +1092,10 @@ __global__ void __launch_bounds__(BS) k_peel(Ws w) {
 __global__ void __launch_bounds__(64) k_close(Ws w) {
   Ctrl *c = w.ctrl;
   if (c->done) return;
+  if (w.team) {  // the next k_team starts from zeroed counters, also where the round goes on: it ends the slot by them
+    unsigned *t = reinterpret_cast<unsigned *>(w.team);
+    for (int i = threadIdx.x; i < (int)(sizeof(TeamCtl) / sizeof(unsigned)); i += 64) t[i] = 0;
+  }
   if (c->has_round && c->phase == PHASE_LAZY && w.policy != POL_BINOMIAL && !c->error) {
     const int pass = c->pass;  // run by this slot, unless it switched
     if (dsearch(c, pass).pending) {
@@ -1113,10 +1117,6 @@ __global__ void __launch_bounds__(64) k_close(Ws w) {
     }
   }
   const long long now = (long long)wall_clock64();
-  if (w.team) {  // the next k_team starts from zeroed counters
-    unsigned *t = reinterpret_cast<unsigned *>(w.team);
-    for (int i = threadIdx.x; i < (int)(sizeof(TeamCtl) / sizeof(unsigned)); i += 64) t[i] = 0;
-  }
   long long lone = 0;  // centers settled by k_select
   long long xlow = 0;  // entries of lower-degree rows recounted at the switch
   {  // fold the spread statistics of the round
