@@ -44,6 +44,57 @@ __device__ inline void hist_add(int *s_hist, int *g_hist, int d, int x) {
   else atomicAdd(&g_hist[d], x);
 }
 
+// --------------------------------------------- settling the blocked ------
+// The blocked vertices of a C4 round in one workgroup's LDS.  A vertex's word
+// counts its earlier active neighbours that are not settled as non-centers:
+// 0 makes it a center, and an earlier center sets RES_NON in it (what the
+// other neighbours take off afterwards leaves it above RES_GONE).  Every
+// thread looks at its edges until each has met its earlier end settled; the
+// edges run from later to earlier ranks and every wave of the workgroup is
+// running, so some edge always can be, and no barrier is needed between one
+// level of the dependence and the next.  (The looks are bounded all the same;
+// a word that is neither then says so.)
+constexpr int RES_NON = 1 << 30, RES_GONE = 1 << 29;
+constexpr int RES_LOOKS = 1 << 24;
+
+__device__ inline int res_word(const int *word, int i) {
+  return __hip_atomic_load(&word[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// `open`: this thread's edges, bit k the edge from blocked vertex a(k) to the
+// earlier u(k) (below 0: a center); the words hold the counts.  Collective for
+// a wave, which looks at eight edges per lane together and stays with them
+// while they settle: neighbours in a chain are often listed next to each other.
+template <int EPT, class A, class U>
+__device__ __forceinline__ void settle_edges(int *word, unsigned open, A &&a, U &&u) {
+  constexpr int CH = 8;
+  for (int look = 0; __any(open) && look < RES_LOOKS; look++) {
+#pragma unroll
+    for (int k0 = 0; k0 < EPT; k0 += CH) {
+      unsigned now = open >> k0 & 0xFF, settled = now;
+      while (__any(now) && __any(settled)) {
+        settled = 0;
+        int wu[CH];
+#pragma unroll
+        for (int k = 0; k < CH; k++) wu[k] = (now >> k & 1) == 0 ? 1 : u(k0 + k) < 0 ? 0 : res_word(word, u(k0 + k));
+#pragma unroll
+        for (int k = 0; k < CH; k++)
+          if (now >> k & 1) {
+            if (wu[k] == 0) atomicOr(&word[a(k0 + k)], RES_NON);
+            else if (wu[k] >= RES_GONE) atomicSub(&word[a(k0 + k)], 1);
+            else continue;
+            settled |= 1u << k;
+          }
+        now &= ~settled;
+      }
+      open = (open & ~(0xFFu << k0)) | now << k0;
+    }
+  }
+}
+
+// After a barrier: 1 a center, 2 a non-center, 0 unsettled.
+__device__ inline int res_decision(int word) { return word == 0 ? 1 : word >= RES_GONE ? 2 : 0; }
+
 // ------------------------------------------------------------ policy ------
 
 __device__ inline long long fixed_batch(long long eps_q, long long n_rem, long long delta) {

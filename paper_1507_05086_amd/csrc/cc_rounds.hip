@@ -738,23 +738,23 @@ __device__ __forceinline__ void promote_decided(const Ws &w, Ctrl *c, int64_t nb
 
 // Up to RES_EDGES conflict edges: every thread holds its share in registers
 // (the blocked vertex and the earlier one it waits for as indices of the
-// blocked list) and the decisions are in LDS, so a level of the dependence
-// costs two barriers and no memory, where the queue below pays a chain of six
-// reads and atomics in the L2.  R-MAT 22 under the learned policy 3.65 -> 3.52
-// ms, C4 7.64 -> 7.44 ms; the limit is what fits the registers.
+// blocked list) and settles them on words in LDS (settle_edges), where the
+// queue below pays a chain of six reads and atomics in the L2 per level.  R-MAT
+// 22 under the learned policy 3.65 -> 3.52 ms, C4 7.64 -> 7.44 ms; a path of
+// 100 K in its own order, whose rounds are one chain: 113 ms by the queue, 542
+// with two barriers a level, 74 so.  The limit is what fits the LDS.
 constexpr int RES_EPT = 32, RES_EDGES = RBS * RES_EPT;
-__device__ void resolve_swept(const Ws &w, Ctrl *c, int nb, int ne, const int64_t *rend) {
-  __shared__ uint8_t dec[RES_EDGES], wait[RES_EDGES];  // (a blocked vertex has an edge)
+__device__ void resolve_edges(const Ws &w, Ctrl *c, int nb, int ne, const int64_t *rend) {
+  __shared__ int word[RES_EDGES];  // (a blocked vertex has an edge)
   const int tid = threadIdx.x;
   for (int i = tid; i < nb; i += RBS) {
     w.bpos[w.blist[i]] = i;
-    dec[i] = 0;
-    wait[i] = 0;
+    word[i] = 0;
   }
   __syncthreads();
   unsigned ed[RES_EPT];  // vertex | (earlier one + 1, 0: a center) << 16
-  unsigned open = 0;     // edges of vertices that are not decided yet
-  static_assert(RES_EDGES <= 1 << 15, "an index and a zero fit 16 bits");
+  unsigned open = 0;
+  static_assert(RES_EDGES <= 1 << 15 && RES_EDGES < RES_GONE, "an index and a zero fit 16 bits");
   constexpr int CH = 8;  // in flight
 #pragma unroll
   for (int k0 = 0; k0 < RES_EPT; k0 += CH) {
@@ -776,37 +776,16 @@ __device__ void resolve_swept(const Ws &w, Ctrl *c, int nb, int ne, const int64_
 #pragma unroll
     for (int k = 0; k < CH; k++) {
       ed[k0 + k] = (unsigned)ia[k] | (su[k] == CENTER ? 0u : (unsigned)(iu[k] + 1) << 16);
-      open |= e[k].x >= 0 ? 1u << (k0 + k) : 0u;
+      if (e[k].x < 0) continue;
+      open |= 1u << (k0 + k);
+      atomicAdd(&word[ia[k]], 1);
     }
   }
-  for (int sweep = 0; sweep <= nb; sweep++) {
-#pragma unroll
-    for (int k = 0; k < RES_EPT; k++) {
-      if (k * RBS >= ne) break;
-      if (open >> k & 1) {
-        const int a = ed[k] & 0xFFFF, u = (int)(ed[k] >> 16) - 1;
-        const int du = u < 0 ? 1 : dec[u];
-        if (dec[a] != 0 || du != 0) open &= ~(1u << k);  // settled either way by what follows
-        if (dec[a] == 0) {
-          if (du == 1) dec[a] = 2;        // an earlier center
-          else if (du == 0) wait[a] = 1;  // an earlier neighbour is open
-        }
-      }
-    }
-    __syncthreads();
-    bool any = false;
-    for (int i = tid; i < nb; i += RBS)
-      if (dec[i] == 0) {
-        if (wait[i]) {
-          wait[i] = 0;
-          any = true;
-        } else {
-          dec[i] = 1;
-        }
-      }
-    if (!__syncthreads_or(any)) break;
-  }
-  promote_decided(w, c, nb, rend, [&](int64_t i) { return (int)dec[i]; });
+  __syncthreads();
+  settle_edges<RES_EPT>(word, open, [&](int k) { return (int)(ed[k] & 0xFFFF); },
+                        [&](int k) { return (int)(ed[k] >> 16) - 1; });
+  __syncthreads();
+  promote_decided(w, c, nb, rend, [&](int64_t i) { return res_decision(word[i]); });
 }
 
 // The conflict edges are listed: build the dependence graph among the blocked
@@ -953,7 +932,7 @@ __global__ void __launch_bounds__(RBS) k_resolve(Ws w) {
   const int64_t nb = h.n_blocked;
   if (nb == 0) return;
   const int64_t ne = h.n_cedges;
-  if (ne <= RES_EDGES) resolve_swept(w, c, (int)nb, (int)ne, round_end(w, h.phase));
+  if (ne <= RES_EDGES) resolve_edges(w, c, (int)nb, (int)ne, round_end(w, h.phase));
   else if (ne <= w.cedge_cap) resolve_listed(w, c, nb, ne, round_end(w, h.phase));
   else resolve_rows(w, c, nb, round_end(w, h.phase), round_col(w, h.phase));
   __syncthreads();

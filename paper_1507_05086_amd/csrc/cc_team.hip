@@ -50,14 +50,13 @@ struct Lds {
   int32_t lv[TTW + 1];   // its vertex
   int32_t loff[TTW + 1]; // where its adjacency starts in col, less lw
   int32_t lval[TTW + 1]; // its rank, or its count (rescan)
-  int32_t cl[TCLAIM];    // newly claimed vertices; row lengths (rescan)
+  int32_t cl[TCLAIM];    // newly claimed vertices; row lengths (rescan); blocked vertices' words (resolve)
   // this workgroup's active rows: vertex, first item, start in col less that, rank
   int32_t rv[TROWS], rw[TROWS], ro[TROWS], rr[TROWS];
   uint8_t rmark[TROWS];  // blocked (C4) or in conflict (ClusterWild!)
   int32_t pw[TNT];       // rows_of_wg: prefix of row lengths, ...
   int32_t poff[TNT];     // ... row starts less the prefix ...
   int32_t pval[TNT];     // ... and a value per row
-  uint8_t dec[TEDGE], wait[TEDGE];  // resolve: decision and mark per blocked vertex
   int hist[HLDS];
   int sh[4][TNW];
   int32_t s_ent;
@@ -351,58 +350,49 @@ __device__ inline void share_of(const Team &tm, int total, int *s0, int *s1) {
 }
 
 // One workgroup settles the blocked vertices of a C4 round (rule 1: the
-// greedy MIS of G[A] in pi order, restricted to them), all in LDS: a blocked
-// vertex is a non-center once an earlier active neighbour is a center, and a
-// center once all of them are non-centers.  Each sweep decides at least the
-// lowest-ranked undecided vertex; the conflict edges stay in registers.
-// The promoted go to the center list; *work_in and *work_out get the row
-// lengths of the promoted and of all blocked vertices.
+// greedy MIS of G[A] in pi order, restricted to them): a blocked vertex is a
+// non-center once an earlier active neighbour is a center, and a center once
+// all of them are non-centers.  The conflict edges stay in registers, the
+// words of settle_edges are in the room of the newly claimed, of which there
+// are none yet.  The promoted go to the center list; *work_in and *work_out
+// get the row lengths of the promoted and of all blocked vertices.
 __device__ inline void resolve_lds(const Ws &w, Lds &L, TeamSlot *sl, int nb, int ne, const int64_t *rend,
                                    int *work_in, int *work_out) {
+  static_assert(TEDGE <= TCLAIM && TEDGE < RES_GONE, "a blocked vertex has an edge");
+  int *word = L.cl;
   for (int i = threadIdx.x; i < nb; i += TNT) {
     w.bpos[ld(&w.blist[i])] = i;
-    L.dec[i] = 0;
+    word[i] = 0;
   }
   wg_sync();
   constexpr int EPT = TEDGE / TNT;
   int ia[EPT], iu[EPT];
+  unsigned open = 0;
 #pragma unroll
   for (int k = 0; k < EPT; k++) {
     const int e = k * TNT + (int)threadIdx.x;
-    ia[k] = -1;
+    ia[k] = 0;
     iu[k] = -1;
     if (e < ne) {
       const int32_t a = ld(&w.cedge[e].x), u = ld(&w.cedge[e].y);
       const uint8_t fu = ld(&w.flag[u]);
       ia[k] = ld(&w.bpos[a]);
       if (fu) iu[k] = ld(&w.bpos[u]);  // not blocked: a root, a center already
+      open |= 1u << k;
+      atomicAdd(&word[ia[k]], 1);
     }
   }
-  for (int sweep = 0; sweep <= nb; sweep++) {
-    for (int i = threadIdx.x; i < nb; i += TNT) L.wait[i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < EPT; k++)
-      if (ia[k] >= 0 && L.dec[ia[k]] == 0) {
-        const int du = iu[k] < 0 ? 1 : L.dec[iu[k]];
-        if (du == 1) L.dec[ia[k]] = 2;
-        else if (du == 0) L.wait[ia[k]] = 1;
-      }
-    __syncthreads();
-    bool any = false;
-    for (int i = threadIdx.x; i < nb; i += TNT)
-      if (L.dec[i] == 0) {
-        if (L.wait[i]) any = true;
-        else L.dec[i] = 1;
-      }
-    if (!__syncthreads_or(any)) break;
-  }
+  __syncthreads();
+  settle_edges<EPT>(word, open, [&](int k) { return ia[k]; }, [&](int k) { return iu[k]; });
+  __syncthreads();
   int win = 0, wout = 0;
   for (int i = threadIdx.x; i < nb; i += TNT) {
     const int32_t a = ld(&w.blist[i]);
     const int32_t start = lo32(&w.off[a]), d = lo32(&rend[a]) - start;
     wout += d;
-    if (L.dec[i] == 1) {
+    const int decided = res_decision(word[i]);
+    if (decided == 0) sl->err = ERR_NO_PROGRESS;
+    if (decided == 1) {
       win += d;
       const int32_t rk = ld(&w.rank[a]);
       w.state[a] = CENTER;
@@ -417,6 +407,7 @@ __device__ inline void resolve_lds(const Ws &w, Lds &L, TeamSlot *sl, int nb, in
   }
   *work_in = win;
   *work_out = wout;
+  __syncthreads();  // the words' room is the newly claimed's again
 }
 
 }  // namespace
