@@ -29,8 +29,10 @@
 // a wave took 8 chunks per visit from the start: nearly every chunk has a
 // neighbour in the chunk before it, so the chunks in flight finished one after
 // the other.  Now a vertex is published when it is decided, a wave keeps the
-// undecided neighbours of its 64 vertices as pairs and looks at those only,
-// and the runs of chunks grow with the position.  Whole calls: R-MAT 24 10.6
+// undecided neighbours of its 64 vertices and looks at those only (at the
+// others of its own chunk in registers: a path of 100 K in its own order 119 ms
+// with a read of the label for each, 11.7 so, 11.3 by whole chunks), and the
+// runs of chunks grow with the position.  Whole calls: R-MAT 24 10.6
 // -> 2.3 ms, R-MAT 26 13.9 -> 7.4, R-MAT 20 10.1 -> 0.48, power law 4 M 31.6 ->
 // 1.1, ER 500 K 16.1 -> 0.35 ms.
 //
@@ -131,10 +133,17 @@ __device__ inline void wave_rows(const int32_t *col, unsigned long long rows, in
   }
 }
 
+__device__ inline unsigned wave_or(unsigned x) {
+  x |= dpp_mov<0x111, 0xf>(0, x);
+  x |= dpp_mov<0x112, 0xf>(0, x);
+  x |= dpp_mov<0x114, 0xf>(0, x);
+  x |= dpp_mov<0x118, 0xf>(0, x);
+  x |= dpp_mov<0x142, 0xf>(0, x);
+  x |= dpp_mov<0x143, 0xf>(0, x);
+  return lane_value((int)x, 63);
+}
 __device__ inline unsigned long long wave_or(unsigned long long x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d, 64);
-  return x;
+  return (unsigned long long)wave_or((unsigned)(x >> 32)) << 32 | wave_or((unsigned)x);
 }
 
 // Next run of chunks of this wave (AS_BATCH of them; ramp: fewer while the
@@ -160,6 +169,7 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
   const int lane = lane_id();
   __shared__ int32_t s_u[ALGO == ALGO_C4 ? AS_BS / 64 : 1][AS_PAIRS];
   __shared__ uint8_t s_j[ALGO == ALGO_C4 ? AS_BS / 64 : 1][AS_PAIRS];
+  __shared__ unsigned s_dep[ALGO == ALGO_C4 ? AS_BS / 64 : 1][2][64];
   __shared__ int s_n[AS_BS / 64];
   const int64_t nchunks = (a.n + 63) / 64;
   unsigned long long walked = 0, claimed = 0, atoms = 0, waits = 0;
@@ -224,17 +234,23 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
       claim(__ballot(won));
     } else {
       // isCenter.  A pass over the rows finds the earlier-ranked neighbours:
-      // a center decides its vertex at once, an undecided one is kept as a
-      // pair (neighbour, lane); then only the pairs are looked at again.  A
-      // vertex is published as soon as it is decided, not with its chunk.
+      // a center decides its vertex at once, an undecided one is kept: as a
+      // bit of the lane's `dep` if it is another of this chunk's vertices, whose
+      // dependences are then followed in registers, else as a pair (neighbour,
+      // lane); only the pairs are looked at again.  A vertex is published as
+      // soon as it is decided, not with its chunk.
       int32_t *pu = s_u[wave_id()];
       uint8_t *pj = s_j[wave_id()];
       int *pn = &s_n[wave_id()];
       unsigned long long undecided = __ballot(pending);
       unsigned long long again = undecided;  // rows (still) to be walked: a pair did not fit
-      unsigned long long toclaim = 0;
+      unsigned long long toclaim = 0, own = 0;  // own: the chunk's centers
+      unsigned long long dep = 0;               // earlier vertices of the chunk that this lane's waits for
       long long t0 = 0;
+      unsigned(*pd)[64] = s_dep[wave_id()];
+      pd[0][lane] = pd[1][lane] = 0;
       if (lane == 0) *pn = 0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       while (undecided) {
         unsigned long long blocked = 0, waiting = 0;
@@ -262,7 +278,10 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
 #pragma unroll
                 for (int k = 0; k < AS_K; k++) {
                   if (x[k] < 0) found |= 1ull << jj[k];  // a center
-                  if (x[k] == INF && !(blocked >> jj[k] & 1)) {
+                  if (x[k] == INF && ru[k] >= c0) {
+                    const int i = (int)(ru[k] - c0);
+                    atomicOr(&pd[i >> 5][jj[k]], 1u << (i & 31));
+                  } else if (x[k] == INF && !(blocked >> jj[k] & 1)) {
                     const int q = atomicAdd(pn, 1);
                     if (q < AS_PAIRS) {
                       pu[q] = u[k];
@@ -280,7 +299,9 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
           again = skip & ~blocked;
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
+          dep = (unsigned long long)pd[1][lane] << 32 | pd[0][lane];
         }
+        const int32_t mine = undecided >> lane & 1 ? lab_load(&a.lab[v]) : INF;
         // the pairs: decided ones go, the others close ranks
         const int np = *pn < AS_PAIRS ? *pn : AS_PAIRS;
         int out = 0;
@@ -318,18 +339,28 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
           waiting = wave_or(wait);
         }
         // a vertex claimed meanwhile has an earlier center too
-        const bool mine = undecided >> lane & 1;
-        const bool taken = mine && lab_load(&a.lab[v]) != INF;
+        const bool taken = (undecided >> lane & 1) && mine != INF;
         blocked = (blocked | __ballot(taken)) & undecided;
-        const unsigned long long centers = undecided & ~blocked & ~waiting & ~again;
-        if (centers >> lane & 1)
+        const unsigned long long held = waiting | again;
+        unsigned long long no = 0, yes = 0, left = undecided;
+        for (unsigned long long next = blocked;;) {  // what is settled settles others of the chunk, a level at a time
+          next |= __ballot((dep & own) != 0) & left;
+          const unsigned long long free = __ballot((dep & left) == 0) & left & ~(next | held);
+          if ((next | free) == 0) break;
+          no |= next;
+          yes |= free;
+          own |= free;
+          left &= ~(next | free);
+          next = 0;
+        }
+        if (yes >> lane & 1)
           __hip_atomic_store(&a.lab[v], -(int32_t)p - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else if ((blocked >> lane & 1) && !taken)
+        else if ((no >> lane & 1) && !taken)
           atomicMin(&a.lab[v], LAB_NONCENTER);
-        undecided &= ~(blocked | centers);
+        undecided = left;
         again &= undecided;
-        toclaim |= centers;
-        if ((blocked | centers) == 0 || undecided == 0) {
+        toclaim |= yes;
+        if ((no | yes) == 0 || undecided == 0) {
           if (toclaim) {  // nothing more to decide for now
             claim(toclaim);
             toclaim = 0;
