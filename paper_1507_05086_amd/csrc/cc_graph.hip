@@ -528,7 +528,7 @@ __global__ void __launch_bounds__(BS) k_cost_edges(CostArgs a, const int32_t *la
 #pragma unroll
     for (int k = 0; k < CE_K; k++) {
       const int x = (k * BS + (int)threadIdx.x) * 4;
-      int j = lds_last_le(lw, nrow, x < items ? x : 0);
+      int j = lds_last_le(lw, nrow, x < items ? x : items - 1);  // (behind the end: no rows to step over)
       int32_t g[4], m[4];
 #pragma unroll
       for (int y = 0; y < 4; y++) {
