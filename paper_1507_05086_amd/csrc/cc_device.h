@@ -187,6 +187,13 @@ constexpr long long TEAM_POS = 1 << 18;     // positions of pi to pass
 constexpr long long TEAM_ITEMS = 1 << 18;   // entries that claims and peeling are expected to walk
 constexpr long long TEAM_WORK = 1 << 20;    // entries of a Delta pass's candidates
 constexpr long long TEAM_SCAN = 1 << 18;    // entries of the bound levels to look through
+// A round's positions go to the workgroups 64 at a time, so that a short round
+// keeps most of them out of its counts.  What an active vertex claims stays
+// with its workgroup, though, so where more entries than this are expected
+// the positions are dealt singly.  ClusterWild! on ER 5 K of degree 300 (seven
+// active, 130 K entries a round) 1.80 -> 0.96 ms, R-MAT 16 in its own order 2.11
+// -> 1.46; 2 K / 8 K / 32 K: ER 5 K 0.95 / 0.96 / 1.00, R-MAT 16 1.47 / 1.48 / 1.80.
+constexpr long long TEAM_SPREAD = 8192;
 // A graph of at most this many vertices and stored entries runs whole in one
 // workgroup (SOLO): C4 on 517 vertices and 14 K entries takes 256 us so, 356
 // us on 8 workgroups and 377 us on 32; ClusterWild! on 5 K and 60 K, 467, 446

@@ -62,7 +62,7 @@ struct Lds {
   int32_t s_ent;
   unsigned long long s_base;
   int32_t lbase[NLVL + 1];
-  int ncl, ok, smax, nrow, nitem;
+  int ncl, ok, smax;
   unsigned n, me;
 };
 
@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
   bool done = false;
   const bool bounded = w.max_rounds > 0;
   long long rounds = 0;  // run here
-  float rate = 0.f;
+  float rate = ld(&c->rate);  // entries walked per active vertex, the round before
   for (unsigned rr = 0;; rr++) {
     TeamSlot *sl = &tm.t->slot[rr & 3];
     const bool exact = phase == PHASE_EXACT;
@@ -583,11 +583,8 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     const long long sel_end = binomial ? (cursor + B < n ? cursor + B : n) : n;
     long long taken = 0, pos0 = cursor;
     int lone = 0;
-    if (tid == 0) {
-      L.ncl = 0;
-      L.nrow = 0;
-      L.nitem = 0;
-    }
+    if (tid == 0) L.ncl = 0;
+    const bool spread = (double)B * rate > (double)TEAM_SPREAD;
     for (int i = tid; i < HLDS; i += TNT) L.hist[i] = 0;
     int nrow = 0, nitem = 0, wlong = 0;  // rows kept here, their items; items of the long rows listed here
     while (pos0 < sel_end && (binomial || taken < B)) {
@@ -597,7 +594,8 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         const long long est = (long long)((double)(B - taken) * per * 1.0625) + 64;
         need = est < need ? est : need;
       }
-      int chunk = need >= (long long)4 * TNT * tm.n ? 4 * TNT : (((int)need + (int)tm.n - 1) / (int)tm.n + 63) / 64 * 64;
+      int chunk = need >= (long long)4 * TNT * tm.n ? 4 * TNT : ((int)need + (int)tm.n - 1) / (int)tm.n;
+      if (!spread || chunk > 64) chunk = (chunk + 63) / 64 * 64;
       if (chunk > 4 * TNT) chunk = 4 * TNT;
       const int q = (chunk + TNT - 1) / TNT;
       int32_t vv[4], rs[4], dg[4];
