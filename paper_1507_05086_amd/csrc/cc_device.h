@@ -187,6 +187,11 @@ constexpr long long TEAM_POS = 1 << 18;     // positions of pi to pass
 constexpr long long TEAM_ITEMS = 1 << 18;   // entries that claims and peeling are expected to walk
 constexpr long long TEAM_WORK = 1 << 20;    // entries of a Delta pass's candidates
 constexpr long long TEAM_SCAN = 1 << 18;    // entries of the bound levels to look through
+// Entries of the listed active rows (over TLONG each, or more rows than fit the
+// LDS) at which the round is left to the device after all: TEAM_ITEMS goes by
+// the mean, and the active may be hubs.  2000 rows of 10 K entries at once: C4
+// 2.9 ms on the team, 0.67 so; a star of 2 M, the hub first: 0.95, 0.44.
+constexpr int TEAM_ACTIVE = 1 << 19;
 // A round's positions go to the workgroups 64 at a time, so that a short round
 // keeps most of them out of its counts.  What an active vertex claims stays
 // with its workgroup, though, so where more entries than this are expected

@@ -738,6 +738,29 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     const unsigned long long lp = uni(ld(&sl->listed)), ap = uni(ld(&sl->a_pack));
     const int na = (int)(lp & 0xFFFFFFFFull), lones = (int)(lp >> 32);
     const int nlong = (int)pk_cnt(ap), along = (int)pk_work(ap);
+    // Lists every active row for the round kernels; false when a wait has expired.
+    auto list_all = [&]() {
+      if (tid == 0) L.s_base = nrow > 0 ? atomicAdd(&sl->a_pack, pk(nitem, nrow)) : 0;
+      __syncthreads();
+      const unsigned long long b0 = L.s_base;
+      for (int i = tid; i < nrow; i += TNT) {
+        const int d = (i + 1 < nrow ? L.rw[i + 1] : nitem) - L.rw[i];
+        w.alist[pk_cnt(b0) + i] = L.rv[i];
+        w.awork[pk_cnt(b0) + i] = pk_work(b0) + L.rw[i];
+        w.ainfo[pk_cnt(b0) + i] = RowInfo{L.ro[i] + L.rw[i], d, L.rr[i]};
+      }
+      if (!team_sync(tm, L)) return false;
+      if (lead) {
+        c->a_pack = ld(&sl->a_pack);
+        c->spread_lone[0] += (unsigned long long)lones;
+      }
+      return true;
+    };
+    if (!SOLO && along > TEAM_ACTIVE) {  // hubs: far more than the rate said
+      if (!list_all()) return;
+      stage = ST_ELECT;
+      break;
+    }
     // this workgroup's share of the long rows' items
     int s0, s1, first = 0;
     share_of(tm, along, &s0, &s1);
@@ -811,22 +834,9 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
       if (!team_sync(tm, L)) return;
       ne = uni((int)ld(&sl->n_cedges));
       nb = uni((int)ld(&sl->n_blocked));
-      if (ne > TEDGE) {  // settled by k_resolve: list every row
-        if (tid == 0) L.s_base = nrow > 0 ? atomicAdd(&sl->a_pack, pk(nitem, nrow)) : 0;
-        __syncthreads();
-        const unsigned long long b0 = L.s_base;
-        for (int i = tid; i < nrow; i += TNT) {
-          const int d = (i + 1 < nrow ? L.rw[i + 1] : nitem) - L.rw[i];
-          w.alist[pk_cnt(b0) + i] = L.rv[i];
-          w.awork[pk_cnt(b0) + i] = pk_work(b0) + L.rw[i];
-          w.ainfo[pk_cnt(b0) + i] = RowInfo{L.ro[i] + L.rw[i], d, L.rr[i]};
-        }
-        if (!team_sync(tm, L)) return;
-        if (lead) {
-          c->a_pack = ld(&sl->a_pack);
-          c->n_cedges = (unsigned)ne;
-          c->spread_lone[0] += (unsigned long long)lones;
-        }
+      if (ne > TEDGE) {  // settled by k_resolve
+        if (!list_all()) return;
+        if (lead) c->n_cedges = (unsigned)ne;
         stage = ST_CLASSIFY;
         break;
       }
