@@ -220,8 +220,13 @@ __global__ void __launch_bounds__(AS_BS) k_async(AsyncArgs a) {
               const int32_t pj = (int32_t)(c0 + jj[k]);
               claimed += u[k] >= 0;
               if (x[k] > pj) {  // stale reads are safe: a label only decreases
-                atomicMin(&a.lab[u[k]], pj);
-                atoms++;
+                // a hub met by many rows of the wave: the first has the lowest rank
+                const bool again = u[k] == __builtin_amdgcn_readfirstlane(u[k]) &&
+                                   lane != __builtin_amdgcn_readfirstlane(lane);
+                if (!again) {
+                  atomicMin(&a.lab[u[k]], pj);
+                  atoms++;
+                }
               }
             }
           },
