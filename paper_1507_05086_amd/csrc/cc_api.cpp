@@ -548,7 +548,7 @@ int32_t run_loop(cc_graph *g, int algo, const int32_t *order, double eps, int32_
     HIP_TRY(launch_init(w, s));
   }
 
-  LaunchShape ls{512, 1024, 512, 0, w.start_exact};
+  LaunchShape ls{512, 1024, 512, w.start_exact};
   // the fixed rule clusters a vertex every round; the practical schedule's
   // rounds may be empty, and it has as many as it drew
   const int64_t round_limit = pol.kind == CC_EPS_BINOMIAL ? std::max<int64_t>(n, w.sched_len) : n;

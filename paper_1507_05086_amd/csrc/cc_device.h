@@ -297,11 +297,11 @@ struct Ws {
   // progress word in pinned host memory, written by k_close at the end of
   // every round slot: slots finished (bits 0..31), done (32), exact phase
   // (33), error (34); by k_team where there is one, which also says whether it
-  // leaves a round to the round kernels (35) and has run one itself (36)
+  // has run a round itself (35)
   unsigned long long *progress;
 };
 
-constexpr int PROGRESS_DONE = 32, PROGRESS_EXACT = 33, PROGRESS_ERROR = 34, PROGRESS_LEFT = 35, PROGRESS_RAN = 36;
+constexpr int PROGRESS_DONE = 32, PROGRESS_EXACT = 33, PROGRESS_ERROR = 34, PROGRESS_RAN = 35;
 
 __host__ __device__ inline int level_of(int64_t x) {  // floor(log2(x)), x >= 1
   return 63 - __builtin_clzll((unsigned long long)x);
@@ -310,16 +310,8 @@ __host__ __device__ inline int level_of(int64_t x) {  // floor(log2(x)), x >= 1
 // ------------------------------------------------------------- atomics ----
 
 template <class T>
-__device__ inline T ld_acq(T *p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
 __device__ inline T ld_rlx(T *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
-__device__ inline void st_rel(T *p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Relaxed device-scope atomic store: coherent across the XCDs like any
 // device-scope atomic, without the release's write-back of the whole L2.
@@ -413,27 +405,8 @@ __device__ inline T wg_excl_scan(T x, T *total, T *sh) {
   return base + inc - x;
 }
 
-// Append the calling lanes' vertices (pred true) to a packed list, one atomic
-// per wave.  weight = max(deg, 1) of the vertex.
-__device__ inline void wave_append(bool pred, int32_t v, int64_t weight, unsigned long long *packc,
-                                   int32_t *list, int64_t *work) {
-  const unsigned long long m = __ballot(pred);
-  if (m == 0) return;
-  const int64_t w = pred ? weight : 0;
-  const int64_t winc = wave_incl_scan(w);
-  const int64_t wtot = lane_value(winc, 63);
-  const int leader = __ffsll((long long)m) - 1;
-  unsigned long long base = 0;
-  if (lane_id() == leader) base = atomicAdd(packc, pk(wtot, __popcll(m)));
-  base = (unsigned long long)from_lane((int64_t)base, leader);
-  if (pred) {
-    const int64_t slot = pk_cnt(base) + __popcll(m & lanemask_lt());
-    list[slot] = v;
-    work[slot] = pk_work(base) + winc - w;
-  }
-}
-
-// wave_append for a list that carries row info (weight = max(deg, 1)).
+// Appends the calling lanes' vertices (pred true) and their row info to a
+// packed list, one atomic per wave (weight = max(deg, 1)).
 __device__ inline void wave_append_info(bool pred, int32_t v, RowInfo ri, unsigned long long *packc, int32_t *list,
                                         int64_t *work, RowInfo *info) {
   const unsigned long long m = __ballot(pred);

@@ -10,7 +10,6 @@ struct LaunchShape {
   unsigned select_grid;  // workgroups of the active-set scan
   unsigned edge_grid;    // workgroups of the edge-balanced passes
   unsigned vertex_grid;  // workgroups of per-vertex list passes
-  unsigned scan_grid;    // unused
   int exact_seen;        // the host saw the run switch to exact degrees
 };
 

@@ -420,7 +420,7 @@ __device__ inline void end_slot(const Ws &w, Ctrl *c, bool done, bool ran, bool 
   c->slots = slots;
   if (!w.progress) return;
   __hip_atomic_store(w.progress, (unsigned long long)(unsigned)slots |
-                                     1ull << (done ? PROGRESS_DONE : PROGRESS_LEFT) |
+                                     (unsigned long long)done << PROGRESS_DONE |
                                      (unsigned long long)ran << PROGRESS_RAN |
                                      (unsigned long long)(phase == PHASE_EXACT) << PROGRESS_EXACT |
                                      (unsigned long long)error << PROGRESS_ERROR,
@@ -552,7 +552,6 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
   const bool binomial = w.policy == POL_BINOMIAL;
   const int tid = threadIdx.x;
   const bool lead = tm.me == 0 && tid == 0;
-  constexpr bool alone = SOLO;
   // the round prepared by the kernel before this one
   long long n_rem = ld(&c->n_rem), delta = ld(&c->delta), B = ld(&c->b), cursor = ld(&c->cursor);
   long long round = ld(&c->round), r_last = ld(&c->r_last), t_start = ld(&c->t_start);
@@ -1074,7 +1073,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         const int tot = uni(L.lbase[NLVL]);
         // entries are only ever added between the barriers that follow, so
         // every workgroup sees the same counts here
-        if (!alone && tot > TEAM_SCAN) {
+        if (tot > TEAM_SCAN) {
           to_device = true;
           break;
         }
@@ -1110,7 +1109,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
         if (!team_sync(tm, L)) return;
         const unsigned long long rp = uni(ld(&sl->r_pack[pass]));
         const int rcnt = (int)(pk_cnt(rp) < w.rcap ? pk_cnt(rp) : w.rcap), rwk = (int)pk_work(rp);
-        if (!alone && rwk > TEAM_WORK) {
+        if (rwk > TEAM_WORK) {
           to_device = true;
           break;
         }
@@ -1280,7 +1279,7 @@ __global__ void __launch_bounds__(TNT) k_team(Ws w) {
     }
     B = b;
     t_start = now;
-    if (!alone) {
+    if (!SOLO) {
       stage = next_stage(w, B, cursor, n_rem, rate);
       if (stage != ST_TEAM) break;
     }
