@@ -94,7 +94,7 @@ typedef struct cc_run_stats {
   int64_t atomics;       /* out: atomic read-modify-writes (claims, degree decrements, bit clears) */
   double loop_ms;        /* out: device time of the round loop (HIP events on `stream`) */
   int32_t policy_fallback; /* out: 1 if the learned policy fell back to the fixed rule */
-  int32_t truncated;       /* out: 1 if more rounds ran than trace_capacity */
+  int32_t truncated;       /* out: 1 if more rounds ran than trace_capacity, or than the 65536 kept */
   cc_round_record *trace;  /* in: host buffer of trace_capacity records, or NULL */
   int64_t trace_capacity;  /* in */
   int32_t *graph_rounds;   /* in: host int32[num_graphs] receiving each graph's rounds

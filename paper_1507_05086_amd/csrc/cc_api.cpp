@@ -834,10 +834,10 @@ int32_t check_shape(const cc_graph *g, const cc_batch_config &c) {
 // The shape of a handle that was not tuned.  The largest graph bounds the
 // launch unless there are many, and more threads finish it sooner, so the
 // block is 1024.  With more than four graphs per compute unit the middle ones
-// run four to a workgroup.  Planted-block batches, (256, 512, 0) / this, when
-// rows were walked edge-balanced: 16 graphs 0.61 / 0.31 ms, 301 0.89 / 0.44,
-// 1000 2.52 / 0.71, 4096 3.60 / 1.17 (C4); at 4096 (1024, 256, 1024) took 1.48
-// ms and at 301 (1024, 384, 1792) 0.51.
+// run four to a workgroup.  Planted-block batches, C4 calls, (256, 512, 0) /
+// (1024, 256, 1024) / (1024, 384, 1792): 16 graphs 0.37 / 0.25 / 0.29 ms, 301
+// 0.47 / 0.28 / 0.32, 1000 1.49 / 0.58 / 0.58, 4096 2.08 / 1.14 / 0.85;
+// ClusterWild! 301 0.43 / 0.22 / 0.24, 4096 2.01 / 0.77 / 0.73.
 cc_batch_config default_shape(const cc_graph *g) {
   return g->num_graphs > 1024 ? cc_batch_config{1024, 384, 1792, 0, 0.0} : cc_batch_config{1024, 256, 1024, 0, 0.0};
 }

@@ -32,9 +32,9 @@
 // undecided neighbours of its 64 vertices and looks at those only (at the
 // others of its own chunk in registers: a path of 100 K in its own order 119 ms
 // with a read of the label for each, 11.7 so, 11.3 by whole chunks), and the
-// runs of chunks grow with the position.  Whole calls: R-MAT 24 10.6
-// -> 2.3 ms, R-MAT 26 13.9 -> 7.4, R-MAT 20 10.1 -> 0.48, power law 4 M 31.6 ->
-// 1.1, ER 500 K 16.1 -> 0.35 ms.
+// runs of chunks grow with the position.  Whole calls: R-MAT 24 11.3
+// -> 2.26 ms, R-MAT 26 13.9 -> 7.3, R-MAT 20 9.2 -> 0.42, power law 3 M 25.7 ->
+// 0.81, ER 3 M 19.7 -> 0.75 ms.
 //
 // Progress: chunks are handed out in pi order (a run of consecutive chunks
 // per visit to the counter, worked through in order), and a vertex waits

@@ -181,7 +181,11 @@ struct RowInfo {
 // / 11.8 ms, TEAM_POS 2^16 / 2^18 / 2^20: R-MAT 22 C4 9.1 / 7.65 / 7.65 ms,
 // learned 3.8 / 3.7 / 4.0 ms.  Graphs above TEAM_MAX_N vertices stay with the
 // kernels: R-MAT 23 C4 11.1 -> 10.9 ms with a team, R-MAT 22 9.8 -> 7.3, but
-// R-MAT 24 14.1 -> 14.2 and R-MAT 26 (C4 + ClusterWild!) 56.6 -> 61 ms.
+// R-MAT 24 14.1 -> 14.2 and R-MAT 26 (C4 + ClusterWild!) 56.6 -> 61 ms.  The line
+// is not right for every run below it: with 2^21 instead of 2^23 R-MAT 22 under
+// the learned policy takes 3.16 ms (3.47) and C4 on power law 4 M 5.65 (5.91),
+// since most of their rounds are wide, and a slot for a single round costs more
+// than a quarter of a graph of four.
 constexpr int64_t TEAM_MAX_N = int64_t(1) << 23;
 constexpr long long TEAM_POS = 1 << 18;     // positions of pi to pass
 constexpr long long TEAM_ITEMS = 1 << 18;   // entries that claims and peeling are expected to walk

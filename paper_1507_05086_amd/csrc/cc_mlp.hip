@@ -47,8 +47,9 @@ __device__ inline float wave_fsum(float x) {
 // Samples a wave of k_mlp_grad works on at a time: each is a chain of six
 // shuffles, so one at a time left the wave waiting.  With the rows that
 // k_mlp_adam adds read 32 at a time, a training step on 300 K samples 305 ->
-// 87 us, 20 K 102 -> 44 us, 1200 35 -> 34 us.  k_mlp_forward has enough waves
-// for one sample each at a time (300 K: 43 us so, 44 us with four).
+// 87 us, 20 K 102 -> 44 us; 1200 samples take 31 us either way.  k_mlp_forward
+// has enough waves for one sample each at a time (300 K: 43 us so, 44 us with
+// four).
 constexpr int MLP_U = 4;
 
 __device__ inline void wave_fsums(float (&x)[MLP_U]) {

@@ -10,17 +10,18 @@
 //   elect     C4: does an active vertex have an earlier-ranked active
 //             neighbour?  (concurrency rule 1; edge-balanced)
 //   classify  C4: roots become centers, the others are blocked
-//   resolve   C4: one workgroup settles the blocked vertices as a fixed point
-//             over the conflict edges (the greedy MIS of G[A] in pi order)
+//   resolve   C4: one workgroup settles the blocked vertices over the conflict
+//             edges (the greedy MIS of G[A] in pi order)
 //   claim     every center claims its unclustered neighbours with atomicMin on
 //             the center rank (concurrency rule 2, createCluster)
 //   clear     the newly clustered leave the unclustered bitmap
-//   peel      exact phase only: neighbours of the newly clustered lose one
+//   candidates / degrees   lazy phase: a pass of the search for the next Delta
+//             from stale upper bounds, which rescans only rows in a band below
+//             the current Delta (a pass per slot); at the end of the phase,
+//             the switch to exact degrees
+//   peel      exact phase: neighbours of the newly clustered lose one
 //             remaining degree each (degree histogram kept per workgroup)
-//   dscan / rescan (x3)   lazy phase: the next Delta from stale upper bounds,
-//             rescanning only candidates in a band below the current Delta
-//   xlist / xcount        switch to exact degrees when the band gets low
-//   close     one workgroup: round record, Delta_{i+1}, B_{i+1}, counters
+//   close     one wave: round record, Delta_{i+1}, B_{i+1}, counters
 //
 // The paper deletes lazily (clustered vertices are skipped, the graph is never
 // changed); here that extends to the remaining degrees: while Delta is large

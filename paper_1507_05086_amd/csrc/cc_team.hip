@@ -6,11 +6,14 @@
 // and then a chain of accesses that the launch has made cold (the L2 does
 // not keep other XCDs' writes, so each goes to the Infinity Cache or HBM).
 // The compute units of one XCD share an L2: a barrier over their 32
-// workgroups takes 1.1 - 1.7 us, against 4.3 us over all 8 XCDs, and what one
-// workgroup stores the others read back from that L2 in 0.1 - 0.2 us.  So the
-// rounds whose lists are short enough for an eighth of the device run here,
-// five to seven barriers a round, and the others on the whole device as
-// kernels (cc_rounds.hip); next_stage() and the limits below draw the line.
+// workgroups takes 1.1 - 1.7 us, and what one workgroup stores the others read
+// back from that L2 in 0.1 - 0.2 us.  (Over all 8 XCDs the same barrier takes
+// 4.2 us with 256 workgroups and 14 with the 1024 of a round kernel, and 30 and
+// 117 with the fences that make one XCD's stores visible to the others.)  So
+// the rounds whose lists are short enough for an eighth of the device run here,
+// with two to five barriers a round and two more for each Delta pass, and the
+// others on the whole device as kernels (cc_rounds.hip); next_stage() and its
+// limits draw the line.
 //
 // Team.  The launch puts one workgroup on every compute unit.  The first to
 // start picks its XCD; the workgroups of that XCD register until the wanted
