@@ -105,7 +105,9 @@ typedef struct cc_run_stats {
   int64_t fault_round;     /* in: 0 in normal use.  Test hook of the error path (single
                               graphs): k > 0 makes the device report an error at the end of
                               round k, as a failing round would, so the call returns
-                              CC_ERR_DEVICE with every kernel having exited normally */
+                              CC_ERR_DEVICE with every kernel having exited normally; its
+                              text also tells the round graphs kept and the round slots
+                              queued and counted */
   int64_t async_waves;     /* in: asynchronous calls only.  0 fills the device; k > 0 runs
                               k waves (1: pi strictly in order, 64 positions at a time, which
                               makes ClusterWild!'s interleaving reproducible) */
