@@ -194,7 +194,8 @@ constexpr long long TEAM_SCAN = 1 << 18;    // entries of the bound levels to lo
 // Entries of the listed active rows (over TLONG each, or more rows than fit the
 // LDS) at which the round is left to the device after all: TEAM_ITEMS goes by
 // the mean, and the active may be hubs.  2000 rows of 10 K entries at once: C4
-// 2.9 ms on the team, 0.67 so; a star of 2 M, the hub first: 0.95, 0.44.
+// 2.9 ms on the team, 0.67 so; a star of 2 M, the hub first: 0.95, 0.44.  2^17 to
+// 2^21 are alike there and on R-MAT 20, power law 500 K and 3 M (within 1 %).
 constexpr int TEAM_ACTIVE = 1 << 19;
 // A round's positions go to the workgroups 64 at a time, so that a short round
 // keeps most of them out of its counts.  What an active vertex claims stays
